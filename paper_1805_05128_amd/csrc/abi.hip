@@ -119,11 +119,11 @@ size_t ws_layout(Ws *w, void *base, int64_t n, int64_t ncell, bool rk2, int64_t 
     t.perm = (int32_t *)take(sizeof(int32_t) * un);
     t.bin_tmp = (int32_t *)take(sizeof(int32_t) * un);
     t.cnt = (int32_t *)take(sizeof(int32_t) * un);
-    // A records: FP64 (32 B each) or FP32 (16 B), each followed by two zero records
+    // A records: FP64 (two arrays of 16 B) or FP32 (16 B, followed by kRecPad zero records)
     t.recA = take(32 * (un + 2));
     t.recB = take(32 * un);
     t.recC = take(16 * un);
-    t.recF = take(16 * (un + 2));  // followed by two zero records, as the mixed A records
+    t.recF = take(16 * (un + 2));  // followed by kRecPad zero records
     t.recD = take(32 * un);
     t.recE = (double *)take(sizeof(double) * un);
     t.eos_part = (double *)take(sizeof(double) * 2 * CSPH_MAX_EOS * ((un + kBlock - 1) / kBlock + 1));
@@ -1134,7 +1134,7 @@ csph_status csph_vlist_build(const csph_state *s_in, csph_state *s_out, const cs
     {
         ProfScope pr(CSPH_PROF_NEIGHBORS, st);
         CSPH_HIP(launch_fill_u64((unsigned long long *)w.nonphys, 0ull, 1, st));
-        CSPH_HIP(launch_vlist(n, (const double4 *)w.recA, w.cs, gd, R, p->wall, yw, cap,
+        CSPH_HIP(launch_vlist(n, w.recA, w.cs, gd, R, p->wall, yw, cap,
                               vl_count, vl_idx, (unsigned long long *)w.nonphys, st));
         const double *ref[3] = {s_out->x, s_out->y, s_out->z};  // the caller's axes
         for (int a = 0; a < 3; ++a)
@@ -1376,9 +1376,9 @@ static csph_status vjp_common(const csph_state *s_in, const csph_params *p, doub
         int32_t *flag = w.bin_tmp;             // free after the binning
         unsigned long long *reach = w.yenc;    // unused without a caller's mesh
         // the change a reflection would make, formed before the first pass writes g (which
-        // may alias the cotangent), in the FP32 candidate records the adjoint does not read;
-        // the signal-speed array (no rate evaluation here) takes the rate sums, then zeros
-        double *dy = (double *)w.recF, *dvy = dy + n, *svy = w.sig;
+        // may alias the cotangent), in rate arrays (no rate evaluation here), the signal-speed
+        // array takes the rate sums, then zeros
+        double *dy = w.rate[0], *dvy = w.rate[1], *svy = w.sig;
         CSPH_HIP(launch_reflect_delta(n, gn[1], gn[4], gn[7], p->wall_v, dy, dvy, st));
         CSPH_HIP(launch_fill_u64(reach, 0ull, 1, st));
         CSPH_HIP(launch_vjp_wall(n, w.perm, w.cs, gd, pc, eos, w, w.srt, w.srt_mat, nullptr, go,
@@ -1418,9 +1418,9 @@ static csph_status vjp_common(const csph_state *s_in, const csph_params *p, doub
                                    p->wall_x0 + p->wall_v * (t + dt), p->wall_v, info, st));
     }
     if (wall && gnext) {
-        // (the CFL step) the cotangents of the pre-reflection y and v_y go to the FP32
-        // candidate records, which only the rate evaluation above reads (2 n + 4 doubles)
-        double *gy = (double *)w.recF, *gvy = gy + n;
+        // (the CFL step) the cotangents of the pre-reflection y and v_y, in rate arrays that
+        // are used up (launch_dt_adjoint has read them; the reflection's test reads rate[2])
+        double *gy = w.rate[0], *gvy = w.rate[1];
         const double yw1 = p->wall_x0 + p->wall_v * (t + dt);
         CSPH_HIP(launch_vjp_reflect(n, w.perm, w.srt[1], w.srt[4], w.rate[2], dt, yw1, p->wall_v,
                                     gn[1], gn[4], gn[7], gy, gvy, st));

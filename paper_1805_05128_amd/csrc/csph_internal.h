@@ -231,9 +231,9 @@ struct Ws {
     int64_t *scan_tmp;            // scan tiles
     int32_t *perm;                // n
     int32_t *bin_tmp;             // n: cell order before the in-cell ranking (binning only)
-    void *recA, *recB, *recC;     // pair records (FP64: 32+32+16 B; mixed: 16+16+8 B)
+    void *recA, *recB, *recC;     // pair records (FP64: 2x16, 2x16, 16 B arrays; mixed: 16 B each)
     void *recF;                   // FP64 stencil walks: cell-relative FP32 records (16 B)
-    void *recD;                   // adjoint pair weights (32 B)
+    void *recD;                   // adjoint pair weights (2x16 B)
     double *recE;                 // adjoint energy weight
     double *eos_part;             // per-block EOS-parameter gradients, ceil(n/kBlock) * 16
     double *srt[9];               // sorted state copy x y z vx vy vz rho E m
@@ -298,7 +298,7 @@ hipError_t launch_vl_guard(csph_vlist_ctl *ctl, const double *t, hipStream_t st)
 hipError_t launch_copy_i32(int32_t *dst, const int32_t *src, int64_t n, const int32_t *gate,
                            hipStream_t st);
 // k_vlist.hip
-hipError_t launch_vlist(int64_t n, const double4 *A, const int32_t *cs, const GridDev &g,
+hipError_t launch_vlist(int64_t n, const void *recA, const int32_t *cs, const GridDev &g,
                         double R, int wall, double yw, int cap, int32_t *count, int32_t *idx,
                         unsigned long long *over, hipStream_t st);
 hipError_t launch_disp(int64_t n, const double *x, const double *y, const double *z,

@@ -27,15 +27,17 @@
 namespace csph {
 
 struct VjpIn {
-    const double4 *A;   // x y z V      (cell order)
-    const double4 *B;   // vx vy vz P
+    Split4 A;           // x y z V      (cell order)
+    Split4 B;           // vx vy vz P
     const double2 *C;   // Z c
-    const double4 *Dw;  // b_rho b_vx b_vy b_vz
+    Split4 Dw;          // b_rho b_vx b_vy b_vz
+    const float4 *F;    // cell-relative FP32 records (the candidate test)
+    const unsigned long long *zflag;  // 0: some impedance is zero (see k_pack)
     const double *Ew;   // b_E
     const double *rho, *E, *m;  // sorted state
     const int32_t *mat;
-    const double *a[5]; // rate cotangents (cell order): rho vx vy vz E
     const double *dsz;  // pair-h mode: particle sizes d (cell order, constants of the map)
+    const float *d32;   // the same in FP32 (the candidate test)
 };
 
 // The piston at the time of the rates: position along the kernels' y, twice its velocity.
@@ -52,7 +54,7 @@ struct VjpOut {
     double *eos_part;   // [gridDim.x][2*CSPH_MAX_EOS]
 };
 
-// Rate cotangents and pair weights in cell order.  For a step VJP the
+// Pair weights of the rate cotangents in cell order.  For a step VJP the
 // cotangents follow from the next-state cotangent gn: a_rho = dt g_rho',
 // a_v = dt (g_v' + dt g_r'), a_E = dt g_E'.
 __global__ __launch_bounds__(kBlock) void k_vjp_weights(int64_t n,
@@ -61,9 +63,7 @@ __global__ __launch_bounds__(kBlock) void k_vjp_weights(int64_t n,
                                                         VjpOut o, const double *a_in0,
                                                         const double *a_in1, const double *a_in2,
                                                         const double *a_in3, const double *a_in4,
-                                                        double *a0, double *a1, double *a2,
-                                                        double *a3, double *a4,
-                                                        double4 *__restrict__ Dw,
+                                                        double2 *__restrict__ Dw,
                                                         double *__restrict__ Ew) {
     int64_t s = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (s >= n) return;
@@ -83,14 +83,10 @@ __global__ __launch_bounds__(kBlock) void k_vjp_weights(int64_t n,
         az = a_in3[i];
         aE = a_in4[i];
     }
-    a0[s] = ar;
-    a1[s] = ax;
-    a2[s] = ay;
-    a3[s] = az;
-    a4[s] = aE;
     double r = rho_s[s];
     double k = 2.0 / r;
-    Dw[s] = make_double4(-2.0 * r * ar, k * ax, k * ay, k * az);
+    Dw[s] = make_double2(-2.0 * r * ar, k * ax);
+    Dw[n + s] = make_double2(k * ay, k * az);
     Ew[s] = k * aE;
 }
 
@@ -134,16 +130,36 @@ __device__ __forceinline__ void mg_eos_dual(const EosDev &eos, int k, double rho
     c2 = dPr + g * (e - er) - g * rder + g * P / rho;
 }
 
-// Sums a particle gathers over its partners.
+// Sums a particle gathers over its partners: dPhi/dq, T the rates' part of the prefactor
+// terms (sum_j V_j W' (b_rho (v_L - v*) - P* (b_v.e + b_E v*))), Sv1 the y-momentum rate sum
+// (the piston's step VJP).
 struct VjpAcc {
     double gr0 = 0, gr1 = 0, gr2 = 0, gv0 = 0, gv1 = 0, gv2 = 0, gP = 0, gZ = 0, gV = 0;
-    double Sr = 0, Sv0 = 0, Sv1 = 0, Sv2 = 0, SE = 0;
+    double T = 0, Sv1 = 0;
+    // ties each sum to one register at the end of a drain (as the rate kernels' settle)
+    __device__ __forceinline__ void settle() {
+        asm volatile(""
+                     : "+v"(gr0), "+v"(gr1), "+v"(gr2), "+v"(gv0), "+v"(gv1), "+v"(gv2),
+                       "+v"(gP), "+v"(gZ), "+v"(gV), "+v"(T), "+v"(Sv1));
+    }
+    __device__ __forceinline__ void sum(int ls) {
+        double *const a[11] = {&gr0, &gr1, &gr2, &gv0, &gv1, &gv2, &gP, &gZ, &gV, &T, &Sv1};
+#pragma unroll
+        for (int k = 0; k < 11; ++k) *a[k] = split_sum(*a[k], ls);
+    }
 };
 
 // dPhi_ij/dq_i for one partner j (i's data: ai = x y z V, bi = v P, zi = Z c,
-// di = b_rho b_v, bEi = b_E), plus the plain rate sums S* the prefactor terms
-// need.  Branch-free: a lane without a partner (use = false) computes on
-// placeholder data (r2 = 1) and keeps its sums.
+// di = b_rho b_v, bEi = b_E), and the sums T and Sv1.  Branch-free: a lane without a partner
+// (use = false) has its kernel constant selected to 0, which every term carries, and every
+// other factor finite.  With d = v_L - v* and the characteristic relations P* = P_i + Z_i d,
+// P_j + Z_j (v_L - v_R) - P* = Z_j d, each partial derivative of (v*, P*) is a product of
+// 1/S, Z_j/S and d: with K = G_v*/S + G_P* Z_j/S (G = V_j G_i + V_i G_j, G_v* and G_P* its
+// partials),
+//   dG/dP_i = K,  dG/dZ_i = K d,  dG/dv_L = V_j b_rho,i + Z_i K,  dG/dv_R = G_v* - Z_i K - V_i b_rho,j.
+// ZS: some impedance may be zero; Z_i + Z_j = 0 takes the mean state (P* = (P_i + P_j)/2,
+// v* = (v_L + v_R)/2, no dependence on Z).
+template <bool ZS>
 __device__ __forceinline__ void vjp_pair(bool use, double dx, double dy, double dz, double r2,
                                          const double4 &ai, const double4 &bi, const double2 &zi,
                                          const double4 &di, double bEi, const double4 &aj,
@@ -152,58 +168,51 @@ __device__ __forceinline__ void vjp_pair(bool use, double dx, double dy, double 
 #pragma clang fp contract(fast)
     const double Vi = ai.w, Pi = bi.w, Zi = zi.x;
     const double Vj = aj.w, Pj = bj.w, Zj = zj.x;
-    const double r = sqrt(use ? r2 : 1.0), ir = 1.0 / r;
+    const double ir = rsqrt64(fmax(r2, 1e-290));
+    const double q = r2 * ir * invH, a1 = 1.0 - q, a2 = a1 * a1;
+    const double dw = use ? dwc : 0.0;
+    const double Wp = -dw * q * (a2 * a1);
+    const double Wpp = -dw * invH * a2 * (1.0 - 4.0 * q);
     const double ex = dx * ir, ey = dy * ir, ez = dz * ir;
-    const double q = r * invH, a1 = 1.0 - q;
-    const double Wp = -dwc * q * (a1 * a1 * a1);
-    const double Wpp = -dwc * invH * (a1 * a1) * (1.0 - 4.0 * q);
     const double vL = (bi.x * ex + bi.y * ey) + bi.z * ez;
     const double vR = (bj.x * ex + bj.y * ey) + bj.z * ez;
+    const double vrel = vL - vR;
     const double S = Zi + Zj;
-    const bool sok = S != 0.0;
-    const double iS = 1.0 / (sok ? S : 1.0);
-    const double vs = sok ? ((Zi * vL + Zj * vR) + (Pi - Pj)) * iS : 0.5 * (vL + vR);
-    const double ps = sok ? ((Zj * Pi + Zi * Pj) + Zi * Zj * (vL - vR)) * iS : 0.5 * (Pi + Pj);
-    const double dvs_dvL = sok ? Zi * iS : 0.5;
-    const double dvs_dvR = sok ? Zj * iS : 0.5;
-    const double dps_dvL = sok ? Zi * Zj * iS : 0.0;
-    const double dps_dvR = -dps_dvL;
-    const double dvs_dP = sok ? iS : 0.0;
-    const double dps_dP = sok ? Zj * iS : 0.5;
-    const double dvs_dZ = sok ? (vL - vs) * iS : 0.0;
-    const double dps_dZ = sok ? ((Pj + Zj * (vL - vR)) - ps) * iS : 0.0;
-    const double bvie = (di.y * ex + di.z * ey) + di.w * ez;
-    const double bvje = (dj.y * ex + dj.z * ey) + dj.w * ez;
-    const double Gi = di.x * (vL - vs) + ps * bvie + bEi * ps * vs;
-    const double Gj = dj.x * (vs - vR) - ps * bvje - bEj * ps * vs;
+    const bool sok = !ZS || S != 0.0;
+    const double iS = sok ? rcp64(sok ? S : 1.0) : 0.0;
+    const double sj = sok ? Zj * iS : 0.5;
+    const double d = sok ? (Zj * vrel - (Pi - Pj)) * iS : 0.5 * vrel;  // v_L - v*
+    const double vs = vL - d, dr = vrel - d;                           // v*, v* - v_R
+    const double ps = sok ? Pi + Zi * d : 0.5 * (Pi + Pj);
+    const double Li = ((di.y * ex + di.z * ey) + di.w * ez) + bEi * vs;
+    const double Lj = ((dj.y * ex + dj.z * ey) + dj.w * ez) + bEj * vs;
+    const double hi = di.x * d;
+    const double Gi = hi + ps * Li, Gj = dj.x * dr - ps * Lj;
     const double G = Vj * Gi + Vi * Gj;
-    const double Gvs = Vj * (bEi * ps - di.x) + Vi * (dj.x - bEj * ps);
-    const double Gps = Vj * (bvie + bEi * vs) - Vi * (bvje + bEj * vs);
-    const double dGdvL = Vj * di.x + Gvs * dvs_dvL + Gps * dps_dvL;
-    const double dGdvR = -Vi * dj.x + Gvs * dvs_dvR + Gps * dps_dvR;
-    const double wv = Wp * dGdvL;
-    const double u0 = (dGdvL * bi.x + dGdvR * bj.x) + ps * (Vj * di.y - Vi * dj.y);
-    const double u1 = (dGdvL * bi.y + dGdvR * bj.y) + ps * (Vj * di.z - Vi * dj.z);
-    const double u2 = (dGdvL * bi.z + dGdvR * bj.z) + ps * (Vj * di.w - Vi * dj.w);
-    const double ue = (u0 * ex + u1 * ey) + u2 * ez;
-    const double k1 = Wpp * G, k2 = Wp * ir;
-    const double w = Vj * Wp;
-    const double f = w * ps;
-    A.gV = use ? A.gV + Wp * Gj : A.gV;
-    A.gP = use ? A.gP + Wp * (Gvs * dvs_dP + Gps * dps_dP) : A.gP;
-    A.gZ = use ? A.gZ + Wp * (Gvs * dvs_dZ + Gps * dps_dZ) : A.gZ;
-    A.gv0 = use ? A.gv0 + wv * ex : A.gv0;
-    A.gv1 = use ? A.gv1 + wv * ey : A.gv1;
-    A.gv2 = use ? A.gv2 + wv * ez : A.gv2;
+    const double Gvs = Vj * (bEi * ps - di.x) - Vi * (bEj * ps - dj.x);
+    const double Gps = Vj * Li - Vi * Lj;
+    const double K = Gvs * iS + Gps * sj;
+    const double ZK = sok ? Zi * K : 0.5 * Gvs;
+    const double gL = Vj * di.x + ZK, gR = (Gvs - ZK) - Vi * dj.x;
+    const double pVj = ps * Vj, pVi = ps * Vi;
+    const double u0 = (gL * bi.x + gR * bj.x) + (pVj * di.y - pVi * dj.y);
+    const double u1 = (gL * bi.y + gR * bj.y) + (pVj * di.z - pVi * dj.z);
+    const double u2 = (gL * bi.z + gR * bj.z) + (pVj * di.w - pVi * dj.w);
+    const double k2 = Wp * ir;
+    const double k1 = Wpp * G - k2 * ((u0 * ex + u1 * ey) + u2 * ez);
+    const double wv = Wp * gL, WK = Wp * K, w = Vj * Wp;
     // dJ/dr_i = -dPhi/dd
-    A.gr0 = use ? A.gr0 - (k1 * ex + k2 * (u0 - ue * ex)) : A.gr0;
-    A.gr1 = use ? A.gr1 - (k1 * ey + k2 * (u1 - ue * ey)) : A.gr1;
-    A.gr2 = use ? A.gr2 - (k1 * ez + k2 * (u2 - ue * ez)) : A.gr2;
-    A.Sr = use ? A.Sr + w * (vL - vs) : A.Sr;
-    A.Sv0 = use ? A.Sv0 + f * ex : A.Sv0;
-    A.Sv1 = use ? A.Sv1 + f * ey : A.Sv1;
-    A.Sv2 = use ? A.Sv2 + f * ez : A.Sv2;
-    A.SE = use ? A.SE + f * vs : A.SE;
+    A.gr0 -= k1 * ex + k2 * u0;
+    A.gr1 -= k1 * ey + k2 * u1;
+    A.gr2 -= k1 * ez + k2 * u2;
+    A.gv0 += wv * ex;
+    A.gv1 += wv * ey;
+    A.gv2 += wv * ez;
+    A.gP += WK;
+    A.gZ += sok ? WK * d : 0.0;
+    A.gV += Wp * Gj;
+    A.T += w * (hi - ps * Li);
+    A.Sv1 += w * ps * ey;
 }
 
 // The stencil walk of the FP64 rate kernel (lock-step rows clipped to the
@@ -221,65 +230,51 @@ __device__ __forceinline__ void vjp_pair(bool use, double dx, double dy, double 
 // walks, for the workgroups holding wall-band particles, their contributions added to the
 // outputs of a gather without the wall (which keeps that gather's register budget, and its
 // occupancy, for every other particle).
-template <bool WALL, bool PER, bool PAIR, bool MIRONLY = false>
-__global__ __launch_bounds__(kBlock) void k_vjp64(int64_t n, VjpIn in, VjpOut o,
-                                                  const int32_t *__restrict__ perm,
-                                                  const int32_t *__restrict__ cs, GridDev g,
-                                                  PairConst pc, EosDev eos, int n_eos,
-                                                  VjpWall wl) {
-    __shared__ int qj[kQ][kBlock];
-    const int tid = threadIdx.x;
-    const int64_t blk = xcd_block_upto(blockIdx.x, gridDim.x, 256);  // as the FP64 rate kernel
-    const int64_t s = blk * kBlock + tid;
-    const bool live = s < n;
-    double ge_gamma = 0.0, ge_pinf = 0.0;
-    int mt = 0;
-    double4 ai = make_double4(0.0, 0.0, 0.0, 0.0), bi = ai, di = ai;
-    double2 zi = make_double2(0.0, 0.0);
-    double bEi = 0.0;
-    if (live) {
-        ai = in.A[s];
-        bi = in.B[s];
-        di = in.Dw[s];
-        zi = in.C[s];
-        bEi = in.Ew[s];
-    }
-    if (wl.p.band) {
-        // correction pass: a workgroup without a particle within the support of the band's
-        // reach adds nothing (a NaN reach, no flagged particle, admits none)
-        const double thr = order_dec(*wl.p.band) + pc.H * (1.0 + 1e-9);
-        if (!__syncthreads_or(live && ai.y <= thr)) {
-            if (!MIRONLY && (int)threadIdx.x < 2 * n_eos)
-                o.eos_part[blk * 2 * CSPH_MAX_EOS + threadIdx.x] = 0.0;
-            return;
-        }
-    }
-    // the mirror-only gather: workgroups without a wall-band particle add nothing
-    if (MIRONLY && !__syncthreads_or(live && mirror_band(g, ai.y, wl.yw, pc.H))) return;
-    const Stencil t = make_stencil(g, ai.x, ai.y, ai.z, pc.H);
-    const double H2 = pc.H2;  // the largest support (pair-h mode), squared
-    const double dself = PAIR && live ? in.dsz[s] : 0.0;
-    const int self = (int)s;
-    // i's mirror image (its y, and its velocity record with the normal component mirrored),
-    // zero weights for the side of a pair that has no rate
-    const double yim = WALL ? 2.0 * wl.yw - ai.y : 0.0;
-    const double4 bim = make_double4(bi.x, wl.vw2 - bi.y, bi.z, bi.w);
-    const double4 d0 = make_double4(0.0, 0.0, 0.0, 0.0);
+constexpr int kUV = 3;  // candidates per lock-step iteration
+static_assert(kUV - 1 <= kRecPad, "the walk reads up to kUV - 1 records past a row");
+template <bool WALL, bool PER, bool PAIR, bool SPLIT>
+struct VjpWalk {
+    VjpIn in;
+    const int32_t *__restrict__ cs;
+    GridDev g;
+    PairConst pc;
+    VjpWall wl;
+    char *qb;        // the workgroup's rings: kQ rows of kBlock 4-byte slots
+    int lane4;       // the lane's byte offset in a ring row
+    uint32_t self16;
+    bool live;
+    double4 ai, bi, di;
+    double2 zi;
+    double bEi, dself;
+    // the FP32 candidate test (as in the FP64 rate kernel): i's record, or of the image point the
+    // walk is on
+    float4 a32, am;
+    float Df, hi32, wd, kd, kdi;
+    int nf = 0;
     VjpAcc acc, accm;  // accm: the pairs (j, image of i), in the image's q
     int qw = 0, qr = 0;
-    // (sx, sy, sz): the walk's periodic shift k L (0 off the periodic walks)
-    auto drain = [&](bool ghost, double sx, double sy, double sz) {
+    int sub = 0, ls = 0;  // SPLIT: the lane's share of i, log2 of the lanes per particle
+
+    __device__ __forceinline__ uint32_t &slot(int q) {
+        return *(uint32_t *)(qb + (((q & (kQ - 1)) * (kBlock * 4)) | lane4));
+    }
+
+    // every lane pops its next partner, if it has one, and decides its membership exactly
+    // ((sx, sy, sz): the walk's periodic shift k L, 0 off the periodic walks)
+    template <bool GHOST, bool ZS>
+    __device__ __forceinline__ void drain(double sx, double sy, double sz) {
         const bool has = qr < qw;
-        const int j = has ? qj[qr & (kQ - 1)][tid] : 0;
+        const uint32_t jo = has ? slot(qr) : 0u;
         qr += has ? 1 : 0;
-        const double4 aj = ld(in.A, j), bj = ld(in.B, j), dj = ld(in.Dw, j);
-        const double2 zj = ld(in.C, j);
-        const double bEj = ld(in.Ew, j);
-        double invH = pc.invH, dwc = pc.dwc, H2p = H2;
+        const double4 aj = in.A.at(jo), bj = in.B.at(jo), dj = in.Dw.at(jo);
+        const double2 zj = *(const double2 *)((const char *)in.C + jo);
+        const double bEj = *(const double *)((const char *)in.Ew + (jo >> 1));
+        double invH = pc.invH, dwc = pc.dwc, H2p = pc.H2;
         if (PAIR) {  // the pair's own support, as the forward pass forms it
-            const double H = pc.kappa * (0.5 * (dself + ld(in.dsz, j)));
+            const double dj2 = *(const double *)((const char *)in.dsz + (jo >> 1));
+            const double H = pc.kappa * (0.5 * (dself + dj2));
             H2p = H * H;
-            invH = 1.0 / (H > 0.0 ? H : 1.0);
+            invH = rcp64(H > 0.0 ? H : 1.0);
             const double i2 = invH * invH;
             dwc = (210.0 / M_PI) * (i2 * i2);
         }
@@ -288,107 +283,205 @@ __global__ __launch_bounds__(kBlock) void k_vjp64(int64_t n, VjpIn in, VjpOut o,
             dx = dx - sx;
             dz = dz - sz;
         }
-        if (!ghost) {
+        if (!GHOST) {
             double dy = aj.y - ai.y;
             if (PER) dy = dy - sy;
             const double r2 = ((dx * dx) + (dy * dy)) + (dz * dz);
-            vjp_pair(has && (!PAIR || r2 < H2p), dx, dy, dz, r2, ai, bi, zi, di, bEi, aj, bj, zj,
-                     dj, bEj, invH, dwc, acc);
+            vjp_pair<ZS>(has && r2 < H2p && r2 != 0.0, dx, dy, dz, r2, ai, bi, zi, di, bEi, aj, bj,
+                         zj, dj, bEj, invH, dwc, acc);
             return;
         }
+        // i's mirror image (its y, and its velocity record with the normal component
+        // mirrored), zero weights for the side of a pair that has no rate
+        const double yim = 2.0 * wl.yw - ai.y;
+        const double4 bim = make_double4(bi.x, wl.vw2 - bi.y, bi.z, bi.w);
+        const double4 d0 = make_double4(0.0, 0.0, 0.0, 0.0);
         // (i, image of j): offset (2 y_w - y_j) - y_i, as the forward pass forms it (the
         // wall's axis y is never periodic: no shift along it)
         const double dya = (2.0 * wl.yw - aj.y) - ai.y;
         const double r2a = ((dx * dx) + (dya * dya)) + (dz * dz);
         const double4 bjm = make_double4(bj.x, wl.vw2 - bj.y, bj.z, bj.w);
-        vjp_pair(has && r2a < H2p && r2a != 0.0, dx, dya, dz, r2a, ai, bi, zi, di, bEi, aj,
-                 bjm, zj, d0, 0.0, invH, dwc, acc);
+        vjp_pair<ZS>(has && r2a < H2p && r2a != 0.0, dx, dya, dz, r2a, ai, bi, zi, di, bEi, aj,
+                     bjm, zj, d0, 0.0, invH, dwc, acc);
         // (j, image of i): j's forward offset (2 y_w - y_i) - y_j, negated exactly
         const double dyb = aj.y - yim;
         const double r2b = ((dx * dx) + (dyb * dyb)) + (dz * dz);
-        vjp_pair(has && r2b < H2p && r2b != 0.0, dx, dyb, dz, r2b, ai, bim, zi, d0, 0.0, aj,
-                 bj, zj, dj, bEj, invH, dwc, accm);
-    };
-    // one walk over stencil st (ghost: the stencil around i's mirror image, whose partners
-    // are tested as both kinds of mirror pair; img: around a periodic image point, shift
-    // (sx, sy, sz)), every entry drained before it returns
-    auto walk = [&](const Stencil &st, bool ghost, bool img, bool on, double sx, double sy,
-                    double sz) {
-        int oy = st.R, oz = -st.R - 1;
-        int k = 0, j0 = 0, len = 0, jlast = 0;
-        for (;;) {
-            if (__any(qw - qr > kQ - kU)) {
-                drain(ghost, sx, sy, sz);
-                continue;
-            }
-            if (!__any(k < len)) {
-                if (++oy > st.R) {
-                    oy = -st.R;
-                    if (++oz > st.R) break;
-                }
-                const int zz = st.cz + oz;
-                const float gz = slab_gap(st.zc, zz);
-                row_range(cs, g, st, on, st.cy + oy, zz, gz * gz, j0, len);
-                jlast = len > 0 ? j0 + len - 1 : 0;
-                k = 0;
-                continue;
-            }
-            double4 aj[kU];
+        vjp_pair<ZS>(has && r2b < H2p && r2b != 0.0, dx, dyb, dz, r2b, ai, bim, zi, d0, 0.0, aj,
+                     bj, zj, dj, bEj, invH, dwc, accm);
+    }
+
+    // one walk over stencil st (GHOST: the stencil around i's mirror image, whose partners
+    // are tested as both kinds of mirror pair; IMG: around a periodic image point, shift
+    // (sx, sy, sz)), every entry drained before it returns.  Candidates within the FP32 band of
+    // the support are queued; the pop decides.
+    template <bool GHOST, bool IMG, bool ZS>
+    __device__ __forceinline__ void walk(const Stencil &st, bool on, int cy0, double sx, double sy,
+                                         double sz) {
+#pragma clang fp contract(fast)
+        auto row = [&](int oy, int yy, int oz, int j0, int len) {
+            const float az = am.z - (float)oz * Df;
+            const float ay = am.y - (float)(yy - cy0) * Df;
+            // the row i lies in (SPLIT: the lanes' rows differ)
+            const bool centre = !GHOST && !IMG && (SPLIT || (oy == 0 && oz == 0));
+            const int jlast = len > 0 ? j0 + len - 1 : 0;
+            int k = 0;
+            do {
+                const uint32_t jb = (uint32_t)min(j0 + k, jlast) * (uint32_t)sizeof(float4);
+                const float4 *Fb = (const float4 *)((const char *)in.F + jb);
+                const float *Db = PAIR ? (const float *)((const char *)in.d32 + (jb >> 2)) : nullptr;
 #pragma unroll
-            for (int u = 0; u < kU; ++u) aj[u] = ld(in.A, min(j0 + k + u, jlast));
-#pragma unroll
-            for (int u = 0; u < kU; ++u) {
-                const int j = j0 + k + u;
-                double dx = aj[u].x - ai.x, dz = aj[u].z - ai.z;
-                if (PER) {
-                    dx = dx - sx;
-                    dz = dz - sz;
+                for (int u = 0; u < kUV; ++u) {
+                    const float4 aj = Fb[u];
+                    const float dx = (aj.x + (aj.w - am.w) * Df) - am.x;
+                    float dy = aj.y - ay;
+                    const float dz = aj.z - az;
+                    if (GHOST) dy = 2.0f * wd - dy;
+                    const float r2 = (dx * dx + dy * dy) + dz * dz;
+                    float hj = hi32;
+                    if (PAIR) {
+                        const float Hj = fmaf(kd, Db[u], kdi);
+                        hj = Hj * Hj;
+                    }
+                    const uint32_t jo = jb + (uint32_t)(u * sizeof(float4));
+                    bool acc = (k + u < len) & (r2 < hj);
+                    if (centre) acc = acc & (jo != self16);
+                    slot(qw) = jo;
+                    qw += acc ? 1 : 0;
                 }
-                bool ok;
-                if (!ghost) {
-                    double dy = aj[u].y - ai.y;
-                    if (PER) dy = dy - sy;
-                    const double r2 = ((dx * dx) + (dy * dy)) + (dz * dz);
-                    ok = (k + u < len) && (img || j != self) && r2 < H2 && r2 != 0.0;
-                } else {
-                    const double dya = (2.0 * wl.yw - aj[u].y) - ai.y, dyb = aj[u].y - yim;
-                    const double dxz = (dx * dx);
-                    const double r2a = (dxz + (dya * dya)) + (dz * dz);
-                    const double r2b = (dxz + (dyb * dyb)) + (dz * dz);
-                    ok = (k + u < len) && ((r2a < H2 && r2a != 0.0) || (r2b < H2 && r2b != 0.0));
+                if (__any(qw - qr > kQ - kUV)) {
+                    do {
+                        drain<GHOST, ZS>(sx, sy, sz);
+                        settle<GHOST>();
+                    } while (__any(qw - qr > kQ - kUV));
                 }
-                qj[qw & (kQ - 1)][tid] = j;
-                qw += ok ? 1 : 0;
-            }
-            k += kU;
+                k += kUV;
+            } while (__any(k < len));
+        };
+        if (SPLIT)
+            walk_rows_split(cs, g, st, on, sub, ls, row);
+        else
+            walk_rows(cs, g, st, on, row);
+        while (__any(qr < qw)) {
+            drain<GHOST, ZS>(sx, sy, sz);
+            settle<GHOST>();
         }
-        while (__any(qr < qw)) drain(ghost, sx, sy, sz);
-    };
-    // the walks around the periodic images of point (px, py, pz) (i, or its mirror image) for
+    }
+
+    template <bool GHOST>
+    __device__ __forceinline__ void settle() {
+        acc.settle();
+        if (GHOST) accm.settle();
+        asm volatile("" : "+v"(qr));
+    }
+
+    // the walks around the periodic images of point (x_i, py, z_i) (i, or its mirror image) for
     // the lanes in `on`, stencil base st
-    const int nf = PER ? image_faces(pc, ai.x, ai.y, ai.z) : 0;
-    auto images = [&](const Stencil &base, bool ghost, bool on, double py) {
+    template <bool GHOST, bool ZS>
+    __device__ __forceinline__ void images(const Stencil &base, bool on, double py, int cy0) {
         for (int m = 1; m < 8; ++m) {
             const bool onm = on && (nf & m) == m;
             if (!__any(onm)) continue;
             const double sx = image_shift(pc, nf, m, 0), sy = image_shift(pc, nf, m, 1),
                          sz = image_shift(pc, nf, m, 2);
-            const Stencil sm = shifted_stencil(g, base, m, ai.x + sx, py + sy, ai.z + sz);
-            walk(sm, ghost, true, onm, sx, sy, sz);
+            const double px = ai.x + sx, pz = ai.z + sz;
+            const Stencil sm = shifted_stencil(g, base, m, px, py + sy, pz);
+            am.x = m & 1 ? (float)(px - (g.ox + (double)sm.cx * g.cell)) : a32.x;
+            am.y = m & 2 && !GHOST ? (float)(py + sy - (g.oy + (double)sm.cy * g.cell)) : a32.y;
+            am.z = m & 4 ? (float)(pz - (g.oz + (double)sm.cz * g.cell)) : a32.z;
+            am.w = (float)sm.cx;
+            walk<GHOST, true, ZS>(sm, onm, GHOST ? cy0 : sm.cy, sx, sy, sz);
         }
-    };
-    if (!MIRONLY) {
-        walk(t, false, false, live, 0.0, 0.0, 0.0);
-        if (PER) images(t, false, live, ai.y);
+        am = a32;
     }
-    if (WALL) {
-        const bool near = live && mirror_band(g, ai.y, wl.yw, pc.H);
-        if (__any(near)) {
-            const Stencil ti = image_stencil(g, t, yim);
-            walk(ti, true, false, near, 0.0, 0.0, 0.0);
-            if (PER) images(ti, true, near, yim);
+
+    template <bool MIRONLY, bool ZS>
+    __device__ __forceinline__ void run(bool near) {
+        const Stencil t = make_stencil(g, ai.x, ai.y, ai.z, pc.H);
+        am = a32;
+        if (!MIRONLY) {
+            walk<false, false, ZS>(t, live, t.cy, 0.0, 0.0, 0.0);
+            if (PER) images<false, ZS>(t, live, ai.y, t.cy);
         }
+        if (WALL && __any(near)) {
+            const double yim = 2.0 * wl.yw - ai.y;
+            const Stencil ti = image_stencil(g, t, yim);
+            walk<true, false, ZS>(ti, near, t.cy, 0.0, 0.0, 0.0);
+            if (PER) images<true, ZS>(ti, near, yim, t.cy);
+        }
+    }
+};
+
+template <bool WALL, bool PER, bool PAIR, bool MIRONLY, bool SPLIT>
+__global__ __launch_bounds__(kBlock, WALL ? 2 : PER ? 3 : 4) void k_vjp64(int64_t n, VjpIn in, VjpOut o,
+                                                  const int32_t *__restrict__ perm,
+                                                  const int32_t *__restrict__ cs, GridDev g,
+                                                  PairConst pc, EosDev eos, int n_eos,
+                                                  VjpWall wl, int ls) {
+    __shared__ int qj[kQ][kBlock];
+    const int tid = threadIdx.x;
+    const int64_t blk = xcd_block_upto(blockIdx.x, gridDim.x, 256);  // as the FP64 rate kernel
+    int64_t s = blk * kBlock + tid;
+    VjpWalk<WALL, PER, PAIR, SPLIT> k;
+    if (SPLIT) {
+        k.sub = tid & ((1 << ls) - 1);
+        k.ls = ls;
+        s >>= ls;
+    }
+    const bool live = s < n, first = live && (!SPLIT || k.sub == 0);
+    double ge_gamma = 0.0, ge_pinf = 0.0;
+    int mt = 0;
+    k.in = in;
+    k.cs = cs;
+    k.g = g;
+    k.pc = pc;
+    k.wl = wl;
+    k.qb = (char *)&qj[0][0];
+    k.lane4 = tid * (int)sizeof(int);
+    k.self16 = (uint32_t)s * 16u;
+    k.live = live;
+    k.ai = make_double4(0.0, 0.0, 0.0, 0.0);
+    k.bi = k.di = k.ai;
+    k.zi = make_double2(0.0, 0.0);
+    k.a32 = make_float4(0.f, 0.f, 0.f, 0.f);
+    k.bEi = k.dself = 0.0;
+    if (live) {
+        k.ai = in.A[s];
+        k.bi = in.B[s];
+        k.di = in.Dw[s];
+        k.zi = in.C[s];
+        k.bEi = in.Ew[s];
+        k.a32 = in.F[s];
+        if (PAIR) k.dself = in.dsz[s];
+    }
+    if (wl.p.band) {
+        // correction pass: a workgroup without a particle within the support of the band's
+        // reach adds nothing (a NaN reach, no flagged particle, admits none)
+        const double thr = order_dec(*wl.p.band) + pc.H * (1.0 + 1e-9);
+        if (!__syncthreads_or(live && k.ai.y <= thr)) {
+            if (!MIRONLY && (int)threadIdx.x < 2 * n_eos)
+                o.eos_part[blk * 2 * CSPH_MAX_EOS + threadIdx.x] = 0.0;
+            return;
+        }
+    }
+    const bool near = WALL && live && mirror_band(g, k.ai.y, wl.yw, pc.H);
+    // the mirror-only gather: workgroups without a wall-band particle add nothing
+    if (MIRONLY && !__syncthreads_or(near)) return;
+    k.Df = uniform_f((float)g.cell);
+    k.hi32 = uniform_f((float)pc.H2 * (1.0f + kBand));
+    k.wd = WALL ? (float)(wl.yw - k.ai.y) : 0.f;
+    k.kd = PAIR ? pair_kd(pc.kappa) : 0.f;
+    k.kdi = k.kd * (float)k.dself;
+    if (PER && live) k.nf = image_faces(pc, k.ai.x, k.ai.y, k.ai.z);
+    if (*in.zflag == 0)
+        k.template run<MIRONLY, true>(near);
+    else
+        k.template run<MIRONLY, false>(near);
+    VjpAcc &acc = k.acc;
+    const double4 bi = k.bi;
+    const double2 zi = k.zi;
+    if (WALL) {
         // the image's q back to i's: y and v_y change sign, P, Z and V are i's own
+        const VjpAcc &accm = k.accm;
         acc.gr0 += accm.gr0;
         acc.gr1 -= accm.gr1;
         acc.gr2 += accm.gr2;
@@ -399,16 +492,13 @@ __global__ __launch_bounds__(kBlock) void k_vjp64(int64_t n, VjpIn in, VjpOut o,
         acc.gZ += accm.gZ;
         acc.gV += accm.gV;
     }
-    if (live) {
+    if (SPLIT) acc.sum(ls);
+    if (first) {
         double gr0 = acc.gr0, gr1 = acc.gr1, gr2 = acc.gr2, gv0 = acc.gv0, gv1 = acc.gv1,
                gv2 = acc.gv2, gP = acc.gP, gZ = acc.gZ, gV = acc.gV;
-        const double Sr = acc.Sr, Sv0 = acc.Sv0, Sv1 = acc.Sv1, Sv2 = acc.Sv2, SE = acc.SE;
-        // prefactors rho_i: dJ/drho_i += (a_rho R_rho - a_v.R_v - a_E R_E)/rho_i
+        // prefactors rho_i: dJ/drho_i += (a_rho R_rho - a_v.R_v - a_E R_E)/rho_i = T/rho_i
         double rho = in.rho[s], E = in.E[s], m = in.m[s];
-        double ar = in.a[0][s], ax = in.a[1][s], ay = in.a[2][s], az = in.a[3][s],
-               aE = in.a[4][s];
-        double Rr = -2.0 * rho * Sr, pre = 2.0 / rho;
-        double grho = (ar * Rr - pre * ((ax * Sv0 + ay * Sv1) + az * Sv2) - aE * pre * SE) / rho;
+        double grho = acc.T / rho;
         // V = m/rho, Z = rho c
         grho += -gV * m / (rho * rho);
         double c = zi.y;
@@ -448,9 +538,9 @@ __global__ __launch_bounds__(kBlock) void k_vjp64(int64_t n, VjpIn in, VjpOut o,
         int i = perm[s];
         if (wl.p.svy) {  // this gather's part of the y-momentum rate sum (k_wall_flags)
             if (MIRONLY)
-                wl.p.svy[s] += Sv1;
+                wl.p.svy[s] += acc.Sv1;
             else
-                wl.p.svy[s] = Sv1;
+                wl.p.svy[s] = acc.Sv1;
         }
         if (!MIRONLY && o.gn[0]) {
             // identity part of the step: r' = r + dt v', v' = v + dt dv, ...
@@ -472,7 +562,7 @@ __global__ __launch_bounds__(kBlock) void k_vjp64(int64_t n, VjpIn in, VjpOut o,
     // the workgroups per CU to the register budget)
     __shared__ double sh[kBlock / 64][2 * CSPH_MAX_EOS];
     for (int k = 0; k < 2 * n_eos; ++k) {
-        double v = (s < n && mt == (k >> 1)) ? ((k & 1) ? ge_pinf : ge_gamma) : 0.0;
+        double v = (first && mt == (k >> 1)) ? ((k & 1) ? ge_pinf : ge_gamma) : 0.0;
         for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
         if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6][k] = v;
     }
@@ -620,12 +710,11 @@ __global__ __launch_bounds__(kBlock) void k_dt_cot_final(const double *__restric
 // The density-change limit binds: d tau/d drho = -rho sgn(drho) / drho^2 joins the rate
 // cotangent a_rho (and its pair weight b_rho = -2 rho a_rho) of the binding slot.
 __global__ void k_dt_fix_weights(const DtInfo *info, double cfl, const double *__restrict__ rho_s,
-                                 double *a0, double4 *Dw) {
+                                 double2 *Dw) {
     if (threadIdx.x != 0 || info->courant != 2) return;
     const unsigned long long s = info->arg;
     const double dr = info->drho;
     const double x = cfl * info->gdt * (-info->rho * (dr > 0.0 ? 1.0 : -1.0) / (dr * dr));
-    a0[s] += x;
     Dw[s].x -= 2.0 * rho_s[s] * x;
 }
 
@@ -854,25 +943,55 @@ hipError_t launch_dt_adjoint(int64_t n, const int32_t *perm, double *const sorte
 // (the epilogue is linear in the walks' sums, so the two launches give the one-walk gather's
 // result up to the order of the additions).  The wall's walks and state take some 60 more
 // VGPRs, which in one kernel would hold every workgroup to two waves per SIMD instead of three.
-static void vjp_gather(unsigned nb, int64_t n, const VjpIn &in, const VjpOut &o,
+static void vjp_gather(unsigned nb, int ls, int64_t n, const VjpIn &in, const VjpOut &o,
                        const int32_t *perm, const int32_t *cs, const GridDev &g,
                        const PairConst &pc, const EosDev &eos, bool wall, const VjpWall &wl,
                        hipStream_t st) {
     VjpOut om = o;  // the mirror-only gather adds to the first one's outputs
     om.accumulate = 1;
-    const bool per = pc.per != 0, pair = pc.pair_mode != 0;
-#define CSPH_VJP_CASE(X, Q)                                                                  \
-    if (per == X && pair == Q) {                                                             \
-        k_vjp64<false, X, Q><<<nb, kBlock, 0, st>>>(n, in, o, perm, cs, g, pc, eos, eos.n, wl); \
-        if (wall)                                                                            \
-            k_vjp64<true, X, Q, true><<<nb, kBlock, 0, st>>>(n, in, om, perm, cs, g, pc, eos, \
-                                                             eos.n, wl);                      \
+    const bool per = pc.per != 0, pair = pc.pair_mode != 0, split = ls > 0;
+#define CSPH_VJP_CASE(X, Q, S)                                                                \
+    if (per == X && pair == Q && split == S) {                                                \
+        k_vjp64<false, X, Q, false, S><<<nb, kBlock, 0, st>>>(n, in, o, perm, cs, g, pc, eos, \
+                                                              eos.n, wl, ls);                 \
+        if (wall)                                                                             \
+            k_vjp64<true, X, Q, true, S><<<nb, kBlock, 0, st>>>(n, in, om, perm, cs, g, pc,   \
+                                                                eos, eos.n, wl, ls);          \
     }
-    CSPH_VJP_CASE(false, false)
-    CSPH_VJP_CASE(false, true)
-    CSPH_VJP_CASE(true, false)
-    CSPH_VJP_CASE(true, true)
+    CSPH_VJP_CASE(false, false, false)
+    CSPH_VJP_CASE(false, true, false)
+    CSPH_VJP_CASE(true, false, false)
+    CSPH_VJP_CASE(true, true, false)
+    CSPH_VJP_CASE(false, false, true)
+    CSPH_VJP_CASE(false, true, true)
+    CSPH_VJP_CASE(true, false, true)
+    CSPH_VJP_CASE(true, true, true)
 #undef CSPH_VJP_CASE
+}
+
+// The gather's per-block EOS-parameter sums, 2 CSPH_MAX_EOS = 16 doubles a block: with several
+// lanes per particle there are up to 16 times the blocks, n / 16 of them, and the sums take a
+// rate array (n doubles, which no adjoint uses by then).
+static_assert(kBlock == 256 && kSplitMax <= 4 && CSPH_MAX_EOS == 8, "the sums fit a rate array");
+static double *vjp_eos_part(const Ws &w, int ls) { return ls > 0 ? w.rate[4] : w.eos_part; }
+
+static VjpIn vjp_in(int64_t n, const Ws &w, double *const sorted[9], const int32_t *mat_sorted,
+                    const double *d_sorted) {
+    VjpIn in;
+    in.A = split4(w.recA, n);
+    in.B = split4(w.recB, n);
+    in.C = (const double2 *)w.recC;
+    in.Dw = split4(w.recD, n);
+    in.F = (const float4 *)w.recF;
+    in.zflag = w.zflag;
+    in.Ew = w.recE;
+    in.rho = sorted[6];
+    in.E = sorted[7];
+    in.m = sorted[8];
+    in.mat = mat_sorted;
+    in.dsz = d_sorted;
+    in.d32 = (const float *)w.rank;
+    return in;
 }
 
 hipError_t launch_vjp(int64_t n, const int32_t *perm, const int32_t *cs, const GridDev &g,
@@ -883,7 +1002,9 @@ hipError_t launch_vjp(int64_t n, const int32_t *perm, const int32_t *cs, const G
                       const double *d_sorted, int wall, double yw, double vw, hipStream_t st,
                       const DtAdj *dta) {
     if (n <= 0) return hipSuccess;
-    unsigned nb = (unsigned)((n + kBlock - 1) / kBlock);
+    const int ls = split_log2(n);
+    const unsigned nb = (unsigned)((n + kBlock - 1) / kBlock);
+    const unsigned nbg = (unsigned)(((n << ls) + kBlock - 1) / kBlock);  // the gather's
     VjpOut o;
     for (int k = 0; k < 8; ++k) {
         o.g[k] = gout[k];
@@ -891,30 +1012,18 @@ hipError_t launch_vjp(int64_t n, const int32_t *perm, const int32_t *cs, const G
     }
     o.dt = dt;
     o.accumulate = accumulate;
-    o.eos_part = w.eos_part;
+    o.eos_part = vjp_eos_part(w, ls);
     k_vjp_weights<<<nb, kBlock, 0, st>>>(n, perm, sorted[6], o, a_in ? a_in[0] : nullptr,
                                          a_in ? a_in[1] : nullptr, a_in ? a_in[2] : nullptr,
                                          a_in ? a_in[3] : nullptr, a_in ? a_in[4] : nullptr,
-                                         w.rate[0], w.rate[1], w.rate[2], w.rate[3], w.rate[4],
-                                         (double4 *)w.recD, w.recE);
+                                         (double2 *)w.recD, w.recE);
     if (dta)  // the density-change limit's term, in the rate cotangent of the binding particle
-        k_dt_fix_weights<<<1, 64, 0, st>>>(dta->info, dta->cfl, sorted[6], w.rate[0],
-                                           (double4 *)w.recD);
-    VjpIn in;
-    in.A = (const double4 *)w.recA;
-    in.B = (const double4 *)w.recB;
-    in.C = (const double2 *)w.recC;
-    in.Dw = (const double4 *)w.recD;
-    in.Ew = w.recE;
-    in.rho = sorted[6];
-    in.E = sorted[7];
-    in.m = sorted[8];
-    in.mat = mat_sorted;
-    for (int k = 0; k < 5; ++k) in.a[k] = w.rate[k];
-    in.dsz = d_sorted;
+        k_dt_fix_weights<<<1, 64, 0, st>>>(dta->info, dta->cfl, sorted[6],
+                                           (double2 *)w.recD);
+    const VjpIn in = vjp_in(n, w, sorted, mat_sorted, d_sorted);
     const VjpWall wl{yw, 2.0 * vw, WallPass{nullptr, nullptr}};
-    vjp_gather(nb, n, in, o, perm, cs, g, pc, eos, wall != 0, wl, st);
-    if (g_eos) k_eos_grad_final<<<1, kBlock, 0, st>>>(w.eos_part, (int64_t)nb, 2 * eos.n, g_eos);
+    vjp_gather(nbg, ls, n, in, o, perm, cs, g, pc, eos, wall != 0, wl, st);
+    if (g_eos) k_eos_grad_final<<<1, kBlock, 0, st>>>(o.eos_part, (int64_t)nbg, 2 * eos.n, g_eos);
     if (dta) {
         DtFix f;
         f.info = dta->info;
@@ -943,7 +1052,9 @@ hipError_t launch_vjp_wall(int64_t n, const int32_t *perm, const int32_t *cs, co
                            double *g_eos, const double *d_sorted, double yw, double vw,
                            const WallPass &wp, hipStream_t st) {
     if (n <= 0) return hipSuccess;
-    unsigned nb = (unsigned)((n + kBlock - 1) / kBlock);
+    const int ls = split_log2(n);
+    const unsigned nb = (unsigned)((n + kBlock - 1) / kBlock);
+    const unsigned nbg = (unsigned)(((n << ls) + kBlock - 1) / kBlock);  // the gather's
     VjpOut o;
     for (int k = 0; k < 8; ++k) {
         o.g[k] = gout[k];
@@ -951,27 +1062,15 @@ hipError_t launch_vjp_wall(int64_t n, const int32_t *perm, const int32_t *cs, co
     }
     o.dt = dt;
     o.accumulate = accumulate;
-    o.eos_part = w.eos_part;
+    o.eos_part = vjp_eos_part(w, ls);
     k_vjp_weights<<<nb, kBlock, 0, st>>>(n, perm, sorted[6], o, a_in ? a_in[0] : nullptr,
                                          a_in ? a_in[1] : nullptr, a_in ? a_in[2] : nullptr,
                                          a_in ? a_in[3] : nullptr, a_in ? a_in[4] : nullptr,
-                                         w.rate[0], w.rate[1], w.rate[2], w.rate[3], w.rate[4],
-                                         (double4 *)w.recD, w.recE);
-    VjpIn in;
-    in.A = (const double4 *)w.recA;
-    in.B = (const double4 *)w.recB;
-    in.C = (const double2 *)w.recC;
-    in.Dw = (const double4 *)w.recD;
-    in.Ew = w.recE;
-    in.rho = sorted[6];
-    in.E = sorted[7];
-    in.m = sorted[8];
-    in.mat = mat_sorted;
-    for (int k = 0; k < 5; ++k) in.a[k] = w.rate[k];
-    in.dsz = d_sorted;
+                                         (double2 *)w.recD, w.recE);
+    const VjpIn in = vjp_in(n, w, sorted, mat_sorted, d_sorted);
     const VjpWall wl{yw, 2.0 * vw, wp};
-    vjp_gather(nb, n, in, o, perm, cs, g, pc, eos, true, wl, st);
-    if (g_eos) k_eos_grad_final<<<1, kBlock, 0, st>>>(w.eos_part, (int64_t)nb, 2 * eos.n, g_eos);
+    vjp_gather(nbg, ls, n, in, o, perm, cs, g, pc, eos, true, wl, st);
+    if (g_eos) k_eos_grad_final<<<1, kBlock, 0, st>>>(o.eos_part, (int64_t)nbg, 2 * eos.n, g_eos);
     return hipGetLastError();
 }
 

@@ -30,10 +30,6 @@ struct DstState {
 
 // Gather particle perm[s] into slot s: sorted FP64 state copy, EOS
 // (e = E - |v|^2/2; ideal gas, stiffened gas or Mie-Grueneisen), pair record.
-// Zero records after the n FP32 stencil records (cell-relative offsets, read by the candidate
-// tests of both kernels): a walk loads up to kUS - 1 (kUS64 - 1) records past a row's last one
-constexpr int kRecPad = 2;
-
 template <bool MIXED>
 __global__ __launch_bounds__(kBlock) void k_pack(int64_t n, SrcState src,
                                                  const int32_t *__restrict__ perm, EosDev eos,
@@ -43,7 +39,8 @@ __global__ __launch_bounds__(kBlock) void k_pack(int64_t n, SrcState src,
                                                  int64_t *__restrict__ nonphys,
                                                  unsigned long long *__restrict__ zflag,
                                                  const int32_t *__restrict__ gate,
-                                                 float4 *__restrict__ recF) {
+                                                 float4 *__restrict__ recF,
+                                                 float *__restrict__ d32) {
     if (gate && *gate == 0) return;
     int64_t s = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (s >= n) return;
@@ -57,7 +54,10 @@ __global__ __launch_bounds__(kBlock) void k_pack(int64_t n, SrcState src,
     }
     int mt = src.mat ? src.mat[i] : 0;
     if (dst.mat) dst.mat[s] = mt;
-    if (src.d && dst.d) dst.d[s] = src.d[i];
+    if (src.d && dst.d) {
+        dst.d[s] = src.d[i];
+        if (d32) d32[s] = (float)src.d[i];
+    }
     if (src.id && dst.id) dst.id[s] = src.id[i];
     double x = v[0], y = v[1], z = v[2], vx = v[3], vy = v[4], vz = v[5], rho = v[6], E = v[7],
            m = v[8];
@@ -94,8 +94,11 @@ __global__ __launch_bounds__(kBlock) void k_pack(int64_t n, SrcState src,
             ((float4 *)recB)[s] = make_float4((float)vx, (float)vy, (float)vz, (float)P);
             ((float4 *)recC)[s] = make_float4((float)Z, (float)c, (float)V, 0.0f);
         } else {
-            ((double4 *)recA)[s] = make_double4(x, y, z, V);
-            ((double4 *)recB)[s] = make_double4(vx, vy, vz, P);
+            // arrays of 16 bytes a record: (x y), (z V), (vx vy), (vz P), (Z c)
+            ((double2 *)recA)[s] = make_double2(x, y);
+            ((double2 *)recA)[n + s] = make_double2(z, V);
+            ((double2 *)recB)[s] = make_double2(vx, vy);
+            ((double2 *)recB)[n + s] = make_double2(vz, P);
             ((double2 *)recC)[s] = make_double2(Z, c);
         }
     }
@@ -115,13 +118,15 @@ hipError_t launch_pack(const csph_state &s, int64_t n, const int32_t *perm, cons
     // perm = NULL: records of the state as it is (Verlet steps); the A record then holds
     // the FP64 position in both precisions
     void *recA = w.recA;
+    // the sizes in FP32 for the candidate tests, in the binning's ranks (used up by then)
+    float *d32 = perm ? (float *)w.rank : nullptr;
     unsigned nb = (unsigned)((n + kBlock - 1) / kBlock);
     if (mixed)
         k_pack<true><<<nb, kBlock, 0, st>>>(n, src, perm, eos, g, recA, w.recB, w.recC, ds,
-                                            nonphys, w.zflag, gate, nullptr);
+                                            nonphys, w.zflag, gate, nullptr, d32);
     else
         k_pack<false><<<nb, kBlock, 0, st>>>(n, src, perm, eos, g, recA, w.recB, w.recC, ds,
-                                             nonphys, w.zflag, gate, (float4 *)w.recF);
+                                             nonphys, w.zflag, gate, (float4 *)w.recF, d32);
     return hipGetLastError();
 }
 
@@ -176,13 +181,6 @@ struct RateOut {
     const unsigned long long *zflag;  // 0: some impedance is zero (see k_pack)
 };
 
-// Candidates whose FP32 squared distance lies within this relative band of
-// the squared support are decided in FP64 from the FP64 positions (the mixed
-// kernel re-tests them at the pop; the FP64 kernel queues them and decides
-// every pop in FP64), so both accept exactly the FP64 neighbour set (the FP32
-// error of r^2 is below 1e-6 relative for offsets within a few cells).
-constexpr float kBand = 4e-5f;
-
 // ---------------------------------------------------------------- FP64 rates
 //
 // The pair step is written without branches: a lane with no partner to
@@ -190,35 +188,6 @@ constexpr float kBand = 4e-5f;
 // placeholder data and keeps its sums by selection.  Divergent branches in
 // the drain made the compiler shuffle the live sums between registers on
 // every pop.
-
-// 1/sqrt(x) and 1/x for x > 0 in FP64: the hardware estimate (v_rsq_f64, v_rcp_f64) refined
-// by two Newton steps.  For 1/sqrt(x) the step is y <- y + (y/2)(1 - x y^2), for 1/x it is
-// y <- y + y (1 - x y); each squares the relative error (up to a factor 3/2 for 1/sqrt), so
-// two steps take the estimate to the last bits of FP64 (the result is within a few ulp, not
-// correctly rounded: the rates are compared with a 1e-12 tolerance).  They replace the
-// compiler's correctly rounded FP64 square root and divisions, which take several times the
-// instructions.
-__device__ __forceinline__ double rsqrt64(double x) {
-#pragma clang fp contract(fast)
-    double y = __builtin_amdgcn_rsq(x);
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        const double e = fma(-x * y, y, 1.0);
-        y = fma(0.5 * y, e, y);
-    }
-    return y;
-}
-
-__device__ __forceinline__ double rcp64(double x) {
-#pragma clang fp contract(fast)
-    double y = __builtin_amdgcn_rcp(x);
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        const double e = fma(-x, y, 1.0);
-        y = fma(y, e, y);
-    }
-    return y;
-}
 
 // One partner of particle i: Riemann problem along e, kernel slope, sums.
 // The membership test that precedes it is exact; here contraction is allowed.
@@ -235,12 +204,13 @@ __device__ __forceinline__ void pair64(bool use, double dx, double dy, double dz
                                        double &ar, double &avx, double &avy, double &avz,
                                        double &aE, double &sig) {
 #pragma clang fp contract(fast)
-    const double ir = rsqrt64(use ? r2 : 1.0);
+    // (a lane without a partner may hold r2 = 0: kept finite)
+    const double ir = rsqrt64(fmax(r2, 1e-290));
     const double r = r2 * ir;
     const double q = r * invH;
     const double a1 = 1.0 - q;
     // a lane without a partner adds exact zeros: its kernel constant is selected to 0 and
-    // every factor it multiplies is finite (placeholder offsets and r2 finite)
+    // every factor it multiplies is finite (finite offsets)
     const double dW = -(use ? dwc : 0.0) * q * (a1 * a1 * a1);
     // v_L - v_R from the velocity difference and the raw offsets
     const double vrel = (((bi.x - vxj) * dx + (bi.y - vyj) * dy) + (bi.z - vzj) * dz) * ir;
@@ -270,12 +240,11 @@ __device__ __forceinline__ void pair64(bool use, double dx, double dy, double dz
 // FP32 kernel: the loop's copies of the live sums are paid once per two pops)
 constexpr int kUS64 = 3;
 constexpr int kPop64 = 2;
-static_assert(kUS64 - 1 <= kRecPad, "the FP64 stencil walk reads up to kUS64 - 1 FP32 records past a row");
+static_assert(kUS64 - 1 <= kRecPad, "the stencil walk reads up to kUS64 - 1 records past a row");
 
-template <bool PAIR, bool WALL, bool PER>
+template <bool PAIR, bool WALL, bool PER, bool SPLIT>
 struct Rates64 {
-    const double4 *__restrict__ A;
-    const double4 *__restrict__ B;
+    Split4 A, B;                   // x y z V, vx vy vz P
     const double2 *__restrict__ Cz;
     const float4 *__restrict__ F;  // stencil walks: cell-relative FP32 records (the test)
     const double *__restrict__ dsz;
@@ -284,7 +253,8 @@ struct Rates64 {
     PairConst pc;
     char *qb;         // the workgroup's rings: kQ rows of kRate64Block 4-byte slots
     int lane4;        // the lane's byte offset in a ring row
-    uint32_t self32;  // byte offset of i's own 32-byte records
+    const float *__restrict__ d32;  // pair-h mode: the sizes in FP32 (the test)
+    uint32_t self16;  // byte offset of i's own 16-byte records
     bool live, near_wall;
     double4 a, b;
     double2 zc;
@@ -294,16 +264,17 @@ struct Rates64 {
     // record (offsets and its cell's x index), D, the support bound (squared, with the band)
     // and the wall's distance
     float4 a32;
-    float Df, hi32, wd;
+    float Df, hi32, wd, kd, kdi;
     // periodic images: i's faces (image_faces), the image the walk is on (wave-uniform mask),
     // its stencil, i's FP32 offsets from the image point's cell origin and that cell's x index
     int nf = 0, im = 0;
     Stencil tm;
     float amx = 0.f, amy = 0.f, amz = 0.f, cxm = 0.f;
     double ar = 0.0, avx = 0.0, avy = 0.0, avz = 0.0, aE = 0.0, sig = 0.0;
-    // ring counters in entries; an entry is the partner's 32-byte record offset, bit 0 set for
+    // ring counters in entries; an entry is the partner's 16-byte record offset, bit 0 set for
     // a mirror image, bits 1-3 the periodic image mask.  cnt: the exact members popped, |N(i)|
     int qw = 0, qr = 0, cnt = 0;
+    int sub = 0, ls = 0;  // SPLIT: the lane's share of i, log2 of the lanes per particle
 
     __device__ __forceinline__ uint32_t &slot(int q) {
         return *(uint32_t *)(qb + (((q & (kQ - 1)) * kSlot64) | lane4));
@@ -315,13 +286,13 @@ struct Rates64 {
         const bool has = qr < qw;
         const uint32_t e = slot(qr);
         qr += has ? 1 : 0;
-        const uint32_t jo = has ? (MIR ? e & ~31u : e) : 0u;
+        const uint32_t jo = has ? (MIR ? e & ~15u : e) : 0u;
         const bool ghost = MIR && (e & 1u);
         const int mm = PER && MIR ? (int)((e >> 1) & 7u) : 0;
-        const int j = (int)(jo >> 5);
-        const double4 aj = *(const double4 *)((const char *)A + jo);
-        const double4 bj = *(const double4 *)((const char *)B + jo);
-        const double2 zj = *(const double2 *)((const char *)Cz + (jo >> 1));
+        const int j = (int)(jo >> 4);
+        const double4 aj = A.at(jo);
+        const double4 bj = B.at(jo);
+        const double2 zj = *(const double2 *)((const char *)Cz + jo);
         const double yj = ghost ? 2.0 * yw - aj.y : aj.y;
         double dx = aj.x - a.x, dy = yj - a.y, dz = aj.z - a.z;
         if (PER) {  // image mm: d = (x_j - x_i) - k L
@@ -346,6 +317,13 @@ struct Rates64 {
                bj.w, zj.x, zj.y, aj.w, invH, dwc, ar, avx, avy, avz, aE, sig);
     }
 
+    // ends a drain (see the FP32 kernel's)
+    __device__ __forceinline__ void settle() {
+        asm volatile(""
+                     : "+v"(ar), "+v"(avx), "+v"(avy), "+v"(avz), "+v"(aE), "+v"(sig),
+                       "+v"(cnt), "+v"(qr));
+    }
+
     // one walk over the stencil: real partners, or mirror partners (GHOST); IMG: the walk
     // around periodic image im of i (or of its mirror image).  The candidates are tested in
     // FP32 from the cell-relative records, as in the mixed kernel, and every one within the
@@ -362,58 +340,56 @@ struct Rates64 {
         const float ay0 = IMG && !GHOST ? amy : a32.y;
         const int cy0 = IMG && !GHOST ? tm.cy : t.cy;
         const uint32_t tag = (GHOST ? 1u : 0u) | (IMG ? (uint32_t)im << 1 : 0u);
-        int oy = st.R, oz = -st.R - 1;  // advanced to (-R, -R) before the first row
-        int k = 0, j0 = 0, len = 0, jlast = 0;
-        float ay = 0.f, az = 0.f, gz2 = 0.f;
-        for (;;) {
-            if (__any(qw - qr > kQ - kUS64)) {  // keep every ring at <= kQ - kUS64 entries
+        auto row = [&](int oy, int yy, int oz, int j0, int len) {
+            const float az = az0 - (float)oz * Df;
+            const float ay = ay0 - (float)(yy - cy0) * Df;
+            // the row i lies in (SPLIT: the lanes' rows differ)
+            const bool centre = !GHOST && !IMG && (SPLIT || (oy == 0 && oz == 0));
+            const int jlast = len > 0 ? j0 + len - 1 : 0;
+            int k = 0;
+            do {
+                // the slots' records from j0 + k on, the start clamped to the row's last
+                // record (the pack appends zero records after the n records)
+                const uint32_t jb = (uint32_t)min(j0 + k, jlast) * (uint32_t)sizeof(float4);
+                const float4 *Fb = (const float4 *)((const char *)F + jb);
+                const float *Db = PAIR ? (const float *)((const char *)d32 + (jb >> 2)) : nullptr;
+                float4 aj[kUS64];
 #pragma unroll
-                for (int p = 0; p < kPop64; ++p) drain<MIR, ZS>();
-                continue;
-            }
-            if (!__any(k < len)) {
-                if (++oy > st.R) {
-                    oy = -st.R;
-                    if (++oz > st.R) break;
-                    const float gz = slab_gap(st.zc, st.cz + oz);  // per plane of rows
-                    gz2 = gz * gz;
-                    az = az0 - (float)oz * Df;
+                for (int u = 0; u < kUS64; ++u) aj[u] = Fb[u];
+#pragma unroll
+                for (int u = 0; u < kUS64; ++u) {
+                    float dx = (aj[u].x + (aj[u].w - cx0) * Df) - ax0;
+                    float dy = aj[u].y - ay, dz = aj[u].z - az;
+                    if (GHOST) dy = 2.0f * wd - dy;
+                    const float r2 = (dx * dx + dy * dy) + dz * dz;
+                    float hj = hi32;
+                    if (PAIR) {
+                        const float Hj = fmaf(kd, Db[u], kdi);
+                        hj = Hj * Hj;
+                    }
+                    // the entry's record offset (16 j for a slot that can be accepted)
+                    const uint32_t jo = jb + (uint32_t)(u * sizeof(float4));
+                    bool acc = (k + u < len) & (r2 < hj);
+                    if (centre) acc = acc & (jo != self16);
+                    // the ring slot qw is free: write always, advance on acceptance
+                    slot(qw) = jo | tag;
+                    qw += acc ? 1 : 0;
                 }
-                const int yy = st.cy + oy, zz = st.cz + oz;
-                row_range(cs, g, st, on, yy, zz, gz2, j0, len);
-                jlast = len > 0 ? j0 + len - 1 : 0;
-                ay = ay0 - (float)(yy - cy0) * Df;
-                k = 0;
-                continue;
-            }
-            // the slots' records from j0 + k on, the start clamped to the row's last record
-            // (the pack appends kUS64 - 1 zero records after the n records)
-            const uint32_t jb = (uint32_t)min(j0 + k, jlast);
-            const float4 *Fb = (const float4 *)((const char *)F + jb * (uint32_t)sizeof(float4));
-            float4 aj[kUS64];
+                // keep every ring at <= kQ - kUS64 entries
+                if (__any(qw - qr > kQ - kUS64)) {
+                    do {
 #pragma unroll
-            for (int u = 0; u < kUS64; ++u) aj[u] = Fb[u];
-#pragma unroll
-            for (int u = 0; u < kUS64; ++u) {
-                const int j = j0 + k + u;
-                float dx = (aj[u].x + (aj[u].w - cx0) * Df) - ax0;
-                float dy = aj[u].y - ay, dz = aj[u].z - az;
-                if (GHOST) dy = 2.0f * wd - dy;
-                const float r2 = (dx * dx + dy * dy) + dz * dz;
-                float hj = hi32;
-                if (PAIR) {
-                    const double H = pc.kappa * (0.5 * (di + ld(dsz, j < jlast ? j : jlast)));
-                    hj = (float)(H * H) * (1.0f + kBand);
+                        for (int p = 0; p < kPop64; ++p) drain<MIR, ZS>();
+                        settle();
+                    } while (__any(qw - qr > kQ - kUS64));
                 }
-                // the entry's FP64 record offset (32 j for a slot that can be accepted)
-                const uint32_t jo = (jb + (uint32_t)u) * (uint32_t)sizeof(double4);
-                const bool acc = (k + u < len) & (GHOST || IMG || jo != self32) & (r2 < hj);
-                // the ring slot qw is free: write always, advance on acceptance
-                slot(qw) = jo | tag;
-                qw += acc ? 1 : 0;
-            }
-            k += kUS64;
-        }
+                k += kUS64;
+            } while (__any(k < len));
+        };
+        if (SPLIT)
+            walk_rows_split(cs, g, st, on, sub, ls, row);
+        else
+            walk_rows(cs, g, st, on, row);
     }
 
     // the walks around every periodic image some lane of the wave has (GHOST: around the
@@ -476,7 +452,7 @@ struct Rates64 {
             int e[kU] = {k < len ? ee.x : 0, k + 1 < len ? ee.y : 0};
             double4 aj[kU];
 #pragma unroll
-            for (int u = 0; u < kU; ++u) aj[u] = ld(A, e[u] & 0x7fffffff);
+            for (int u = 0; u < kU; ++u) aj[u] = A.at((uint32_t)e[u] << 4);
 #pragma unroll
             for (int u = 0; u < kU; ++u) {
                 const bool ghost = WALL && e[u] < 0;
@@ -486,7 +462,7 @@ struct Rates64 {
                 const bool acc = (k + u < len) && r2 < pc.H2;
                 // list entries carry the mirror flag in the sign bit
                 const uint32_t eu = (uint32_t)e[u];
-                slot(qw) = WALL ? (eu << 5) | (eu >> 31) : eu << 5;
+                slot(qw) = WALL ? (eu << 4) | (eu >> 31) : eu << 4;
                 qw += acc ? 1 : 0;
             }
             k += kU;
@@ -497,21 +473,22 @@ struct Rates64 {
 // Occupancy hint of 4 waves per SIMD (up to 128 VGPRs): with the FP32 candidate test the
 // kernel would spill at the 96 VGPRs of 5 waves (measured 9.22 against 7.72 ms on the porous
 // shock's first 20 steps).
-template <bool PAIR, bool WALL, bool LIST, bool PER>
-__global__ __launch_bounds__(kRate64Block, 4) void k_rates64(int64_t n, const double4 *__restrict__ A,
-                                                    const double4 *__restrict__ B,
+template <bool PAIR, bool WALL, bool LIST, bool PER, bool SPLIT>
+__global__ __launch_bounds__(kRate64Block, 4) void k_rates64(int64_t n, Split4 A, Split4 B,
                                                     const double2 *__restrict__ Cz,
                                                     const float4 *__restrict__ F,
                                                     const double *__restrict__ rho,
                                                     const double *__restrict__ dsz,
+                                                    const float *__restrict__ d32,
                                                     const int32_t *__restrict__ cs, GridDev g,
                                                     PairConst pc, const double *t_dev,
                                                     double t_host, RateOut o, int want_dt,
-                                                    VList vl) {
+                                                    VList vl, int ls) {
     if (LIST && vl.gate && *vl.gate == 0) return;
     __shared__ int qj[kQ][kRate64Block];
-    Rates64<PAIR, WALL, PER> k;
+    Rates64<PAIR, WALL, PER, SPLIT> k;
     k.qb = (char *)&qj[0][0];
+    k.d32 = d32;
     k.lane4 = threadIdx.x * (int)sizeof(int);
     k.A = A;
     k.B = B;
@@ -521,9 +498,13 @@ __global__ __launch_bounds__(kRate64Block, 4) void k_rates64(int64_t n, const do
     k.cs = cs;
     k.g = g;
     k.pc = pc;
-    const int64_t s =
-        xcd_block_upto(blockIdx.x, gridDim.x, kRate64Chunk) * kRate64Block + threadIdx.x;
-    k.self32 = (uint32_t)s * (uint32_t)sizeof(double4);
+    int64_t s = xcd_block_upto(blockIdx.x, gridDim.x, kRate64Chunk) * kRate64Block + threadIdx.x;
+    if (SPLIT) {
+        k.sub = (int)s & ((1 << ls) - 1);
+        k.ls = ls;
+        s >>= ls;
+    }
+    k.self16 = (uint32_t)s * (uint32_t)sizeof(float4);
     k.live = s < n;
     k.a = make_double4(0.0, 0.0, 0.0, 0.0);
     k.b = k.a;
@@ -540,8 +521,10 @@ __global__ __launch_bounds__(kRate64Block, 4) void k_rates64(int64_t n, const do
     k.t = make_stencil(g, k.a.x, k.a.y, k.a.z, pc.H);
     k.ti = k.t;
     k.sig = k.zc.y;
-    k.Df = (float)g.cell;
-    k.hi32 = (float)pc.H2 * (1.0f + kBand);
+    k.Df = uniform_f((float)g.cell);
+    k.hi32 = uniform_f((float)pc.H2 * (1.0f + kBand));
+    k.kd = PAIR ? pair_kd(pc.kappa) : 0.f;
+    k.kdi = k.kd * (float)k.di;
     k.yw = 0.0;
     k.vw2 = 0.0;
     k.wd = 0.f;
@@ -558,10 +541,21 @@ __global__ __launch_bounds__(kRate64Block, 4) void k_rates64(int64_t n, const do
     if (PER && k.live) k.nf = image_faces(pc, k.a.x, k.a.y, k.a.z);
     const int len = LIST && k.live ? min(vl.count[s], vl.cap) : 0;
     const int32_t *lst = LIST ? vl.idx + (k.live ? s * kVlChunk : 0) : nullptr;
-    const int cnt = *o.zflag == 0 ? k.template run<LIST, true>(lst, len, n)
-                                  : k.template run<LIST, false>(lst, len, n);
+    int cnt = *o.zflag == 0 ? k.template run<LIST, true>(lst, len, n)
+                            : k.template run<LIST, false>(lst, len, n);
+    if (SPLIT) {
+        k.ar = split_sum(k.ar, ls);
+        k.avx = split_sum(k.avx, ls);
+        k.avy = split_sum(k.avy, ls);
+        k.avz = split_sum(k.avz, ls);
+        k.aE = split_sum(k.aE, ls);
+        for (int h = 1; h < (1 << ls); h <<= 1) {
+            k.sig = fmax(k.sig, __shfl_xor(k.sig, h, 64));
+            cnt += __shfl_xor(cnt, h, 64);
+        }
+    }
     double dtv = INFINITY;
-    if (k.live) {
+    if (k.live && (!SPLIT || k.sub == 0)) {
         double ri = rho[s];
         double pre = 2.0 / ri;
         double drho = -2.0 * ri * k.ar;
@@ -588,21 +582,27 @@ __device__ __forceinline__ float fmax_nonneg(float a, float b) {
     return __int_as_float(max(__float_as_int(a), __float_as_int(b)));
 }
 
-template <bool ZS>
+// Each fused multiply-add is written out (no contraction by the compiler, whose choice of
+// the product that stays rounded moves with the surrounding code): the FP32 results do not
+// depend on how the walk around them is compiled.  YF: the y product of the closing speed is
+// the rounded one (else the x product).
+template <bool ZS, bool YF>
 __device__ __forceinline__ void pair32(bool use, float dx, float dy, float dz, float r2,
                                        const float4 &bi, const float4 &ci, float vxj, float vyj,
                                        float vzj, float Pj, float Zj, float cj, float Vj,
                                        float invH, float dwch, float &ar, float &avx, float &avy,
                                        float &avz, float &aE, float &sig) {
-#pragma clang fp contract(fast)
     // dwch = (210/pi)/H^5, so that dW/dr = -dwch r (1 - r/H)^3
-    const float ir = __builtin_amdgcn_rsqf(use ? r2 : 1.0f);
+    // (a lane without a partner may hold r2 = 0: kept finite)
+    const float ir = __builtin_amdgcn_rsqf(fmax_nonneg(r2, 1e-37f));
     const float r = r2 * ir;
-    const float a1 = 1.0f - r * invH;
+    const float a1 = fmaf(-r, invH, 1.0f);
     const float dWr = -(use ? dwch : 0.0f) * r * (a1 * a1 * a1);
     // v_L - v_R from the velocity difference and the raw offsets (no cancellation of bulk
     // motion); e = (dx, dy, dz) / r
-    const float vrel = (((bi.x - vxj) * dx + (bi.y - vyj) * dy) + (bi.z - vzj) * dz) * ir;
+    const float wx = bi.x - vxj, wy = bi.y - vyj, wz = bi.z - vzj;
+    const float wxy = YF ? fmaf(wx, dx, wy * dy) : fmaf(wy, dy, wx * dx);
+    const float vrel = fmaf(wz, dz, wxy) * ir;
     const float Zi = ci.x, Pi = bi.w;
     const float S = Zi + Zj;
     // (v_L - v*) S and P* S; S = 0 (both impedances zero) takes the mean state, written as
@@ -611,24 +611,23 @@ __device__ __forceinline__ void pair32(bool use, float dx, float dy, float dz, f
     const float iS = __builtin_amdgcn_rcpf(sok ? S : 2.0f);
     const float Zjd = sok ? Zj : 1.0f, Zid = sok ? Zi : 1.0f;
     const float dP = sok ? Pi - Pj : 0.0f, ZZ = sok ? Zi * Zj : 0.0f;
-    const float dvlS = Zjd * vrel - dP;
-    const float psS = (Zjd * Pi + Zid * Pj) + ZZ * vrel;
+    const float dvlS = fmaf(Zjd, vrel, -dP);
+    const float psS = fmaf(ZZ, vrel, fmaf(Zid, Pj, Pi * Zjd));
     // a lane without a partner adds exact zeros: its weight is 0 (the kernel constant selected
-    // to 0) and every factor it multiplies is finite (r2 = 1, finite offsets)
+    // to 0) and every factor it multiplies is finite (finite offsets)
     const float wS = (Vj * iS) * dWr;  // V_j dW/dr / S
     const float f = wS * psS;          // V_j dW/dr P*
     const float fr = f * ir;
     const float sp = fmax_nonneg(ci.y, cj) + fmaxf(vrel, 0.0f);
-    ar += wS * dvlS;
-    avx += fr * dx;
-    avy += fr * dy;
-    avz += fr * dz;
+    ar = fmaf(dvlS, wS, ar);
+    avx = fmaf(dx, fr, avx);
+    avy = fmaf(dy, fr, avy);
+    avz = fmaf(dz, fr, avz);
     // energy flux f v* = f v_L - f (v_L - v*); the f v_L part sums to v_i . sum_j f e_ij, which
     // the kernel adds once from the momentum sums
-    aE -= f * (dvlS * iS);
+    aE = fmaf(-(iS * dvlS), f, aE);
     sig = fmax_nonneg(sig, use ? sp : 0.0f);
 }
-
 
 // The exact FP64 membership test of a pair from its FP64 offsets, rounded as written (a
 // product, a product, a sum, a product, a sum): this function lies outside the
@@ -652,12 +651,13 @@ struct Rates32 {
     GridDev g;
     PairConst pc;
     char *qb;         // the wave's rings: kQ rows of kRate32Block float4 slots
+    const float *__restrict__ d32;  // pair-h mode: the sizes in FP32 (the test)
     int lane16;       // the lane's byte offset in a ring row
     uint32_t self16;  // byte offset of i's own records
     bool live, near_wall;
     float4 a, b, c;
     double xi, yi, zi, di, yw;  // yw: wall position along y
-    float wd, vw2, Df, cxf, lo, hi, dwch0;
+    float wd, vw2, Df, cxf, lo, hi, near, invH0, dwch0, kd, kdi;
     Stencil t, ti;               // stencils of i and of its mirror image
     // periodic images: i's faces (image_faces); the image the walk is on (wave-uniform mask),
     // its stencil, i's offsets from the image point's cell origin and that cell's x index
@@ -669,7 +669,7 @@ struct Rates32 {
     // slot's address is the counter masked to the ring, or'ed with the lane's offset;
     // unsigned, so that the fill level qw - qr stays exact if the counters wrap
     unsigned qw = 0, qr = 0;
-    int cnt = 0;
+    int drop = 0, ghosts = 0;
 
     __device__ __forceinline__ float4 &slot(unsigned q) {
         return *(float4 *)(qb + ((q & (kRing - 1)) | (unsigned)lane16));
@@ -680,7 +680,6 @@ struct Rates32 {
     // every lane pops its next partner, if it has one; MIR: the wave may hold mirror entries
     template <bool MIR, bool ZS>
     __device__ __forceinline__ void drain() {
-#pragma clang fp contract(fast)
         const bool has = qr != qw;
         const float4 q = slot(qr);
         qr += has ? kSlot : 0;
@@ -691,26 +690,27 @@ struct Rates32 {
         const int j = (int)(jo >> 4);
         const float4 bj = *(const float4 *)((const char *)B + jo);
         const float4 cj = *(const float4 *)((const char *)Cz + jo);
-        float invH = (float)pc.invH, dwch = dwch0;
-        float H2lo = lo;
+        float invH = invH0, dwch = dwch0;
+        float H2lo = lo, H2near = near;
         double H2d = pc.H2;
         if (PAIR) {
             const double H = pc.kappa * (0.5 * (di + dsz[j]));
             H2d = H * H;
             H2lo = (float)H2d * (1.0f - kBand);
-            invH = (float)(1.0 / H);
+            H2near = H2lo * 1e-4f;
+            invH = (float)rcp64(H > 0.0 ? H : 1.0);
             const float i2 = invH * invH;
             dwch = (float)(210.0 / M_PI) * (i2 * i2) * invH;
         }
         float qx = q.x, qy = q.y, qz = q.z;
-        float r2 = (qx * qx + qy * qy) + qz * qz;
+        float r2 = fmaf(qz, qz, fmaf(qx, qx, qy * qy));
         // a list walk queues exact FP64 members only, with offsets rounded from FP64
-        bool in = has && (LIST || r2 < H2lo);
+        bool use = has & (LIST ? r2 != 0.0f : r2 < H2lo);
         // (rare) near the support, decide membership in FP64; nearly coincident (r < H/100),
         // take the offsets from FP64 too: the cell-relative FP32 offsets carry ~1e-7 absolute
         // error, which would bend the direction e of so short a pair (and with it the
         // closing speed in the signal speed, which the kernel weight does not damp)
-        if (!LIST && has && (!(r2 < H2lo) || r2 < H2lo * 1e-4f)) {
+        if (!LIST && (has & (!(r2 < H2lo) | (r2 < H2near)))) {
             const double yj = ghost ? 2.0 * yw - ys[j] : ys[j];
             double ex = xs[j] - xi, ey = yj - yi, ez = zs[j] - zi;
             if (PER) {  // image mm: d = (x_j - x_i) - k L
@@ -718,16 +718,29 @@ struct Rates32 {
                 ey = ey - image_shift(pc, nf, mm, 1);
                 ez = ez - image_shift(pc, nf, mm, 2);
             }
-            in = member64(ex, ey, ez, H2d);
+            const bool in = member64(ex, ey, ez, H2d);
             qx = (float)ex;
             qy = (float)ey;
             qz = (float)ez;
-            r2 = (qx * qx + qy * qy) + qz * qz;
+            r2 = fmaf(qz, qz, fmaf(qy, qy, qx * qx));
+            use = in && r2 != 0.0f;  // a coincident partner counts and adds nothing
+            drop += in || ghost ? 0 : 1;
         }
-        cnt += (in && !ghost) ? 1 : 0;
-        pair32<ZS>(in && r2 != 0.0f, qx, qy, qz, r2, b, c, bj.x, ghost ? vw2 - bj.y : bj.y,
+        if (MIR) ghosts += has && ghost ? 1 : 0;
+        pair32<ZS, PAIR || LIST>(use, qx, qy, qz, r2, b, c, bj.x, ghost ? vw2 - bj.y : bj.y,
                    bj.z, bj.w, cj.x, cj.y, cj.z, invH, dwch, ar, avx, avy, avz, aE, sig);
     }
+
+    // Ends a drain: ties each live sum to one register, without which the compiler moves all of
+    // them to other registers and back on every trigger.
+    __device__ __forceinline__ void settle() {
+        asm volatile(""
+                     : "+v"(ar), "+v"(avx), "+v"(avy), "+v"(avz), "+v"(aE), "+v"(sig),
+                       "+v"(drop), "+v"(qr));
+    }
+
+    // |N(i)|: the entries queued less the mirror entries and those the FP64 test turned down
+    __device__ __forceinline__ int count() const { return (int)(qw / kSlot) - ghosts - drop; }
 
     // flat loop as in the FP64 kernel.  IMG: the walk around image point im of i (or of its
     // mirror image), offsets relative to that point's cells; the wall axis y is never periodic,
@@ -742,64 +755,55 @@ struct Rates32 {
         const float ay0 = IMG && !GHOST ? amy : a.y;
         const int cy0 = IMG && !GHOST ? tm.cy : t.cy;
         const uint32_t tag = (GHOST ? 1u : 0u) | (IMG ? (uint32_t)im << 1 : 0u);
-        int oy = st.R, oz = -st.R - 1;
-        int k = 0, j0 = 0, len = 0, jlast = 0;
-        float ay = 0.f, az = 0.f, gz2 = 0.f;
-        for (;;) {
-            // two pops per trigger: some lane holds kQ - 1 entries, most lanes hold several,
-            // and the loop's copies of the live sums are paid once per two pops
-            if (__any(qw - qr > (kQ - kUS) * kSlot)) {
-                drain<MIR, ZS>();
-                drain<MIR, ZS>();
-                continue;
-            }
-            if (!__any(k < len)) {
-                if (++oy > st.R) {
-                    oy = -st.R;
-                    if (++oz > st.R) break;
-                    // per plane of rows: squared z gap, i's z offset from the plane's cells
-                    const float gz = slab_gap(st.zc, st.cz + oz);
-                    gz2 = gz * gz;
-                    az = az0 - (float)oz * Df;
-                }
-                const int yy = st.cy + oy, zz = st.cz + oz;
-                row_range(cs, g, st, on, yy, zz, gz2, j0, len);
-                jlast = len > 0 ? j0 + len - 1 : 0;
-                // i's y offset from the row's cell origin (rows counted from i's own cell)
-                ay = ay0 - (float)(yy - cy0) * Df;
-                k = 0;
-                continue;
-            }
-            // the slots' records from j0 + k on, the start clamped to the row's last record:
-            // every load then reads a finite record (a lane with nothing left to pop reads the
-            // slot written last), up to kUS - 1 past the row, which the zero records the pack
-            // appends after the n records keep in bounds
-            const uint32_t jbo = (uint32_t)min(j0 + k, jlast) * (uint32_t)sizeof(float4);
-            const float4 *Ab = (const float4 *)((const char *)A + jbo);
-            float4 aj[kUS];
+        walk_rows(cs, g, st, on, [&](int oy, int yy, int oz, int j0, int len) {
+            // i's offsets from the row's cell origin (rows counted from i's own cell)
+            const float az = fmaf(-Df, (float)oz, az0);
+            const float ay = fmaf(-Df, (float)(yy - cy0), ay0);
+            const bool centre = !GHOST && !IMG && oy == 0 && oz == 0;  // the row i lies in
+            const int jlast = len > 0 ? j0 + len - 1 : 0;
+            int k = 0;
+            do {
+                // the slots' records from j0 + k on, the start clamped to the row's last
+                // record: every load then reads a finite record (a lane with nothing left to
+                // pop reads the slot written last), up to kUS - 1 past the row, which the zero
+                // records the pack appends after the n records keep in bounds
+                const uint32_t jb = (uint32_t)min(j0 + k, jlast) * (uint32_t)sizeof(float4);
+                const float4 *Ab = (const float4 *)((const char *)A + jb);
+                const float *Db = PAIR ? (const float *)((const char *)d32 + (jb >> 2)) : nullptr;
+                float4 aj[kUS];
 #pragma unroll
-            for (int u = 0; u < kUS; ++u) aj[u] = Ab[u];
+                for (int u = 0; u < kUS; ++u) aj[u] = Ab[u];
 #pragma unroll
-            for (int u = 0; u < kUS; ++u) {
-                const int j = j0 + k + u;
-                float dx = (aj[u].x + (aj[u].w - cx0) * Df) - ax0;
-                float dy = aj[u].y - ay, dz = aj[u].z - az;
-                if (GHOST) dy = 2.0f * wd - dy;
-                float r2 = (dx * dx + dy * dy) + dz * dz;
-                float hj = hi;
-                if (PAIR) {
-                    double H = pc.kappa * (0.5 * (di + ld(dsz, j < jlast ? j : jlast)));
-                    hj = (float)(H * H) * (1.0f + kBand);
+                for (int u = 0; u < kUS; ++u) {
+                    const float dx = fmaf(aj[u].w - cx0, Df, aj[u].x) - ax0;
+                    float dy = aj[u].y - ay;
+                    const float dz = aj[u].z - az;
+                    if (GHOST) dy = fmaf(2.0f, wd, -dy);
+                    const float r2 = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
+                    float hj = hi;
+                    if (PAIR) {
+                        const float Hj = fmaf(kd, Db[u], kdi);
+                        hj = Hj * Hj;
+                    }
+                    // the entry's record offset (16 j for a slot that can be accepted); one
+                    // select per slot: the tests combine as lane masks
+                    const uint32_t jo = jb + (uint32_t)(u * sizeof(float4));
+                    bool acc = (k + u < len) & (r2 < hj);
+                    if (centre) acc = acc & (jo != self16);
+                    slot(qw) = make_float4(dx, dy, dz, __uint_as_float(jo | tag));
+                    qw += acc ? kSlot : 0;
                 }
-                // the entry's record offset (16 j for a slot that can be accepted); one select
-                // per slot: the three tests combine as lane masks
-                const uint32_t jo = jbo + (uint32_t)(u * sizeof(float4));
-                const bool acc = (k + u < len) & (GHOST || IMG || jo != self16) & (r2 < hj);
-                slot(qw) = make_float4(dx, dy, dz, __uint_as_float(jo | tag));
-                qw += acc ? kSlot : 0;
-            }
-            k += kUS;
-        }
+                // two pops per trigger: some lane holds kQ - 1 entries, most lanes several
+                if (__any(qw - qr > (kQ - kUS) * kSlot)) {
+                    do {
+                        drain<MIR, ZS>();
+                        drain<MIR, ZS>();
+                        settle();
+                    } while (__any(qw - qr > (kQ - kUS) * kSlot));
+                }
+                k += kUS;
+            } while (__any(k < len));
+        });
     }
 
     // Point of image m of i (GHOST: of its mirror image) and its stencil and offsets.
@@ -887,7 +891,7 @@ struct Rates32 {
 };
 
 template <bool PAIR, bool WALL, bool LIST, bool PER>
-__global__ __launch_bounds__(kRate32Block) void k_rates32(int64_t n, const float4 *__restrict__ A,
+__global__ __launch_bounds__(kRate32Block, 4) void k_rates32(int64_t n, const float4 *__restrict__ A,
                                                     const float4 *__restrict__ B,
                                                     const float4 *__restrict__ Cz,
                                                     const double *__restrict__ xs,
@@ -895,6 +899,7 @@ __global__ __launch_bounds__(kRate32Block) void k_rates32(int64_t n, const float
                                                     const double *__restrict__ zs,
                                                     const double *__restrict__ rho,
                                                     const double *__restrict__ dsz,
+                                                    const float *__restrict__ d32,
                                                     const int32_t *__restrict__ cs, GridDev g,
                                                     PairConst pc, const double *t_dev,
                                                     double t_host, RateOut o, int want_dt,
@@ -917,6 +922,7 @@ __global__ __launch_bounds__(kRate32Block) void k_rates32(int64_t n, const float
     k.g = g;
     k.pc = pc;
     k.qb = (char *)&qd[0][0];
+    k.d32 = d32;
     k.lane16 = threadIdx.x * (int)sizeof(float4);
     const int64_t s =
         xcd_block_upto(blockIdx.x, gridDim.x, kRate32Chunk) * kRate32Block + threadIdx.x;
@@ -937,11 +943,15 @@ __global__ __launch_bounds__(kRate32Block) void k_rates32(int64_t n, const float
     }
     k.t = make_stencil(g, k.xi, k.yi, k.zi, pc.H);
     k.sig = k.c.y;
-    k.Df = (float)g.cell;
+    k.Df = uniform_f((float)g.cell);
     k.cxf = (float)k.t.cx;
-    k.lo = (float)pc.H2 * (1.0f - kBand);
-    k.hi = (float)pc.H2 * (1.0f + kBand);
-    k.dwch0 = (float)(pc.dwc * pc.invH);
+    k.lo = uniform_f((float)pc.H2 * (1.0f - kBand));
+    k.hi = uniform_f((float)pc.H2 * (1.0f + kBand));
+    k.near = uniform_f(k.lo * 1e-4f);
+    k.kd = PAIR ? pair_kd(pc.kappa) : 0.f;
+    k.kdi = k.kd * (float)k.di;
+    k.invH0 = uniform_f((float)pc.invH);
+    k.dwch0 = uniform_f((float)(pc.dwc * pc.invH));
     k.ti = k.t;
     k.yw = 0.0;
     k.wd = 0.f;
@@ -952,7 +962,7 @@ __global__ __launch_bounds__(kRate32Block) void k_rates32(int64_t n, const float
         k.yw = pc.wall_y0 + pc.wall_v * tt;
         k.near_wall = k.live && mirror_band(g, k.yi, k.yw, pc.H);
         k.wd = (float)(k.yw - k.yi);
-        k.vw2 = (float)(2.0 * pc.wall_v);
+        k.vw2 = uniform_f((float)(2.0 * pc.wall_v));
         k.ti = image_stencil(g, k.t, 2.0 * k.yw - k.yi);
     }
     k.tm = k.t;
@@ -976,7 +986,7 @@ __global__ __launch_bounds__(kRate32Block) void k_rates32(int64_t n, const float
                           (double)k.b.z * (double)k.avz;
         o.E[s] = pre * ((double)k.aE + vf);
         if (o.sig) o.sig[s] = (double)k.sig;
-        if (o.cnt) o.cnt[s] = k.cnt;
+        if (o.cnt) o.cnt[s] = k.count();
         dtv = fmin((PAIR ? k.di : pc.h_dt) / (double)k.sig, ri / fabs(drho));
     }
     if (want_dt) wave_min_to(dtv, o.dtmin);
@@ -993,22 +1003,26 @@ hipError_t launch_rates(int64_t n, int mixed, const GridDev &g, const PairConst 
               w.zflag};
     VList vl{vl_count, vl_idx, vl_cap, gate};
     const unsigned nb32 = (unsigned)((n + kRate32Block - 1) / kRate32Block);
-    const unsigned nb64 = (unsigned)((n + kRate64Block - 1) / kRate64Block);
+    const int ls = vl_idx ? 0 : split_log2(n);
+    const unsigned nb64 = (unsigned)(((n << ls) + kRate64Block - 1) / kRate64Block);
     const bool pair = pc.pair_mode != 0, wall = pc.wall != 0, list = vl_idx != nullptr;
     const bool per = pc.per != 0;
     if (list && (pair || per)) return hipErrorInvalidValue;
+#define CSPH_RATES64_ARGS                                                                     \
+    n, split4(w.recA, n), split4(w.recB, n), (const double2 *)w.recC, (const float4 *)w.recF, \
+        rho_sorted, d_sorted, (const float *)w.rank, w.cs, g, pc, t_dev, t_host, o, want_dt, vl, ls
 #define CSPH_RATES_CASE(P, W, L, X)                                                           \
     if (pair == P && wall == W && list == L && per == X) {                                    \
         if (mixed)                                                                            \
             k_rates32<P, W, L, X><<<nb32, kRate32Block, 0, st>>>(                             \
                 n, (const float4 *)w.recA, (const float4 *)w.recB, (const float4 *)w.recC,    \
-                sorted[0], sorted[1], sorted[2], rho_sorted, d_sorted, w.cs, g, pc, t_dev,    \
+                sorted[0], sorted[1], sorted[2], rho_sorted, d_sorted, (const float *)w.rank, \
+                w.cs, g, pc, t_dev,                                                           \
                 t_host, o, want_dt, vl);                                                      \
+        else if (ls > 0 && !L)                                                                \
+            k_rates64<P, W, false, X, true><<<nb64, kRate64Block, 0, st>>>(CSPH_RATES64_ARGS); \
         else                                                                                  \
-            k_rates64<P, W, L, X><<<nb64, kRate64Block, 0, st>>>(                             \
-                n, (const double4 *)w.recA, (const double4 *)w.recB,                          \
-                (const double2 *)w.recC, (const float4 *)w.recF, rho_sorted, d_sorted, w.cs,  \
-                g, pc, t_dev, t_host, o, want_dt, vl);                                        \
+            k_rates64<P, W, L, X, false><<<nb64, kRate64Block, 0, st>>>(CSPH_RATES64_ARGS);   \
     }
     CSPH_RATES_CASE(false, false, false, false)
     CSPH_RATES_CASE(false, true, false, false)
@@ -1021,6 +1035,7 @@ hipError_t launch_rates(int64_t n, int mixed, const GridDev &g, const PairConst 
     CSPH_RATES_CASE(true, false, false, true)
     CSPH_RATES_CASE(true, true, false, true)
 #undef CSPH_RATES_CASE
+#undef CSPH_RATES64_ARGS
     return hipGetLastError();
 }
 

@@ -13,7 +13,7 @@
 namespace csph {
 
 template <bool WALL>
-__global__ __launch_bounds__(kBlock) void k_vlist(int64_t n, const double4 *__restrict__ A,
+__global__ __launch_bounds__(kBlock) void k_vlist(int64_t n, Split4 A,
                                                   const int32_t *__restrict__ cs, GridDev g,
                                                   double R, double R2, double yw, int cap,
                                                   int32_t *__restrict__ count,
@@ -42,43 +42,31 @@ __global__ __launch_bounds__(kBlock) void k_vlist(int64_t n, const double4 *__re
         const bool on = live && (!ghost || near);
         // mirror partners: the particles on the stencil around the image of i
         const Stencil &st = ghost ? ti : t;
-        int oy = st.R, oz = -st.R - 1;
-        int k = 0, j0 = 0, len = 0, jlast = 0;
-        for (;;) {
-            if (!__any(k < len)) {
-                if (++oy > st.R) {
-                    oy = -st.R;
-                    if (++oz > st.R) break;
-                }
-                const int zz = st.cz + oz;
-                const float gz = slab_gap(st.zc, zz);
-                row_range(cs, g, st, on, st.cy + oy, zz, gz * gz, j0, len);
-                jlast = len > 0 ? j0 + len - 1 : 0;
-                k = 0;
-                continue;
-            }
+        walk_rows(cs, g, st, on, [&](int, int, int, int j0, int len) {
+            const int jlast = len > 0 ? j0 + len - 1 : 0;
+            for (int k = 0; __any(k < len); k += kU) {
 #pragma unroll
-            for (int u = 0; u < kU; ++u) {
-                const int j = min(j0 + k + u, jlast);
-                const double4 aj = ld(A, j);
-                const double yj = ghost ? 2.0 * yw - aj.y : aj.y;
-                const double dx = aj.x - xi, dy = yj - yi, dz = aj.z - zi;
-                const double r2 = ((dx * dx) + (dy * dy)) + (dz * dz);
-                const bool acc = (k + u < len) && (ghost || j != (int)s) && r2 < R2;
-                if (acc) {
-                    stage[c & (kVlChunk - 1)] = ghost ? (j | (int)0x80000000) : j;
-                    ++c;
-                    if ((c & (kVlChunk - 1)) == 0) {  // chunk full: store it (within cap)
-                        if (c <= cap) {
-                            chunk[0] = make_int4(stage[0], stage[1], stage[2], stage[3]);
-                            chunk[1] = make_int4(stage[4], stage[5], stage[6], stage[7]);
+                for (int u = 0; u < kU; ++u) {
+                    const int j = min(j0 + k + u, jlast);
+                    const double4 aj = A.at((uint32_t)j * (uint32_t)sizeof(double2));
+                    const double yj = ghost ? 2.0 * yw - aj.y : aj.y;
+                    const double dx = aj.x - xi, dy = yj - yi, dz = aj.z - zi;
+                    const double r2 = ((dx * dx) + (dy * dy)) + (dz * dz);
+                    const bool acc = (k + u < len) && (ghost || j != (int)s) && r2 < R2;
+                    if (acc) {
+                        stage[c & (kVlChunk - 1)] = ghost ? (j | (int)0x80000000) : j;
+                        ++c;
+                        if ((c & (kVlChunk - 1)) == 0) {  // chunk full: store it (within cap)
+                            if (c <= cap) {
+                                chunk[0] = make_int4(stage[0], stage[1], stage[2], stage[3]);
+                                chunk[1] = make_int4(stage[4], stage[5], stage[6], stage[7]);
+                            }
+                            chunk += cstride;
                         }
-                        chunk += cstride;
                     }
                 }
             }
-            k += kU;
-        }
+        });
     }
     if (live) {
         // the last, partly filled chunk (entries past the count are never read)
@@ -118,12 +106,13 @@ __global__ __launch_bounds__(kBlock) void k_disp(int64_t n, const double *__rest
     }
 }
 
-hipError_t launch_vlist(int64_t n, const double4 *A, const int32_t *cs, const GridDev &g,
+hipError_t launch_vlist(int64_t n, const void *recA, const int32_t *cs, const GridDev &g,
                         double R, int wall, double yw, int cap, int32_t *count, int32_t *idx,
                         unsigned long long *over, hipStream_t st) {
     if (n <= 0) return hipSuccess;
     unsigned nb = (unsigned)((n + kBlock - 1) / kBlock);
     const double R2 = R * R;
+    const Split4 A = split4(recA, n);
     if (wall)
         k_vlist<true><<<nb, kBlock, 0, st>>>(n, A, cs, g, R, R2, yw, cap, count, idx, over);
     else

@@ -35,13 +35,66 @@ __device__ __forceinline__ T ld(const T *__restrict__ base, int idx) {
     return *(const T *)((const char *)base + (uint32_t)idx * (uint32_t)sizeof(T));
 }
 
-// Per-particle view of the stencil: cell, position in cell units, reach.
+// Records of four doubles kept as two arrays of 16-byte halves (n records each): a wave
+// gathering the records of neighbouring particles then reads whole lines in each of its two
+// loads, where an array of 32-byte records gives it every other 16 bytes of twice the lines.
+// off: the record's byte offset in either array (16 j).
+struct Split4 {
+    const double2 *__restrict__ lo;
+    const double2 *__restrict__ hi;
+    __device__ __forceinline__ double4 at(uint32_t off) const {
+        const double2 a = *(const double2 *)((const char *)lo + off);
+        const double2 b = *(const double2 *)((const char *)hi + off);
+        return make_double4(a.x, a.y, b.x, b.y);
+    }
+    __device__ __forceinline__ double4 operator[](int64_t j) const {
+        return make_double4(lo[j].x, lo[j].y, hi[j].x, hi[j].y);
+    }
+};
+inline Split4 split4(const void *rec, int64_t n) {
+    return Split4{(const double2 *)rec, (const double2 *)rec + n};
+}
+
+// A wave-uniform float in a scalar register (it would otherwise hold a vector register, since
+// the scalar unit has no floating point to form it in).
+__device__ __forceinline__ float uniform_f(float v) {
+    return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
+}
+
+// 1/sqrt(x) and 1/x for x > 0 in FP64: the hardware estimate y (v_rsq_f64, v_rcp_f64, relative
+// error d of about 2^-23) refined by one step of third order.  With e = 1 - x y^2 = O(d),
+// 1/sqrt(x) = y (1 - e)^(-1/2) = y (1 + e/2 + 3 e^2/8 + O(d^3)); with e = 1 - x y,
+// 1/x = y / (1 - e) = y (1 + e + e^2 + O(d^3)): d^3 lies below FP64's last bit, so the result
+// is within a few ulp (not correctly rounded: the rates are compared with a 1e-12 tolerance),
+// in 5 and 3 operations where two Newton steps take 8 and 4.  They replace the compiler's
+// correctly rounded FP64 square root and divisions, which take several times the instructions.
+__device__ __forceinline__ double rsqrt64(double x) {
+#pragma clang fp contract(fast)
+    const double y = __builtin_amdgcn_rsq(x);
+    const double e = fma(-x * y, y, 1.0);
+    return fma(y * e, fma(0.375, e, 0.5), y);
+}
+
+__device__ __forceinline__ double rcp64(double x) {
+#pragma clang fp contract(fast)
+    const double y = __builtin_amdgcn_rcp(x);
+    const double e = fma(-x, y, 1.0);
+    return fma(y, fma(e, e, e), y);
+}
+
+// Per-particle view of the stencil: cell, position within the cell in cell units (the
+// difference formed in FP64, so it stays exact to ~1e-7 on a mesh of any length), reach.
 struct Stencil {
     int cx, cy, cz;
-    float xc, yc, zc;  // (x - origin) / D
+    float fx, fy, fz;  // (x - origin) / D - cx; outside [0, 1) off the mesh
     float w2;          // (support/D)^2 with margin
     int R;
 };
+
+// Offset from cell c of coordinate v (in cell units), bounded for positions far off the mesh.
+__device__ __forceinline__ float cell_offset(double v, double o, double inv, int c) {
+    return (float)fmin(fmax((v - o) * inv - (double)c, -1048576.0), 1048576.0);
+}
 
 __device__ __forceinline__ Stencil make_stencil(const GridDev &g, double x, double y, double z,
                                                 double H) {
@@ -49,11 +102,11 @@ __device__ __forceinline__ Stencil make_stencil(const GridDev &g, double x, doub
     t.cx = cell_coord(x, g.ox, g.inv, g.dx);
     t.cy = cell_coord(y, g.oy, g.inv, g.dy);
     t.cz = cell_coord(z, g.oz, g.inv, g.dz);
-    t.xc = (float)((x - g.ox) * g.inv);
-    t.yc = (float)((y - g.oy) * g.inv);
-    t.zc = (float)((z - g.oz) * g.inv);
+    t.fx = cell_offset(x, g.ox, g.inv, t.cx);
+    t.fy = cell_offset(y, g.oy, g.inv, t.cy);
+    t.fz = cell_offset(z, g.oz, g.inv, t.cz);
     float hc = (float)(H * g.inv) * 1.0001f + 1e-3f;
-    t.w2 = hc * hc;
+    t.w2 = uniform_f(hc * hc);
     t.R = g.reach;
     return t;
 }
@@ -69,7 +122,7 @@ __device__ __forceinline__ Stencil image_stencil(const GridDev &g, const Stencil
     Stencil s = t;
     const double f = floor((y_image - g.oy) * g.inv);
     s.cy = (int)fmin(fmax(f, -1048576.0), 1048576.0);
-    s.yc = (float)((y_image - g.oy) * g.inv);
+    s.fy = cell_offset(y_image, g.oy, g.inv, s.cy);
     return s;
 }
 
@@ -110,15 +163,15 @@ __device__ __forceinline__ Stencil shifted_stencil(const GridDev &g, Stencil s, 
                                                    double py, double pz) {
     if (m & 1) {
         s.cx = free_cell(px, g.ox, g.inv);
-        s.xc = (float)((px - g.ox) * g.inv);
+        s.fx = cell_offset(px, g.ox, g.inv, s.cx);
     }
     if (m & 2) {
         s.cy = free_cell(py, g.oy, g.inv);
-        s.yc = (float)((py - g.oy) * g.inv);
+        s.fy = cell_offset(py, g.oy, g.inv, s.cy);
     }
     if (m & 4) {
         s.cz = free_cell(pz, g.oz, g.inv);
-        s.zc = (float)((pz - g.oz) * g.inv);
+        s.fz = cell_offset(pz, g.oz, g.inv, s.cz);
     }
     return s;
 }
@@ -131,36 +184,131 @@ __device__ __forceinline__ bool mirror_band(const GridDev &g, double y, double y
     return y - yw < H + fmax(yw - ymin, 0.0);
 }
 
-// Distance in cell units from coordinate c to the slab [k, k+1) (0 inside),
-// shrunk by a margin.
-__device__ __forceinline__ float slab_gap(float c, int k) {
-    float d = fmaxf(fmaxf((float)k - c, c - (float)(k + 1)), 0.0f);
-    return fmaxf(d - 1e-3f, 0.0f);
+// Gap in cell units between a point at offset f from its cell and the cell o places on
+// (0 inside), shrunk by a margin of 1e-3: |o + 1/2 - f| is the distance to that cell's middle.
+__device__ __forceinline__ float cell_gap(float o, float f) {
+    return fmaxf(fabsf(o - (f - 0.5f)) - 0.501f, 0.0f);
 }
 
-// Candidate range [j0, j0+len) of row (yy, zz) for a particle (or its
-// image): the cells of the row within the chord its support sphere cuts
-// through the row.  gz2 = squared z gap.  Branch-free per lane; a row off the
-// mesh or missing the sphere gets len = 0, and when it does so for every lane
-// of the wave the cell-range loads are skipped.
-__device__ __forceinline__ void row_range(const int32_t *__restrict__ cs, const GridDev &g,
-                                          const Stencil &t, bool on, int yy, int zz, float gz2,
-                                          int &j0, int &len) {
-    const bool inb = on && zz >= 0 && zz < g.dz && yy >= 0 && yy < g.dy;
-    const float gy = slab_gap(t.yc, yy);
-    const float rem = t.w2 - (gy * gy + gz2);
-    // chord half-width; v_sqrt_f32 (1 ulp) is ample under the margins
-    const float hw = __builtin_amdgcn_sqrtf(fmaxf(rem, 0.0f)) * 1.0001f + 1e-3f;
-    const int xa = max(max((int)floorf(t.xc - hw), t.cx - t.R), 0);
-    const int xb = min(min((int)floorf(t.xc + hw), t.cx + t.R), g.dx - 1);
-    const bool ok = inb && rem > 0.0f && xb >= xa;
+// Squared support left for a row of plane zz after the z gap (cell units); -1 when no row of
+// the plane counts (off the mesh, or a lane that does not walk).
+__device__ __forceinline__ float plane_rem(const GridDev &g, const Stencil &t, bool on, int oz,
+                                           int zz) {
+    const float gz = cell_gap((float)oz, t.fz);
+    return on && (unsigned)zz < (unsigned)g.dz ? t.w2 - gz * gz : -1.0f;
+}
+
+// Candidate range [j0, j0+len) of row (yy, zz), `key` its first cell's: the cells of the row
+// within the chord the support sphere cuts through it.  Branch-free per lane; a row off the
+// mesh or missing the sphere gets len = 0, and when it does so for every lane of the wave the
+// chord and the cell-range loads are skipped (and false returned).
+__device__ __forceinline__ bool row_range(const int32_t *__restrict__ cs, const GridDev &g,
+                                          const Stencil &t, float rem_z, int oy, int yy,
+                                          uint32_t key, int &j0, int &len) {
+    const float gy = cell_gap((float)oy, t.fy);
+    const float rem = rem_z - gy * gy;
+    bool ok = rem > 0.0f && (unsigned)yy < (unsigned)g.dy;
     j0 = 0;
     len = 0;
-    if (__any(ok)) {
-        const int row = (int)cell_key(g, 0, yy, zz);
-        const int ia = ok ? row + xa : 0, ib = ok ? row + xb + 1 : 0;
-        j0 = ld(cs, ia);
-        len = ld(cs, ib) - j0;
+    if (!__any(ok)) return false;
+    // chord half-width; v_sqrt_f32 (1 ulp) is ample under the margins (a lane that is not ok may
+    // take the root of a negative number: it is given an empty range below)
+    const float hw = __builtin_amdgcn_sqrtf(rem) * 1.0001f + 1e-3f;
+    const int xa = max(t.cx + (int)floorf(t.fx - hw), 0);
+    const int xb = min(t.cx + (int)floorf(t.fx + hw), g.dx - 1);
+    ok = ok && xb >= xa;
+    const int ia = ok ? (int)key + xa : 0, ib = ok ? (int)key + xb + 1 : 0;
+    j0 = ld(cs, ia);
+    len = ld(cs, ib) - j0;
+    return __any(len > 0);
+}
+
+// Candidates whose FP32 squared distance lies within this relative band of the squared
+// support are decided in FP64 from the FP64 positions (the FP32 error of r^2 is below 1e-6
+// relative for offsets within a few cells), so every kernel accepts exactly the FP64
+// neighbour set.
+constexpr float kBand = 4e-5f;
+// Pair-h mode: the FP32 test takes (kd d_i + kd d_j)^2 for H_ij^2 (1 + kBand), with room for
+// the rounding of the sizes.
+inline __device__ float pair_kd(double kappa) {
+    return uniform_f((float)(0.5 * kappa) * (1.0f + 0.5f * kBand + 1e-6f));
+}
+// Zero records after the n FP32 stencil records (cell-relative offsets, read by the candidate
+// tests): a walk reads up to kRecPad records past a row's last one.
+constexpr int kRecPad = 2;
+
+// Walks the rows (fixed y, z) of a lane's stencil in the order z, then y, calling
+// row(oy, yy, oz, j0, len), some lane's len > 0, for every row that some lane of the wave has candidates in.  The
+// offsets are wave-uniform; a row's key is carried from row to row (one addition) and formed
+// anew where some lane enters another slab, since its three 32-bit products issue at a
+// quarter of the rate; the z gap is squared once per plane, and a plane off every lane's mesh
+// or sphere is left out.
+template <typename F>
+__device__ __forceinline__ void walk_rows(const int32_t *__restrict__ cs, const GridDev &g,
+                                          const Stencil &t, bool on, F &&row) {
+    for (int oz = -t.R; oz <= t.R; ++oz) {
+        const int zz = t.cz + oz;
+        const float rem_z = plane_rem(g, t, on, oz, zz);
+        if (!__any(rem_z > 0.0f)) continue;
+        int yy = t.cy - t.R;
+        uint32_t key = cell_key(g, 0, yy, zz);
+        for (int oy = -t.R;;) {
+            int j0, len;
+            if (row_range(cs, g, t, rem_z, oy, yy, key, j0, len)) row(oy, yy, oz, j0, len);
+            if (++oy > t.R) break;
+            ++yy;
+            key = __any((yy & g.ymask) == 0) ? cell_key(g, 0, yy, zz) : key + (uint32_t)g.dx;
+        }
+    }
+}
+
+// ---------------------------------------------------------------- particles shared by lanes
+//
+// A small set leaves the chip idle with one lane per particle: 4 096 particles are 64 waves on
+// 1 024 SIMDs, and the FP64 rates of such a set took the ~180 us one wave needs for its walk.
+// The FP64 kernels then give each particle 2^ls neighbouring lanes, which deal its stencil rows
+// out among themselves (or, where the stencil has only 3 x 3 long rows, each row's candidates)
+// and add up their sums at the end in a fixed tree.  The results differ from the one-lane sums
+// by the order of the additions only; the FP32 kernels keep one lane per particle, whose sums
+// are taken in the walk's order.
+constexpr int kSplitMax = 4;
+constexpr int64_t kSplitLanes = 4096 * 64;  // lanes that fill the chip at four waves per SIMD
+
+inline int split_log2(int64_t n) {
+    int ls = 0;
+    while (ls < kSplitMax && (n << (ls + 1)) <= kSplitLanes) ++ls;
+    return ls;
+}
+
+// v summed over the 2^ls lanes of each particle (every lane gets the sum).
+__device__ __forceinline__ double split_sum(double v, int ls) {
+    for (int o = 1; o < (1 << ls); o <<= 1) v += __shfl_xor(v, o, 64);
+    return v;
+}
+
+// walk_rows for a lane that takes share `sub` of 2^ls of its particle's candidates.
+template <typename F>
+__device__ __forceinline__ void walk_rows_split(const int32_t *__restrict__ cs, const GridDev &g,
+                                                const Stencil &t, bool on, int sub, int ls,
+                                                F &&row) {
+    const int W = 2 * t.R + 1;
+    const bool deal = t.R > 1;  // rows dealt out, else each row's candidates cut into shares
+    const float iw = 1.0f / (float)W;
+    for (int q0 = 0; q0 < W * W; q0 += deal ? 1 << ls : 1) {
+        const int q = q0 + (deal ? sub : 0);
+        // q / W for q < 16 641 + 16, W <= 129: (q + 1/2) / W lies at least 1/258 from an integer
+        const int z = (int)(((float)q + 0.5f) * iw);
+        const int oz = z - t.R, oy = q - z * W - t.R;
+        const int yy = t.cy + oy, zz = t.cz + oz;
+        const float rem_z = plane_rem(g, t, on && q < W * W, oz, zz);
+        int j0, len;
+        if (!row_range(cs, g, t, rem_z, oy, yy, cell_key(g, 0, yy, zz), j0, len)) continue;
+        if (!deal) {
+            const int share = (len + (1 << ls) - 1) >> ls, a = share * sub;
+            j0 = len > a ? j0 + a : 0;
+            len = max(min(len - a, share), 0);
+        }
+        row(oy, yy, oz, j0, len);
     }
 }
 
