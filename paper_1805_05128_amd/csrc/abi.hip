@@ -558,6 +558,28 @@ static csph_status need_ws(size_t have, int64_t n, int64_t ncell, size_t *ws_nee
     return CSPH_OK;
 }
 
+// The mesh `g` with cells of a third of its size, for passes whose results do not depend on the
+// mesh: where the cells are as large as the support, the 27 cells around a particle hold ~6x
+// its neighbours, the rows of thirds clipped to the support ~1.7x.  false (and g as it is)
+// when the stencil is finer already, or the set so sparse that the cells would outnumber the
+// particles fourfold.
+static bool refine_grid(csph_grid *g, int64_t n, double Hmax) {
+    const double D = g->cell / 3.0;
+    if (g->reach != 1 || g->ncell > (4 * n + 4096) / 27) return false;
+    csph_grid f = *g;
+    f.cell = D;
+    f.inv_cell = 1.0 / D;
+    f.reach = 3.0 * D >= Hmax ? 3 : 4;
+    f.ncell = 1;
+    for (int a = 0; a < 3; ++a) {
+        f.dims[a] = 3 * g->dims[a];
+        f.ncell *= f.dims[a];
+    }
+    f.nkey = f.ncell;
+    *g = f;
+    return true;
+}
+
 // A mesh the caller gives for a step (csph_step_mesh): a positive cell, consistent dims and
 // cell count, and a stencil reach covering the support H.
 static csph_status check_mesh(const csph_grid *m, double H) {
@@ -728,12 +750,19 @@ csph_status csph_neighbors(const csph_state *s, const csph_params *p, int64_t *o
     const csph_state sv = kernel_view(*s, kernel_axes(p));
     r = make_grid(sv.x, sv.y, sv.z, s->d, n, p, ws, ws_bytes, st, &g, &dmax, &ymin, true);
     if (r) return r;
+    PairConst pc = pair_const(p, dmax);
+    // thirds of the cells where the workspace holds them; one too short for the mesh asked for
+    // is told the size that holds them
+    csph_grid fine = g;
+    if (refine_grid(&fine, n, pc.H) &&
+        (ws_bytes >= ws_layout(nullptr, nullptr, n, fine.ncell) ||
+         ws_bytes < ws_layout(nullptr, nullptr, n, g.ncell)))
+        g = fine;
     r = need_ws(ws_bytes, n, g.ncell, ws_needed);
     if (r) return r;
     Ws w;
     ws_layout(&w, ws, n, g.ncell);
     GridDev gd = grid_dev(g, true, ymin);
-    PairConst pc = pair_const(p, dmax);
     const double *dd = p->h_mode == CSPH_H_PAIR ? s->d : nullptr;
     ProfScope pn(CSPH_PROF_NEIGHBORS, st);
     CSPH_HIP(launch_bin(sv.x, sv.y, sv.z, n, gd, w, w.perm, nullptr, w.cs, st));

@@ -60,6 +60,20 @@ __device__ void heap_sort(int32_t *a, int c) {
     }
 }
 
+// One wave per particle: the lanes take the particle's stencil rows (64 at a time), clipped to
+// the chord of the support, lay the rows' candidates end to end in LDS (row by row where they
+// are too many) and test four of them each at once; the accepted ones are appended in candidate
+// order, ranked among themselves in LDS and stored ascending.  A thread per particle walked
+// ~570 candidates by itself, stored its row scattered and heap-sorted it in memory: for 83 143
+// particles off the lattice (H = 3, ~92 neighbours) the count took 142 us and the fill 1 224 us;
+// now 61 and 122 us (98 and 166 us on cells of the support's size, which the export cuts in
+// three), bound by vector issue: ~350 instructions a particle for the search, ~370 for the ranks.
+constexpr int kNbrWaves = kBlock / 64;
+constexpr int kNbrList = 1024;     // candidates laid out at once
+constexpr int kNbrShort = 32;      // longest row its own lane lays out
+constexpr int kNbrBatch = 4;       // 64-candidate tests in flight
+constexpr int kNbrCap = 512;       // neighbours ranked in LDS; a longer row is heap-sorted
+
 template <bool PAIR, bool FILL, bool PER>
 __global__ __launch_bounds__(kBlock) void k_nbr(int64_t n, GridDev g, PairConst pc,
                                                 const double *__restrict__ x,
@@ -71,66 +85,153 @@ __global__ __launch_bounds__(kBlock) void k_nbr(int64_t n, GridDev g, PairConst 
                                                 int32_t *__restrict__ count_orig,
                                                 const int64_t *__restrict__ offsets,
                                                 int32_t *__restrict__ idx) {
-    int64_t s = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (s >= n) return;
-    double xi = x[s], yi = y[s], zi = z[s];
-    double di = PAIR ? d[s] : 0.0;
-    const int R = g.reach;
+    __shared__ int lst[kNbrWaves][kNbrList];
+    __shared__ __align__(16) int acc[FILL ? kNbrWaves : 1][FILL ? kNbrCap : 4];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int64_t s = xcd_block_upto(blockIdx.x, gridDim.x, 16384) * kNbrWaves + wave;
+    if (s >= n) return;  // whole waves; no barrier follows
+    const double xi = x[s], yi = y[s], zi = z[s];
+    const double di = PAIR ? d[s] : 0.0;
     const int nf = PER ? image_faces(pc, xi, yi, zi) : 0;
-    int i = perm[s];
-    int64_t wpos = FILL ? offsets[i] : 0;
+    const int i = perm[s];
+    const int64_t wpos = FILL ? offsets[i] : 0;
+    const bool ranked = FILL && offsets[i + 1] - wpos <= kNbrCap;
+    int *const mine = acc[FILL ? wave : 0];
     int cnt = 0;
     // image m = 0: i itself; m > 0: the periodic image of i across the faces of mask m
     for (int m = 0; m < (PER ? 8 : 1); ++m) {
         if ((nf & m) != m) continue;
         const double shx = image_shift(pc, nf, m, 0), shy = image_shift(pc, nf, m, 1),
                      shz = image_shift(pc, nf, m, 2);
-        const int cx = m & 1 ? free_cell(xi + shx, g.ox, g.inv) : cell_coord(xi, g.ox, g.inv, g.dx);
-        const int cy = m & 2 ? free_cell(yi + shy, g.oy, g.inv) : cell_coord(yi, g.oy, g.inv, g.dy);
-        const int cz = m & 4 ? free_cell(zi + shz, g.oz, g.inv) : cell_coord(zi, g.oz, g.inv, g.dz);
-        const int x0 = max(cx - R, 0), x1 = min(cx + R, g.dx - 1);
-        if (x0 > x1) continue;
-        for (int oz = -R; oz <= R; ++oz) {
-            int zz = cz + oz;
-            if (zz < 0 || zz >= g.dz) continue;
-            for (int oy = -R; oy <= R; ++oy) {
-                int yy = cy + oy;
-                if (yy < 0 || yy >= g.dy) continue;
-                int row = (int)cell_key(g, 0, yy, zz);
-                int j0 = cs[row + x0], j1 = cs[row + x1 + 1];
-                for (int j = j0; j < j1; ++j) {
-                    if (m == 0 && j == (int)s) continue;
-                    double dx = x[j] - xi, dy = y[j] - yi, dz = z[j] - zi;
-                    if (PER) {
-                        dx = dx - shx;
-                        dy = dy - shy;
-                        dz = dz - shz;
+        Stencil st = make_stencil(g, xi, yi, zi, pc.H);
+        if (PER) st = shifted_stencil(g, st, m, xi + shx, yi + shy, zi + shz);
+        // kNbrBatch candidates per lane (j < 0: none), their positions all asked for at once
+        auto test = [&](const int (&j)[kNbrBatch]) {
+            double dx[kNbrBatch], dy[kNbrBatch], dz[kNbrBatch], dd[kNbrBatch];
+            int id[kNbrBatch];
+#pragma unroll
+            for (int u = 0; u < kNbrBatch; ++u) {
+                const int k = j[u] >= 0 ? j[u] : 0;
+                dx[u] = x[k];
+                dy[u] = y[k];
+                dz[u] = z[k];
+                dd[u] = PAIR ? d[k] : 0.0;
+                id[u] = FILL ? perm[k] : 0;
+            }
+#pragma unroll
+            for (int u = 0; u < kNbrBatch; ++u) {
+                double ex = dx[u] - xi, ey = dy[u] - yi, ez = dz[u] - zi;
+                if (PER) {
+                    ex = ex - shx;
+                    ey = ey - shy;
+                    ez = ez - shz;
+                }
+                const double r2 = ((ex * ex) + (ey * ey)) + (ez * ez);
+                double H2 = pc.H2;
+                if (PAIR) {
+                    const double H = pc.kappa * (0.5 * (di + dd[u]));
+                    H2 = H * H;
+                }
+                const bool in = j[u] >= 0 && !(m == 0 && j[u] == (int)s) && r2 < H2;
+                const unsigned long long hit = __ballot(in);
+                if (FILL && in) {
+                    const int at = cnt + __popcll(hit & ((1ull << lane) - 1ull));
+                    if (ranked)
+                        mine[at] = id[u];
+                    else
+                        idx[wpos + at] = id[u];
+                }
+                cnt += __popcll(hit);
+            }
+        };
+        const int W = 2 * st.R + 1;
+        const float iw = 1.0f / (float)W;
+        for (int q0 = 0; q0 < W * W; q0 += 64) {
+            const int q = q0 + lane;
+            const int iz = (int)(((float)q + 0.5f) * iw);  // q / W (as walk_rows_split)
+            const int oz = iz - st.R, oy = q - iz * W - st.R;
+            const int yy = st.cy + oy, zz = st.cz + oz;
+            int j0, len;
+            if (!row_range(cs, g, st, plane_rem(g, st, q < W * W, oz, zz), oy, yy,
+                           cell_key(g, 0, yy, zz), j0, len))
+                continue;
+            int end = len;  // candidates of the rows up to the lane's
+            for (int o = 1; o < 64; o <<= 1) {
+                const int p = __shfl_up(end, o, 64);
+                if (lane >= o) end += p;
+            }
+            const int total = __shfl(end, 63, 64);
+            if (total <= kNbrList) {
+                wave_fence();
+                if (!__any(len > kNbrShort)) {
+                    for (int k = 0; __any(k < len); ++k)
+                        if (k < len) lst[wave][end - len + k] = j0 + k;
+                } else {
+                    for (unsigned long long rows = __ballot(len > 0); rows; rows &= rows - 1) {
+                        const int r = __builtin_ctzll(rows);
+                        const int a = __builtin_amdgcn_readlane(j0, r);
+                        const int c = __builtin_amdgcn_readlane(len, r);
+                        const int at = __builtin_amdgcn_readlane(end, r) - c;
+                        for (int t = lane; t < c; t += 64) lst[wave][at + t] = a + t;
                     }
-                    double r2 = ((dx * dx) + (dy * dy)) + (dz * dz);
-                    double H2;
-                    if (PAIR) {
-                        double H = pc.kappa * (0.5 * (di + d[j]));
-                        H2 = H * H;
-                    } else {
-                        H2 = pc.H2;
+                }
+                wave_fence();
+                for (int t = 0; t < total; t += 64 * kNbrBatch) {
+                    int j[kNbrBatch];
+#pragma unroll
+                    for (int u = 0; u < kNbrBatch; ++u) {
+                        const int at = t + 64 * u + lane;
+                        j[u] = at < total ? lst[wave][at] : -1;
                     }
-                    if (r2 < H2) {
-                        if (FILL) idx[wpos + cnt] = perm[j];
-                        ++cnt;
+                    test(j);
+                }
+            } else {
+                for (unsigned long long rows = __ballot(len > 0); rows; rows &= rows - 1) {
+                    const int r = __builtin_ctzll(rows);
+                    const int a = __builtin_amdgcn_readlane(j0, r);
+                    const int c = __builtin_amdgcn_readlane(len, r);
+                    for (int t = 0; t < c; t += 64 * kNbrBatch) {
+                        int j[kNbrBatch];
+#pragma unroll
+                        for (int u = 0; u < kNbrBatch; ++u) {
+                            const int at = t + 64 * u + lane;
+                            j[u] = at < c ? a + at : -1;
+                        }
+                        test(j);
                     }
                 }
             }
         }
     }
-    if (FILL) heap_sort(idx + wpos, cnt);  // the row ascending, O(c log c)
-    if (!FILL) count_orig[i] = cnt;
+    if (!FILL) {
+        if (lane == 0) count_orig[i] = cnt;
+        return;
+    }
+    if (ranked) {  // ascending: a neighbour's place is the number of smaller ones
+        wave_fence();
+        if (lane < 4 && cnt + lane < kNbrCap) mine[cnt + lane] = INT32_MAX;
+        wave_fence();
+        for (int t = lane; t < cnt; t += 64) {
+            const int v = mine[t];
+            int place = 0;
+            for (int k = 0; k < cnt; k += 4) {
+                const int4 w = *(const int4 *)(mine + k);
+                place += (w.x < v) + (w.y < v) + (w.z < v) + (w.w < v);
+            }
+            idx[wpos + place] = v;
+        }
+    } else {  // the wave's stores reach lane 0, which sorts the row, O(c log c)
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+        if (lane == 0) heap_sort(idx + wpos, cnt);
+    }
 }
 
 hipError_t launch_nbr_count(int64_t n, const GridDev &g, const PairConst &pc, const double *x,
                             const double *y, const double *z, const double *d, const int32_t *cs,
                             const int32_t *perm, int32_t *count_orig, hipStream_t st) {
     if (n <= 0) return hipSuccess;
-    unsigned nb = (unsigned)((n + kBlock - 1) / kBlock);
+    const unsigned nb = (unsigned)((n + kNbrWaves - 1) / kNbrWaves);
 #define CSPH_NBR(P, X)                                                                    \
     if (!!pc.pair_mode == P && !!pc.per == X)                                             \
         k_nbr<P, false, X><<<nb, kBlock, 0, st>>>(n, g, pc, x, y, z, d, cs, perm, count_orig, \
@@ -148,7 +249,7 @@ hipError_t launch_nbr_fill(int64_t n, const GridDev &g, const PairConst &pc, con
                            const int32_t *perm, const int64_t *offsets, int32_t *idx,
                            hipStream_t st) {
     if (n <= 0) return hipSuccess;
-    unsigned nb = (unsigned)((n + kBlock - 1) / kBlock);
+    const unsigned nb = (unsigned)((n + kNbrWaves - 1) / kNbrWaves);
 #define CSPH_NBR(P, X)                                                                    \
     if (!!pc.pair_mode == P && !!pc.per == X)                                             \
         k_nbr<P, true, X><<<nb, kBlock, 0, st>>>(n, g, pc, x, y, z, d, cs, perm, nullptr,    \

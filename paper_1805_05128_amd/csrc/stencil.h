@@ -190,6 +190,13 @@ __device__ __forceinline__ float cell_gap(float o, float f) {
     return fmaxf(fabsf(o - (f - 0.5f)) - 0.501f, 0.0f);
 }
 
+// Orders a wave's LDS accesses for the compiler (the hardware carries them out in order).
+__device__ __forceinline__ void wave_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Squared support left for a row of plane zz after the z gap (cell units); -1 when no row of
 // the plane counts (off the mesh, or a lane that does not walk).
 __device__ __forceinline__ float plane_rem(const GridDev &g, const Stencil &t, bool on, int oz,
@@ -217,9 +224,10 @@ __device__ __forceinline__ bool row_range(const int32_t *__restrict__ cs, const 
     const int xa = max(t.cx + (int)floorf(t.fx - hw), 0);
     const int xb = min(t.cx + (int)floorf(t.fx + hw), g.dx - 1);
     ok = ok && xb >= xa;
-    const int ia = ok ? (int)key + xa : 0, ib = ok ? (int)key + xb + 1 : 0;
-    j0 = ld(cs, ia);
-    len = ld(cs, ib) - j0;
+    // 64-bit addresses: a mesh may have 2e9 cells
+    const uint32_t ia = ok ? key + (uint32_t)xa : 0u, ib = ok ? key + (uint32_t)xb + 1u : 0u;
+    j0 = cs[ia];
+    len = cs[ib] - j0;
     return __any(len > 0);
 }
 
