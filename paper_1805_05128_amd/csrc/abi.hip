@@ -455,18 +455,19 @@ static csph_status bounds_polled(const double *x, const double *y, const double 
 }
 
 // A 64-bit device word to the host: through the thread's slot when it can be had (the word
-// as b[0]'s bits), else a copy and a synchronisation.
+// as b[0]'s bits), else a copy and a synchronisation; added to *sum (device) when given.
 static csph_status word_to_host(const unsigned long long *src, unsigned long long *out,
-                                hipStream_t st) {
+                                hipStream_t st, unsigned long long *sum = nullptr) {
     HostBounds *dslot = nullptr, *hb = host_slot(&dslot);
     if (hb) {
         const unsigned long long want = ++g_poll.seq;
-        CSPH_HIP(launch_word_host(src, dslot, want, st));
+        CSPH_HIP(launch_word_host(src, sum, dslot, want, st));
         csph_status r = poll_slot(hb, want, st, "device word");
         if (r) return r;
         *out = ((volatile const unsigned long long *)hb->b)[0];
         return CSPH_OK;
     }
+    if (sum) CSPH_HIP(launch_add_i64((int64_t *)sum, (const int64_t *)src, st));
     CSPH_HIP(hipMemcpyAsync(out, src, sizeof(*out), hipMemcpyDeviceToHost, st));
     CSPH_HIP(hipStreamSynchronize(st));
     return CSPH_OK;
@@ -600,12 +601,21 @@ static csph_status check_mesh(const csph_grid *m, double H) {
 }
 
 // The call's own non-physical count (counted into the workspace counter): added to the
-// caller's counter, brought to the host (synchronises), CSPH_ENONPHYS when not 0.
-static csph_status finish_nonphys(const Ws &w, int64_t *nonphys, hipStream_t st) {
-    if (nonphys) CSPH_HIP(launch_add_i64(nonphys, w.nonphys, st));
-    int64_t bad = 0;
-    CSPH_HIP(hipMemcpyAsync(&bad, w.nonphys, sizeof(bad), hipMemcpyDeviceToHost, st));
-    CSPH_HIP(hipStreamSynchronize(st));
+// caller's counter, brought to the host (the call's last kernel stores it, so the host's wait for
+// it is the call's closing synchronisation), CSPH_ENONPHYS when not 0.  poll = false: by a copy
+// and a synchronisation.
+static csph_status finish_nonphys(const Ws &w, int64_t *nonphys, hipStream_t st,
+                                  bool poll = true) {
+    unsigned long long bad = 0;
+    if (poll) {
+        csph_status r = word_to_host((unsigned long long *)w.nonphys, &bad, st,
+                                     (unsigned long long *)nonphys);
+        if (r) return r;
+    } else {
+        if (nonphys) CSPH_HIP(launch_add_i64(nonphys, w.nonphys, st));
+        CSPH_HIP(hipMemcpyAsync(&bad, w.nonphys, sizeof(bad), hipMemcpyDeviceToHost, st));
+        CSPH_HIP(hipStreamSynchronize(st));
+    }
     if (bad > 0) return fail(CSPH_ENONPHYS, "%lld particles in a non-physical state", (long long)bad);
     return CSPH_OK;
 }
@@ -815,10 +825,12 @@ csph_status csph_rates(const csph_state *s, const csph_params *p, double t, csph
     bool pair = p->h_mode == CSPH_H_PAIR;
     {
         ProfScope pr(CSPH_PROF_BIN, st);
-        CSPH_HIP(launch_bin(sv.x, sv.y, sv.z, n, gd, w, w.perm, nullptr, w.cs, st));
+        ClearWords cw;
+        cw.add(w.dtmin, 0x7ff0000000000000ull);
+        cw.add(w.zflag, 0x7ff0000000000000ull);
+        cw.add(w.nonphys, 0ull);
+        CSPH_HIP(launch_bin(sv.x, sv.y, sv.z, n, gd, w, w.perm, nullptr, w.cs, st, nullptr, &cw));
     }
-    CSPH_HIP(launch_fill_u64(w.dtmin, 0x7ff0000000000000ull, 2, st));  // dt min, Z flag
-    CSPH_HIP(launch_fill_u64((unsigned long long *)w.nonphys, 0ull, 1, st));
     {
         ProfScope pr(CSPH_PROF_PACK, st);
         CSPH_HIP(launch_pack(sv, n, w.perm, eos, mixed, gd, w, w.srt, w.srt_mat,
@@ -826,12 +838,8 @@ csph_status csph_rates(const csph_state *s, const csph_params *p, double t, csph
     }
     {
         ProfScope pr(CSPH_PROF_RATES, st);
-        CSPH_HIP(launch_rates(n, mixed, gd, pc, w, w.srt, pair ? w.srt_d : nullptr, nullptr, t,
-                              0, st));
-    }
-    {
-        ProfScope pr(CSPH_PROF_REORDER, st);
-        CSPH_HIP(launch_unsort_rates(n, w.perm, w, ov, signal, nbr_count, st));
+        CSPH_HIP(launch_rates_to(n, mixed, gd, pc, w, w.srt, pair ? w.srt_d : nullptr, t,
+                                 RatesTo{w.perm, ov, signal, nbr_count}, st));
     }
     return finish_nonphys(w, nonphys, st);
 }
@@ -988,17 +996,21 @@ static csph_status step_impl(const csph_state *s_in, csph_state *s_out, const cs
         dd = pair ? w.srt_d : nullptr;
         did = vin.id ? w.srt_id : nullptr;
     }
-    // dt = cfl * min h/s (an empty set takes dt = 0); the pack clears the Z flag
-    CSPH_HIP(launch_fill_u64(w.dtmin, n > 0 ? 0x7ff0000000000000ull : 0ull, 2, st));
-    // checked: the pack counts into the workspace, read back at the end
+    // dt = cfl * min h/s (an empty set takes dt = 0); the pack clears the Z flag; checked: the
+    // pack counts into the workspace, read back at the end
     const bool check = p->check_nonphys != 0;
-    if (check) CSPH_HIP(launch_fill_u64((unsigned long long *)w.nonphys, 0ull, 1, st));
+    ClearWords cw;
+    cw.add(w.dtmin, n > 0 ? 0x7ff0000000000000ull : 0ull);
+    cw.add(w.zflag, 0x7ff0000000000000ull);
+    if (check) cw.add(w.nonphys, 0ull);
+    if (chk.yenc) cw.add(chk.yenc, ~0ull);
+    if (n == 0)
+        for (int k = 0; k < cw.n; ++k) CSPH_HIP(launch_fill_u64(cw.p[k], cw.v[k], 1, st));
     if (n > 0) {
         {
             ProfScope pr(CSPH_PROF_BIN, st, prof);
-            if (chk.yenc) CSPH_HIP(launch_fill_u64(chk.yenc, ~0ull, 1, st));
             CSPH_HIP(launch_bin(vin.x, vin.y, vin.z, n, gd, w, w.perm, nullptr, w.cs, st,
-                                mesh ? &chk : nullptr));
+                                mesh ? &chk : nullptr, &cw));
         }
         ProfScope pr(CSPH_PROF_PACK, st, prof);
         CSPH_HIP(launch_pack(vin, n, w.perm, eos, mixed, gd, w, dst, dmat, dd, did, vin.id,
@@ -1039,13 +1051,14 @@ static csph_status step_impl(const csph_state *s_in, csph_state *s_out, const cs
                       w.stg[6], w.stg[7], dst[8],   dmat,     d1,       nullptr};
         {
             ProfScope pr(CSPH_PROF_BIN, st, prof);
-            if (chk2.yenc) CSPH_HIP(launch_fill_u64(chk2.yenc, ~0ull, 1, st));
+            ClearWords cw2;
+            cw2.add(w.zflag, 0x7ff0000000000000ull);
+            if (chk2.yenc) cw2.add(chk2.yenc, ~0ull);
             CSPH_HIP(launch_bin(u1.x, u1.y, u1.z, n, gd2, w2, w.perm2, nullptr, w.cs2, st,
-                                mesh ? &chk2 : nullptr));
+                                mesh ? &chk2 : nullptr, &cw2));
         }
         {
             ProfScope pr(CSPH_PROF_PACK, st, prof);
-            CSPH_HIP(launch_fill_u64(w.zflag, 0x7ff0000000000000ull, 1, st));
             CSPH_HIP(launch_pack(u1, n, w.perm2, eos, mixed, gd2, w2, w.srt2, nullptr,
                                  pair ? w.srt2_d : nullptr, nullptr, nullptr,
                                  check ? w.nonphys : nonphys, st));
@@ -1071,8 +1084,21 @@ static csph_status step_impl(const csph_state *s_in, csph_state *s_out, const cs
             vd.site_part = (unsigned long long *)va->site_particles;
             vd.site_pairs = (unsigned long long *)va->site_pairs;
         }
+        // the caller's order: the update writes there
+        KeptOut ko{};
+        if (!p->reorder) {
+            ko.perm = w.perm;
+            ko.out = vout;
+            ko.copy_m = vout.m != vin.m;
+            ko.mat = vin.mat && vout.mat != vin.mat ? w.srt_mat : nullptr;
+            ko.d = pair && vout.d != vin.d ? dd : nullptr;
+            ko.id = vin.id && vout.id != vin.id ? did : nullptr;
+            ko.cnt = w.cnt;
+            ko.nbr_count = nbr_count;
+        }
         // n = 0 writes zero partials
-        CSPH_HIP(launch_integrate(n, dst, w, p->cfl, dt_in, pc, t, st, va ? &vd : nullptr));
+        CSPH_HIP(launch_integrate(n, dst, w, p->cfl, dt_in, pc, t, st, va ? &vd : nullptr,
+                                  nullptr, p->reorder ? nullptr : &ko));
         CSPH_HIP(launch_finish_step(n, w, p->cfl, dt_in, t, dt_used, totals, ax.k, st));
     }
     ProfScope pro(CSPH_PROF_REORDER, st, prof);
@@ -1081,7 +1107,7 @@ static csph_status step_impl(const csph_state *s_in, csph_state *s_out, const cs
             if (nbr_count && cnt_out != nbr_count)
                 CSPH_HIP(hipMemcpyAsync(nbr_count, cnt_out, sizeof(int32_t) * n,
                                         hipMemcpyDeviceToDevice, st));
-        } else {
+        } else if (rk2) {
             csph_state o = vout;
             if (!pair) o.d = nullptr;
             CSPH_HIP(launch_unpermute(n, w.perm, w.srt, vin.mat ? w.srt_mat : nullptr, dd,
@@ -1089,7 +1115,7 @@ static csph_status step_impl(const csph_state *s_in, csph_state *s_out, const cs
         }
     }
     pro.stop();
-    return check ? finish_nonphys(w, nonphys, st) : CSPH_OK;
+    return check ? finish_nonphys(w, nonphys, st, prof) : CSPH_OK;
 }
 
 }  // namespace csph
@@ -1383,8 +1409,10 @@ static csph_status vjp_common(const csph_state *s_in, const csph_params *p, doub
     ProfScope pr(CSPH_PROF_ADJOINT, st);
     double *const dsrt = pair ? w.srt_d : nullptr;  // pair-h mode: the sizes in cell order
     // dt minimum and Z flag (the pack clears the flag where an impedance is zero)
-    CSPH_HIP(launch_fill_u64(w.dtmin, 0x7ff0000000000000ull, 2, st));
-    CSPH_HIP(launch_bin(s->x, s->y, s->z, n, gd, w, w.perm, nullptr, w.cs, st));
+    ClearWords cw;
+    cw.add(w.dtmin, 0x7ff0000000000000ull);
+    cw.add(w.zflag, 0x7ff0000000000000ull);
+    CSPH_HIP(launch_bin(s->x, s->y, s->z, n, gd, w, w.perm, nullptr, w.cs, st, nullptr, &cw));
     CSPH_HIP(launch_pack(*s, n, w.perm, eos, 0, gd, w, w.srt, w.srt_mat, dsrt, nullptr,
                          nullptr, nullptr, st));
     double *go[8] = {gout.x, gout.y, gout.z, gout.vx, gout.vy, gout.vz, gout.rho, gout.E};

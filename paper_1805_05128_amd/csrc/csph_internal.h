@@ -272,9 +272,21 @@ size_t ws_layout(Ws *w, void *base, int64_t n, int64_t ncell, bool rk2 = false,
 // k_bin.hip
 hipError_t launch_bounds(const double *x, const double *y, const double *z, const double *d,
                          int64_t n, double *part, double *out, hipStream_t st);
+// Words the binning's first kernel sets for the passes that follow (minima, flags, counters),
+// instead of a fill kernel each.
+struct ClearWords {
+    unsigned long long *p[4];
+    unsigned long long v[4];
+    int n = 0;
+    void add(void *at, unsigned long long value) {
+        p[n] = (unsigned long long *)at;
+        v[n++] = value;
+    }
+};
 hipError_t launch_bin(const double *x, const double *y, const double *z, int64_t n,
                       const GridDev &g, const Ws &w, int32_t *perm, uint32_t *key_out,
-                      int32_t *cell_start, hipStream_t st, const BinCheck *chk = nullptr);
+                      int32_t *cell_start, hipStream_t st, const BinCheck *chk = nullptr,
+                      const ClearWords *words = nullptr);
 template <typename TI, typename TO>
 hipError_t launch_scan_exclusive(const TI *in, TO *out, int64_t len, int64_t *tmp, hipStream_t st);
 
@@ -291,6 +303,16 @@ hipError_t launch_rates(int64_t n, int mixed, const GridDev &g, const PairConst 
                         const double *t_dev, double t_host, int want_dt, hipStream_t st,
                         const int32_t *vl_count = nullptr, const int32_t *vl_idx = nullptr,
                         int vl_cap = 0, const int32_t *gate = nullptr);
+// The same with the results at perm[s] of the caller's arrays (signal, nbr_count optional).
+struct RatesTo {
+    const int32_t *perm;
+    csph_rates_out out;
+    double *signal;
+    int32_t *nbr_count;
+};
+hipError_t launch_rates_to(int64_t n, int mixed, const GridDev &g, const PairConst &pc,
+                           const Ws &w, double *const sorted[9], const double *d_sorted,
+                           double t_host, const RatesTo &to, hipStream_t st);
 // Verlet-list control block: reset at a build; the per-step guard (csph_step_vlist).
 hipError_t launch_vl_init(csph_vlist_ctl *ctl, const double *t, double margin, double vw2,
                           hipStream_t st);
@@ -304,12 +326,22 @@ hipError_t launch_vlist(int64_t n, const void *recA, const int32_t *cs, const Gr
 hipError_t launch_disp(int64_t n, const double *x, const double *y, const double *z,
                        const double *ref, unsigned long long *out, hipStream_t st,
                        const int32_t *gate = nullptr);
-hipError_t launch_unsort_rates(int64_t n, const int32_t *perm, const Ws &w, csph_rates_out out,
-                               double *signal, int32_t *nbr_count, hipStream_t st);
 
 // k_step.hip
 hipError_t launch_fill_u64(unsigned long long *p, unsigned long long v, int64_t count, hipStream_t st);
 hipError_t launch_add_i64(int64_t *dst, const int64_t *src, hipStream_t st);  // *dst += *src
+// Where a step that keeps the caller's order puts its results: slot s at perm[s] of `out` (arrays
+// that `out` shares with the input need no copy: mass, materials, ids; in pair-h mode the sizes)
+struct KeptOut {
+    const int32_t *perm;
+    csph_state out;
+    int copy_m;
+    const int32_t *mat;   // cell order; null: nothing to copy
+    const double *d;
+    const int64_t *id;
+    const int32_t *cnt;
+    int32_t *nbr_count;
+};
 // Voronoi ownership computed by the step's update (csph_step_voronoi): K generators (K x 3,
 // the caller's axes; swap = the kernels see x and y exchanged), owner written at i (cell
 // order) or at owner_at[i], per-site particle and pair counts (cnt, cell order) overwritten.
@@ -341,7 +373,8 @@ hipError_t launch_rk2_combine(int64_t n, double *const st8[9], const Ws &w, doub
                               double dt_in, const PairConst &pc, const double *t, hipStream_t st);
 hipError_t launch_integrate(int64_t n, double *const st8[9], const Ws &w, double cfl, double dt_in,
                             const PairConst &pc, const double *t, hipStream_t st,
-                            const VoroDev *vo = nullptr, const ListGate *lg = nullptr);
+                            const VoroDev *vo = nullptr, const ListGate *lg = nullptr,
+                            const KeptOut *ko = nullptr);
 hipError_t launch_finish_step(int64_t n, const Ws &w, double cfl, double dt_in, double *t, double *dt_used,
                               double *totals, const int ax[3], hipStream_t st,
                               const ListGate *lg = nullptr);

@@ -19,8 +19,9 @@ hipError_t launch_bounds_host(const double *x, const double *y, const double *z,
                               const double *d, int64_t n, double *part, double *out,
                               HostBounds *hb, unsigned long long seq, hipStream_t st);
 
-// One 64-bit word to the slot (as b[0]'s bits), then `seq`, as launch_bounds_host does.
-hipError_t launch_word_host(const unsigned long long *src, HostBounds *hb,
-                            unsigned long long seq, hipStream_t st);
+// One 64-bit word to the slot (as b[0]'s bits), then `seq`, as launch_bounds_host does; added to
+// *sum too when given.
+hipError_t launch_word_host(const unsigned long long *src, unsigned long long *sum,
+                            HostBounds *hb, unsigned long long seq, hipStream_t st);
 
 }  // namespace csph

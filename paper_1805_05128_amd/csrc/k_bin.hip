@@ -13,6 +13,14 @@
 
 namespace csph {
 
+// Small sets (kSmallN particles at most; binning also fewer than kSmallKeys keys, and no more than
+// 64 particles to a key on average, since a particle's place in its cell takes a look at each of
+// the cell's others): one workgroup finds the bounds, and one bins, since at this size the chain
+// of launches, ~4 us each, takes longer than the work.
+constexpr int kSmallBlock = 1024;
+constexpr int kSmallPer = 16;  // particles and keys a thread
+constexpr int kSmallN = kSmallPer * kSmallBlock;
+
 // ---------------------------------------------------------------- reductions
 
 __device__ __forceinline__ double wave_min(double v) {
@@ -74,19 +82,13 @@ __global__ __launch_bounds__(kBlock) void k_bounds_final(const double *__restric
     }
 }
 
-// k_bounds_final, also writing the result to the host's pinned slot: each value with a
-// system-scope fence, then (after the workgroup barrier) the sequence number with a
-// system-scope release, which the host polls.
-__global__ __launch_bounds__(kBlock) void k_bounds_final_host(const double *__restrict__ part,
-                                                              int nblocks,
-                                                              double *__restrict__ out,
-                                                              HostBounds *hb,
-                                                              unsigned long long seq) {
-    double v[7] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY, 0.0};
-    for (int b = threadIdx.x; b < nblocks; b += kBlock)
-        for (int k = 0; k < 7; ++k)
-            v[k] = k < 3 ? fmin(v[k], part[b * 8 + k]) : fmax(v[k], part[b * 8 + k]);
-    __shared__ double sh[kBlock / 64][7];
+// The workgroup's minima and maxima of its threads' v (NW waves), also written to the host's
+// pinned slot: each value with a system-scope fence, then (after the workgroup barrier) the
+// sequence number with a system-scope release, which the host polls.
+template <int NW>
+__device__ __forceinline__ void bounds_to_host(const double (&v)[7], double *__restrict__ out,
+                                               HostBounds *hb, unsigned long long seq) {
+    __shared__ double sh[NW][7];
     int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     for (int k = 0; k < 7; ++k) {
         double r = k < 3 ? wave_min(v[k]) : wave_max(v[k]);
@@ -96,7 +98,7 @@ __global__ __launch_bounds__(kBlock) void k_bounds_final_host(const double *__re
     if (threadIdx.x < 7) {
         int k = threadIdx.x;
         double r = sh[0][k];
-        for (int q = 1; q < kBlock / 64; ++q) r = k < 3 ? fmin(r, sh[q][k]) : fmax(r, sh[q][k]);
+        for (int q = 1; q < NW; ++q) r = k < 3 ? fmin(r, sh[q][k]) : fmax(r, sh[q][k]);
         out[k] = r;
         hb->b[k] = r;
         __threadfence_system();
@@ -106,9 +108,54 @@ __global__ __launch_bounds__(kBlock) void k_bounds_final_host(const double *__re
         __hip_atomic_store(&hb->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+__global__ __launch_bounds__(kBlock) void k_bounds_final_host(const double *__restrict__ part,
+                                                              int nblocks,
+                                                              double *__restrict__ out,
+                                                              HostBounds *hb,
+                                                              unsigned long long seq) {
+    double v[7] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY, 0.0};
+    for (int b = threadIdx.x; b < nblocks; b += kBlock)
+        for (int k = 0; k < 7; ++k)
+            v[k] = k < 3 ? fmin(v[k], part[b * 8 + k]) : fmax(v[k], part[b * 8 + k]);
+    bounds_to_host<kBlock / 64>(v, out, hb, seq);
+}
+
+// A small set's bounds in one workgroup: one launch instead of two before the host's wait.
+__global__ __launch_bounds__(kSmallBlock) void k_bounds_small(const double *__restrict__ x,
+                                                              const double *__restrict__ y,
+                                                              const double *__restrict__ z,
+                                                              const double *__restrict__ d, int n,
+                                                              double *__restrict__ out,
+                                                              HostBounds *hb,
+                                                              unsigned long long seq) {
+    double v[7] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY, 0.0};
+    for (int i0 = threadIdx.x; i0 < n; i0 += 4 * kSmallBlock) {
+        double a[4], b[4], c[4], e[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {  // past the end: the thread's first particle again
+            const int i = i0 + q * kSmallBlock < n ? i0 + q * kSmallBlock : i0;
+            a[q] = x[i];
+            b[q] = y[i];
+            c[q] = z[i];
+            e[q] = d ? d[i] : 0.0;
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            v[0] = fmin(v[0], a[q]); v[1] = fmin(v[1], b[q]); v[2] = fmin(v[2], c[q]);
+            v[3] = fmax(v[3], a[q]); v[4] = fmax(v[4], b[q]); v[5] = fmax(v[5], c[q]);
+            v[6] = fmax(v[6], e[q]);
+        }
+    }
+    bounds_to_host<kSmallBlock / 64>(v, out, hb, seq);
+}
+
 hipError_t launch_bounds_host(const double *x, const double *y, const double *z,
                               const double *d, int64_t n, double *part, double *out,
                               HostBounds *hb, unsigned long long seq, hipStream_t st) {
+    if (n <= kSmallN) {
+        k_bounds_small<<<1, kSmallBlock, 0, st>>>(x, y, z, d, (int)n, out, hb, seq);
+        return hipGetLastError();
+    }
     int64_t want = (n + kBlock - 1) / kBlock;
     int nb = (int)(want < 1 ? 1 : (want > kReduceBlocks ? kReduceBlocks : want));
     k_bounds<<<nb, kBlock, 0, st>>>(x, y, z, d, n, part);
@@ -116,16 +163,18 @@ hipError_t launch_bounds_host(const double *x, const double *y, const double *z,
     return hipGetLastError();
 }
 
-__global__ void k_word_host(const unsigned long long *__restrict__ src, HostBounds *hb,
-                            unsigned long long seq) {
+__global__ void k_word_host(const unsigned long long *__restrict__ src, unsigned long long *sum,
+                            HostBounds *hb, unsigned long long seq) {
     if (threadIdx.x != 0) return;
-    ((unsigned long long *)hb->b)[0] = *src;
+    const unsigned long long v = *src;
+    if (sum) *sum += v;
+    ((unsigned long long *)hb->b)[0] = v;
     __hip_atomic_store(&hb->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-hipError_t launch_word_host(const unsigned long long *src, HostBounds *hb,
-                            unsigned long long seq, hipStream_t st) {
-    k_word_host<<<1, 64, 0, st>>>(src, hb, seq);
+hipError_t launch_word_host(const unsigned long long *src, unsigned long long *sum,
+                            HostBounds *hb, unsigned long long seq, hipStream_t st) {
+    k_word_host<<<1, 64, 0, st>>>(src, sum, hb, seq);
     return hipGetLastError();
 }
 
@@ -208,12 +257,15 @@ __global__ __launch_bounds__(kBlock) void k_scan_tops(int64_t *__restrict__ tile
     if (threadIdx.x == 0) out[len] = (TO)total;
 }
 
-// vec: in and out are 16-byte aligned 32-bit arrays; a thread's kScanItems = 8 values then move
+constexpr int64_t kOwnTiles = 1024;
+
+// sums: every workgroup adds up the sums of the tiles before its own (up to kOwnTiles of
+// them), which leaves out the launch that scans them.  vec: in and out are 16-byte aligned 32-bit arrays; a thread's kScanItems = 8 values then move
 // as two 16-byte loads and stores (the tail tile goes element by element).
 template <typename TI, typename TO>
 __global__ __launch_bounds__(kBlock) void k_scan_apply(const TI *in, TO *out, int64_t len,
                                                        const int64_t *__restrict__ tile_off,
-                                                       int vec) {
+                                                       int vec, int sums) {
     static_assert(kScanItems == 8, "two 16-byte vectors per thread");
     int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
     const bool wide = sizeof(TI) == 4 && sizeof(TO) == 4 && vec && base + kScanItems <= len;
@@ -232,7 +284,16 @@ __global__ __launch_bounds__(kBlock) void k_scan_apply(const TI *in, TO *out, in
     for (int k = 0; k < kScanItems; ++k) s += v[k];
     __shared__ int64_t lds[kBlock / 64 + 1];
     int64_t total;
-    int64_t run = block_exclusive_scan<int64_t>(s, lds, total) + tile_off[blockIdx.x];
+    int64_t run = block_exclusive_scan<int64_t>(s, lds, total);
+    if (sums) {  // tile_off holds the tiles' sums: add up those before this tile
+        int64_t before = 0, all;
+        for (int k = threadIdx.x; k < (int)blockIdx.x; k += kBlock) before += tile_off[k];
+        block_exclusive_scan<int64_t>(before, lds, all);
+        run += all;
+        if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) out[len] = (TO)(all + total);
+    } else {
+        run += tile_off[blockIdx.x];
+    }
     if (wide) {
         int o[kScanItems];
         for (int k = 0; k < kScanItems; ++k) {
@@ -258,9 +319,10 @@ hipError_t launch_scan_exclusive(const TI *in, TO *out, int64_t len, int64_t *tm
     int64_t ntiles = (len + kScanTile - 1) / kScanTile;
     const int vec = ((uintptr_t)in % 16 == 0) && ((uintptr_t)out % 16 == 0);
     if (ntiles > 0) k_scan_reduce<TI><<<(unsigned)ntiles, kBlock, 0, st>>>(in, len, tmp, vec);
-    k_scan_tops<TO><<<1, kBlock, 0, st>>>(tmp, ntiles, out, len);
+    const int own = ntiles > 0 && ntiles <= kOwnTiles;
+    if (!own) k_scan_tops<TO><<<1, kBlock, 0, st>>>(tmp, ntiles, out, len);
     if (ntiles > 0)
-        k_scan_apply<TI, TO><<<(unsigned)ntiles, kBlock, 0, st>>>(in, out, len, tmp, vec);
+        k_scan_apply<TI, TO><<<(unsigned)ntiles, kBlock, 0, st>>>(in, out, len, tmp, vec, own);
     return hipGetLastError();
 }
 
@@ -275,6 +337,14 @@ __global__ __launch_bounds__(kBlock) void k_fill_i32(int32_t *p, int32_t v, int6
     for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < count;
          i += (int64_t)gridDim.x * kBlock)
         p[i] = v;
+}
+
+// The histogram cleared, and the caller's words set.
+__global__ __launch_bounds__(kBlock) void k_clear(int32_t *p, int64_t count, ClearWords w) {
+    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < count;
+         i += (int64_t)gridDim.x * kBlock)
+        p[i] = 0;
+    if (blockIdx.x == 0 && (int)threadIdx.x < w.n) *w.p[threadIdx.x] = w.v[threadIdx.x];
 }
 
 // Whether coordinate v lies on the mesh axis (origin o, 1/D inv, dim cells), in the cell
@@ -353,15 +423,111 @@ __global__ __launch_bounds__(kBlock) void k_cell_rank(const uint32_t *__restrict
     perm[a + r] = p;
 }
 
+// The whole binning of a small set in one workgroup: the histogram (16-bit counts, two to a
+// word, whose atomics also rank the particles in their cells), its scan, the cell segments and
+// the places in them, all in LDS.  Seven launches became one; a 13 824-particle binning took
+// ~17 us of kernels in ~30 us of launches.
+constexpr int kSmallKeys = 16 * 1024;
+__global__ __launch_bounds__(kSmallBlock) void k_bin_small(
+    const double *__restrict__ x, const double *__restrict__ y, const double *__restrict__ z,
+    int n, GridDev g, int nkey, int32_t *__restrict__ perm, uint32_t *__restrict__ key_out,
+    int32_t *__restrict__ cs, ClearWords w) {
+    __shared__ uint32_t hist[kSmallKeys / 2];  // counts, then cell starts, as 16-bit halves
+    __shared__ uint16_t seg[kSmallN];          // particles by cell, in atomic order
+    __shared__ int lds[kSmallBlock / 64 + 1];
+    uint16_t *const start = (uint16_t *)hist;
+    const int tid = threadIdx.x;
+    for (int k = tid; k < kSmallKeys / 2; k += kSmallBlock) hist[k] = 0u;
+    if (tid < w.n) *w.p[tid] = w.v[tid];
+    __syncthreads();
+    uint32_t key[kSmallPer];
+    int rank[kSmallPer];
+#pragma unroll
+    for (int q0 = 0; q0 < kSmallPer; q0 += 8) {  // eight particles' positions in flight
+        if (q0 * kSmallBlock >= n) break;
+        double px[8], py[8], pz[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int i = (q0 + q) * kSmallBlock + tid, j = i < n ? i : 0;
+            px[q] = x[j];
+            py[q] = y[j];
+            pz[q] = z[j];
+        }
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int i = (q0 + q) * kSmallBlock + tid;
+            const int cx = cell_coord(px[q], g.ox, g.inv, g.dx);
+            const int cy = cell_coord(py[q], g.oy, g.inv, g.dy);
+            const int cz = cell_coord(pz[q], g.oz, g.inv, g.dz);
+            const uint32_t k = g.morton ? morton_key(cx, cy, cz) : cell_key(g, cx, cy, cz);
+            key[q0 + q] = k;
+            if (i < n) {
+                if (key_out) key_out[i] = k;
+                const int sh = (k & 1u) ? 16 : 0;
+                rank[q0 + q] = (int)((atomicAdd(&hist[k >> 1], 1u << sh) >> sh) & 0xffffu);
+            }
+        }
+    }
+    __syncthreads();
+    // exclusive scan: each thread's run of 16 keys, then the workgroup's
+    const int k0 = tid * (kSmallKeys / kSmallBlock);
+    int c[kSmallKeys / kSmallBlock], sum = 0;
+#pragma unroll
+    for (int k = 0; k < kSmallKeys / kSmallBlock; ++k) {
+        c[k] = start[k0 + k];
+        sum += c[k];
+    }
+    int inc = sum;
+    for (int o = 1; o < 64; o <<= 1) {
+        const int v = __shfl_up(inc, o, 64);
+        if ((tid & 63) >= o) inc += v;
+    }
+    if ((tid & 63) == 63) lds[tid >> 6] = inc;
+    __syncthreads();
+    int run = inc - sum;
+    for (int q = 0; q < (tid >> 6); ++q) run += lds[q];
+#pragma unroll
+    for (int k = 0; k < kSmallKeys / kSmallBlock; ++k) {
+        start[k0 + k] = (uint16_t)run;  // the thread's own keys only; n <= 16 384
+        if (k0 + k <= nkey) cs[k0 + k] = run;
+        run += c[k];
+    }
+    if (tid == 0) cs[nkey] = n;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kSmallPer; ++q) {
+        const int i = q * kSmallBlock + tid;
+        if (i >= n) break;
+        seg[start[key[q]] + rank[q]] = (uint16_t)i;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kSmallPer; ++q) {
+        const int i = q * kSmallBlock + tid;
+        if (i >= n) break;
+        const int a = start[key[q]], b = (int)key[q] + 1 < kSmallKeys ? start[key[q] + 1] : n;
+        int r = 0;
+        for (int t = a; t < b; ++t) r += (int)seg[t] < i ? 1 : 0;
+        perm[a + r] = i;
+    }
+}
+
 static unsigned blocks_for(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
 
 hipError_t launch_bin(const double *x, const double *y, const double *z, int64_t n,
                       const GridDev &g, const Ws &w, int32_t *perm, uint32_t *key_out,
-                      int32_t *cell_start, hipStream_t st, const BinCheck *chk) {
+                      int32_t *cell_start, hipStream_t st, const BinCheck *chk,
+                      const ClearWords *words) {
     const BinCheck c = chk ? *chk : BinCheck{nullptr, nullptr, 0, {0, 0, 0}, {0, 0, 0}};
+    const ClearWords cw = words ? *words : ClearWords{};
     const int64_t ncell = g.nkey;  // keys (cells, or the Morton key space)
+    if (n > 0 && n <= kSmallN && ncell < kSmallKeys && n <= 64 * ncell && !chk) {
+        k_bin_small<<<1, kSmallBlock, 0, st>>>(x, y, z, (int)n, g, (int)ncell, perm, key_out,
+                                               cell_start, cw);
+        return hipGetLastError();
+    }
     unsigned fb = blocks_for(ncell + 1);
-    k_fill_i32<<<fb > 65535u ? 65535u : fb, kBlock, 0, st>>>(cell_start, 0, ncell + 1);
+    k_clear<<<fb > 65535u ? 65535u : fb, kBlock, 0, st>>>(cell_start, ncell + 1, cw);
     if (n > 0)
         k_keys<<<blocks_for(n), kBlock, 0, st>>>(x, y, z, n, g, w.key, w.rank, cell_start,
                                                  key_out, c);

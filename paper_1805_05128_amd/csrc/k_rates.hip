@@ -179,6 +179,7 @@ struct RateOut {
     int32_t *cnt;
     unsigned long long *dtmin;
     const unsigned long long *zflag;  // 0: some impedance is zero (see k_pack)
+    const int32_t *perm;              // the results go to perm[s] (null: to s)
 };
 
 // ---------------------------------------------------------------- FP64 rates
@@ -557,17 +558,18 @@ __global__ __launch_bounds__(kRate64Block, 4) void k_rates64(int64_t n, Split4 A
     double dtv = INFINITY;
     if (k.live && (!SPLIT || k.sub == 0)) {
         double ri = rho[s];
+        const int64_t to = o.perm ? (int64_t)o.perm[s] : s;
         double pre = 2.0 / ri;
         double drho = -2.0 * ri * k.ar;
-        o.rho[s] = drho;
-        o.vx[s] = pre * k.avx;
-        o.vy[s] = pre * k.avy;
-        o.vz[s] = pre * k.avz;
+        o.rho[to] = drho;
+        o.vx[to] = pre * k.avx;
+        o.vy[to] = pre * k.avy;
+        o.vz[to] = pre * k.avz;
         // sum_j f v* = v_i . sum_j f e_ij - sum_j f (v_L - v*)
         const double vf = (k.b.x * k.avx + k.b.y * k.avy) + k.b.z * k.avz;
-        o.E[s] = pre * (k.aE + vf);
-        if (o.sig) o.sig[s] = k.sig;
-        if (o.cnt) o.cnt[s] = cnt;
+        o.E[to] = pre * (k.aE + vf);
+        if (o.sig) o.sig[to] = k.sig;
+        if (o.cnt) o.cnt[to] = cnt;
         // Courant limit and relative density-change limit of one explicit step
         dtv = fmin((PAIR ? k.di : pc.h_dt) / k.sig, ri / fabs(drho));
     }
@@ -976,36 +978,33 @@ __global__ __launch_bounds__(kRate32Block, 4) void k_rates32(int64_t n, const fl
     double dtv = INFINITY;
     if (k.live) {
         double ri = rho[s];
+        const int64_t to = o.perm ? (int64_t)o.perm[s] : s;
         double pre = 2.0 / ri;
         double drho = -2.0 * ri * (double)k.ar;
-        o.rho[s] = drho;
-        o.vx[s] = pre * (double)k.avx;
-        o.vy[s] = pre * (double)k.avy;
-        o.vz[s] = pre * (double)k.avz;
+        o.rho[to] = drho;
+        o.vx[to] = pre * (double)k.avx;
+        o.vy[to] = pre * (double)k.avy;
+        o.vz[to] = pre * (double)k.avz;
         const double vf = ((double)k.b.x * (double)k.avx + (double)k.b.y * (double)k.avy) +
                           (double)k.b.z * (double)k.avz;
-        o.E[s] = pre * ((double)k.aE + vf);
-        if (o.sig) o.sig[s] = (double)k.sig;
-        if (o.cnt) o.cnt[s] = k.count();
+        o.E[to] = pre * ((double)k.aE + vf);
+        if (o.sig) o.sig[to] = (double)k.sig;
+        if (o.cnt) o.cnt[to] = k.count();
         dtv = fmin((PAIR ? k.di : pc.h_dt) / (double)k.sig, ri / fabs(drho));
     }
     if (want_dt) wave_min_to(dtv, o.dtmin);
 }
 
-hipError_t launch_rates(int64_t n, int mixed, const GridDev &g, const PairConst &pc,
-                        const Ws &w, double *const sorted[9], const double *d_sorted,
-                        const double *t_dev, double t_host, int want_dt, hipStream_t st,
-                        const int32_t *vl_count, const int32_t *vl_idx, int vl_cap,
-                        const int32_t *gate) {
+static hipError_t rates_out(int64_t n, int mixed, const GridDev &g, const PairConst &pc,
+                            const Ws &w, double *const sorted[9], const double *d_sorted,
+                            const double *t_dev, double t_host, int want_dt, const RateOut &o,
+                            const VList &vl, hipStream_t st) {
     if (n <= 0) return hipSuccess;
     const double *rho_sorted = sorted[6];
-    RateOut o{w.rate[0], w.rate[1], w.rate[2], w.rate[3], w.rate[4], w.sig, w.cnt, w.dtmin,
-              w.zflag};
-    VList vl{vl_count, vl_idx, vl_cap, gate};
     const unsigned nb32 = (unsigned)((n + kRate32Block - 1) / kRate32Block);
-    const int ls = vl_idx ? 0 : split_log2(n);
+    const int ls = vl.idx ? 0 : split_log2(n);
     const unsigned nb64 = (unsigned)(((n << ls) + kRate64Block - 1) / kRate64Block);
-    const bool pair = pc.pair_mode != 0, wall = pc.wall != 0, list = vl_idx != nullptr;
+    const bool pair = pc.pair_mode != 0, wall = pc.wall != 0, list = vl.idx != nullptr;
     const bool per = pc.per != 0;
     if (list && (pair || per)) return hipErrorInvalidValue;
 #define CSPH_RATES64_ARGS                                                                     \
@@ -1039,33 +1038,26 @@ hipError_t launch_rates(int64_t n, int mixed, const GridDev &g, const PairConst 
     return hipGetLastError();
 }
 
-// ---------------------------------------------------------------- back to input order
-
-__global__ __launch_bounds__(kBlock) void k_unsort_rates(int64_t n,
-                                                         const int32_t *__restrict__ perm,
-                                                         RateOut src, csph_rates_out out,
-                                                         double *__restrict__ signal,
-                                                         int32_t *__restrict__ nbr_count) {
-    int64_t s = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (s >= n) return;
-    int i = perm[s];
-    out.drho[i] = src.rho[s];
-    out.dvx[i] = src.vx[s];
-    out.dvy[i] = src.vy[s];
-    out.dvz[i] = src.vz[s];
-    out.dE[i] = src.E[s];
-    if (signal) signal[i] = src.sig[s];
-    if (nbr_count) nbr_count[i] = src.cnt[s];
+hipError_t launch_rates(int64_t n, int mixed, const GridDev &g, const PairConst &pc,
+                        const Ws &w, double *const sorted[9], const double *d_sorted,
+                        const double *t_dev, double t_host, int want_dt, hipStream_t st,
+                        const int32_t *vl_count, const int32_t *vl_idx, int vl_cap,
+                        const int32_t *gate) {
+    const RateOut o{w.rate[0], w.rate[1], w.rate[2], w.rate[3], w.rate[4],
+                    w.sig,     w.cnt,     w.dtmin,   w.zflag,   nullptr};
+    return rates_out(n, mixed, g, pc, w, sorted, d_sorted, t_dev, t_host, want_dt, o,
+                     VList{vl_count, vl_idx, vl_cap, gate}, st);
 }
 
-hipError_t launch_unsort_rates(int64_t n, const int32_t *perm, const Ws &w, csph_rates_out out,
-                               double *signal, int32_t *nbr_count, hipStream_t st) {
-    if (n <= 0) return hipSuccess;
-    RateOut src{w.rate[0], w.rate[1], w.rate[2], w.rate[3], w.rate[4], w.sig, w.cnt, w.dtmin,
-                w.zflag};
-    k_unsort_rates<<<(unsigned)((n + kBlock - 1) / kBlock), kBlock, 0, st>>>(n, perm, src, out,
-                                                                             signal, nbr_count);
-    return hipGetLastError();
+// The rates in the caller's order: every particle's results stored at its place there, which a
+// separate pass over 52 bytes a particle did before.
+hipError_t launch_rates_to(int64_t n, int mixed, const GridDev &g, const PairConst &pc,
+                           const Ws &w, double *const sorted[9], const double *d_sorted,
+                           double t_host, const RatesTo &to, hipStream_t st) {
+    const RateOut o{to.out.drho, to.out.dvx,   to.out.dvy, to.out.dvz, to.out.dE,
+                    to.signal,   to.nbr_count, w.dtmin,    w.zflag,    to.perm};
+    return rates_out(n, mixed, g, pc, w, sorted, d_sorted, nullptr, t_host, 0, o,
+                     VList{nullptr, nullptr, 0, nullptr}, st);
 }
 
 }  // namespace csph

@@ -131,6 +131,19 @@ __device__ __forceinline__ void reflect(const WallDev &wall, double yw, double &
     }
 }
 
+// A step that keeps the caller's order (ko.perm): the new state goes from the cell-ordered copy
+// straight to the particles' places in the caller's arrays (fields the two share stay as they
+// are), instead of back into the copy and from there by another pass.
+struct KeptDev {
+    const int32_t *perm;
+    double *f[9], *d_to;
+    int32_t *mat_to, *cnt_to;
+    int64_t *id_to;
+    const int32_t *mat, *cnt;
+    const double *d;
+    const int64_t *id;
+};
+
 // With VORO the kernel also assigns each particle's new position to its Voronoi generator
 // (eq. VoronoiDefinition: FP64 argmin of ((dx dx) + (dy dy)) + (dz dz) without contraction,
 // k scanned upwards with a strict comparison, so a tie keeps the smaller k) and counts
@@ -141,7 +154,7 @@ __device__ __forceinline__ void reflect(const WallDev &wall, double yw, double &
 __global__ __launch_bounds__(kBlock) void k_integrate(int64_t n, State9 s, Rates5 r,
                                                       const unsigned long long *dtmin, double cfl,
                                                       double dt_in, WallDev wall, PerDev per,
-                                                      VoroDev vo, ListGate lg,
+                                                      VoroDev vo, ListGate lg, KeptDev ko,
                                                       double *__restrict__ part) {
     if (lg.gate && *lg.gate == 0) return;
     extern __shared__ double vsm[];
@@ -179,9 +192,11 @@ __global__ __launch_bounds__(kBlock) void k_integrate(int64_t n, State9 s, Rates
             y = wrap_axis(per, 1, y);
             z = wrap_axis(per, 2, z);
         }
-        s.f[0][i] = x;
-        s.f[1][i] = y;
-        s.f[2][i] = z;
+        const int64_t to = ko.perm ? (int64_t)ko.perm[i] : i;
+        double *const *const out = ko.perm ? ko.f : s.f;
+        out[0][to] = x;
+        out[1][to] = y;
+        out[2][to] = z;
         if (vo.K > 0) {
             int best = 0;
             double bd = INFINITY;
@@ -197,12 +212,19 @@ __global__ __launch_bounds__(kBlock) void k_integrate(int64_t n, State9 s, Rates
             atomicAdd(&hp[best], 1u);
             atomicAdd(&hq[best], (unsigned long long)vo.cnt[i]);
         }
-        s.f[3][i] = vx;
-        s.f[4][i] = vy;
-        s.f[5][i] = vz;
-        s.f[6][i] = rho;
-        s.f[7][i] = E;
+        out[3][to] = vx;
+        out[4][to] = vy;
+        out[5][to] = vz;
+        out[6][to] = rho;
+        out[7][to] = E;
         double m = s.f[8][i];
+        if (ko.perm) {
+            if (ko.f[8]) ko.f[8][to] = m;
+            if (ko.mat_to) ko.mat_to[to] = ko.mat[i];
+            if (ko.d_to) ko.d_to[to] = ko.d[i];
+            if (ko.id_to) ko.id_to[to] = ko.id[i];
+            if (ko.cnt_to) ko.cnt_to[to] = ko.cnt[i];
+        }
         acc[0] = dd_add1(acc[0], m);
         acc[1] = dd_add1(acc[1], m * vx);
         acc[2] = dd_add1(acc[2], m * vy);
@@ -326,7 +348,7 @@ static int integrate_blocks(int64_t n) {
 
 hipError_t launch_integrate(int64_t n, double *const st8[9], const Ws &w, double cfl, double dt_in,
                             const PairConst &pc, const double *t, hipStream_t st,
-                            const VoroDev *vo, const ListGate *lg) {
+                            const VoroDev *vo, const ListGate *lg, const KeptOut *ko) {
     State9 s;
     for (int k = 0; k < 9; ++k) s.f[k] = st8[k];
     Rates5 r{{w.rate[0], w.rate[1], w.rate[2], w.rate[3], w.rate[4]}};
@@ -341,8 +363,23 @@ hipError_t launch_integrate(int64_t n, double *const st8[9], const Ws &w, double
         shm = (size_t)v.K * (3 * sizeof(double) + sizeof(unsigned long long) + sizeof(unsigned));
     }
     const ListGate g = lg ? *lg : ListGate{nullptr, nullptr, nullptr, nullptr};
+    KeptDev k{};
+    if (ko) {
+        const csph_state &o = ko->out;
+        double *const f[9] = {o.x, o.y, o.z, o.vx, o.vy, o.vz, o.rho, o.E, ko->copy_m ? o.m : nullptr};
+        k.perm = ko->perm;
+        for (int q = 0; q < 9; ++q) k.f[q] = f[q];
+        k.mat = ko->mat;
+        k.mat_to = ko->mat ? o.mat : nullptr;
+        k.d = ko->d;
+        k.d_to = ko->d ? o.d : nullptr;
+        k.id = ko->id;
+        k.id_to = ko->id ? o.id : nullptr;
+        k.cnt = ko->cnt;
+        k.cnt_to = ko->nbr_count;
+    }
     int nb = integrate_blocks(n);
-    k_integrate<<<nb, kBlock, shm, st>>>(n, s, r, w.dtmin, cfl, dt_in, wall, per, v, g,
+    k_integrate<<<nb, kBlock, shm, st>>>(n, s, r, w.dtmin, cfl, dt_in, wall, per, v, g, k,
                                          w.tot_part);
     return hipGetLastError();
 }

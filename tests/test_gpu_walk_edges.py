@@ -107,3 +107,52 @@ def test_step_vjp_lanes_per_particle(k, cell, wall, periodic):
         # reaches the gradients through offsets of order one
         assert np.abs(got[f] - one[f]).max() <= 2e-9 * scale, f
     assert np.allclose(gek, ge1, rtol=1e-8, atol=1e-9 * np.abs(ge1).max())
+
+
+@pytest.mark.parametrize("key_mode", ["linear", "morton"])
+@pytest.mark.parametrize("n,box,cell", [(1, 1.0, 0.5), (1023, 5.0, 0.7), (1025, 9.0, 1.0),
+                                        (8192, 24.0, 1.0), (16384, 20.0, 0.85),
+                                        (16384, 25.0, 1.0), (16385, 20.0, 1.0),
+                                        (5000, 1.9, 1.0), (300, 24.9, 1.0)])
+def test_bin_sizes(n, box, cell, key_mode):
+    """Binning at the limits of its one-workgroup form (16 384 particles, fewer than 16 384 keys,
+    64 particles a key) equals the stable sort by key."""
+    w = ci.random_cloud(n, seed=n, box=box)
+    params = P.Params.from_workload(w, cell_size=cell, key_mode=key_mode)
+    x, y, z = (torch.as_tensor(a, device=DEV) for a in (w.x, w.y, w.z))
+    g = P.csph_grid_build(x, y, z, params)
+    key, perm, start = P.csph_bin(x, y, z, g)
+    key, perm, start = to_np(key), to_np(perm), to_np(start)
+    c = [np.clip(np.floor((a - g.origin[k]) * g.inv_cell), 0, g.dims[k] - 1).astype(np.int64)
+         for k, a in enumerate((w.x, w.y, w.z))]
+    if key_mode == "linear":
+        ref = (c[2] * g.dims[1] + c[1]) * g.dims[0] + c[0]
+    else:
+        ref = sum(((c[a] >> b) & 1) << (3 * b + a) for a in range(3) for b in range(10))
+    assert np.array_equal(key, ref)
+    assert np.array_equal(perm, np.argsort(ref, kind="stable"))
+    assert np.array_equal(start, np.searchsorted(np.sort(ref), np.arange(g.nkey + 1)))
+
+
+@pytest.mark.parametrize("in_place", [True, False])
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_step_kept_order_equals_renumbered(precision, in_place):
+    """A step that keeps the caller's order writes what the renumbering step writes, bit for bit,
+    at the particles' places, with materials, ids and counts; other arrays stay whole."""
+    w = ci.random_cloud(3000, seed=9, box=14.0, n_mat=2)
+    w.wall = (0.0, 0.2)
+    over = dict(precision=precision, cell_size=1.0)
+    pr = P.Params.from_workload(w, **over)
+    pk = P.Params.from_workload(w, reorder=False, **over)
+    st = P.state_from_workload(w, pr, DEV)
+    counts = [torch.empty(w.n, dtype=torch.int32, device=DEV) for _ in range(2)]
+    scal = [P.StepScalars(DEV, t0=0.1) for _ in range(2)]
+    a = P.csph_step(st, pr, scal[0], nbr_count=counts[0])
+    kept = st if in_place else st.like()
+    b = P.csph_step(st, pk, scal[1], s_out=kept, nbr_count=counts[1])
+    order = a["id"]
+    assert torch.equal(torch.sort(order).values, torch.arange(w.n, device=DEV))
+    for f in P.GRAD_FIELDS + ("m", "mat", "id"):
+        assert torch.equal(a[f], b[f][order]), f
+    assert torch.equal(counts[0], counts[1][order])
+    assert torch.equal(scal[0].dt, scal[1].dt) and torch.equal(scal[0].totals, scal[1].totals)
