@@ -102,6 +102,8 @@ def load():
                           "`python -m paper_1805_05128_amd.build` (no CPU fallback exists)")
     L = C.CDLL(LIB_PATH)
     vp = C.c_void_p
+    # arrays go by address: integers (a tensor's data_ptr) and ctypes pointers alike
+    _dp = _ip = _lp = _up = vp
     sz = C.c_size_t
     szp = C.POINTER(C.c_size_t)
     L.csph_status_string.restype = C.c_char_p

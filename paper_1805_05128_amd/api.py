@@ -7,6 +7,7 @@ kernels behind ``include/csph.h``.
 from __future__ import annotations
 
 import ctypes as C
+import struct
 from dataclasses import dataclass, field
 from typing import Dict, List, Optional, Sequence, Tuple
 
@@ -19,28 +20,38 @@ EOS_IDEAL, EOS_STIFFENED = N.CSPH_EOS_IDEAL, N.CSPH_EOS_STIFFENED
 EOS_MIE_GRUNEISEN = N.CSPH_EOS_MIE_GRUNEISEN
 
 
-def _ptr(t: Optional[torch.Tensor], ctype):
-    if t is None:
-        return None
-    return C.cast(C.c_void_p(t.data_ptr()), C.POINTER(ctype))
+# Array arguments are passed by address.  The structs of pointers are packed in one call: a
+# ctypes cast and assignment per array took ~1.5 us each, 40-60 us a step, which at a few
+# thousand particles is as long as the step's kernels.
+_F64, _I32, _I64 = torch.float64, torch.int32, torch.int64
+_PACK_STATE = struct.Struct("=q12Q")
+_PACK5, _PACK8 = struct.Struct("=5Q"), struct.Struct("=8Q")
 
 
 def _dp(t):
-    if t is not None:
-        assert t.dtype == torch.float64 and t.is_contiguous() and t.is_cuda, (t.dtype, t.device)
-    return _ptr(t, C.c_double)
+    if t is None:
+        return None
+    assert t.dtype is _F64 and t.is_contiguous() and t.is_cuda, (t.dtype, t.device)
+    return t.data_ptr()
 
 
 def _ip(t):
-    if t is not None:
-        assert t.dtype == torch.int32 and t.is_contiguous() and t.is_cuda
-    return _ptr(t, C.c_int32)
+    if t is None:
+        return None
+    assert t.dtype is _I32 and t.is_contiguous() and t.is_cuda
+    return t.data_ptr()
 
 
 def _lp(t):
-    if t is not None:
-        assert t.dtype == torch.int64 and t.is_contiguous() and t.is_cuda
-    return _ptr(t, C.c_int64)
+    if t is None:
+        return None
+    assert t.dtype is _I64 and t.is_contiguous() and t.is_cuda
+    return t.data_ptr()
+
+
+def _rates_struct(g: Dict[str, torch.Tensor]) -> N.CsphRatesOut:
+    return N.CsphRatesOut.from_buffer_copy(
+        _PACK5.pack(*[_dp(g[k]) for k in ("drho", "dvx", "dvy", "dvz", "dE")]))
 
 
 def _stream(stream=None):
@@ -150,14 +161,10 @@ class State:
         return out
 
     def c(self) -> N.CsphState:
-        s = N.CsphState()
-        s.n = self.n
-        for k in STATE_FIELDS:
-            setattr(s, k, _dp(self.t[k]))
-        s.mat = _ip(self.mat)
-        s.d = _dp(self.d)
-        s.id = _lp(self.id)
-        return s
+        t = self.t
+        return N.CsphState.from_buffer_copy(_PACK_STATE.pack(
+            self.n, *[_dp(t[k]) for k in STATE_FIELDS], _ip(self.mat) or 0, _dp(self.d) or 0,
+            _lp(self.id) or 0))
 
 
 class Workspace:
@@ -262,7 +269,7 @@ def csph_bin(x, y, z, grid: N.CsphGrid, ws: Optional[Workspace] = None, stream=N
     perm = torch.empty(max(n, 1), dtype=torch.int32, device=x.device)
     cs = torch.empty(grid.nkey + 1, dtype=torch.int32, device=x.device)
     _with_ws(lambda w, b, nd: L.csph_bin(_dp(x), _dp(y), _dp(z), n, C.byref(grid),
-                                         C.cast(C.c_void_p(key.data_ptr()), C.POINTER(C.c_uint32)),
+                                         key.data_ptr(),
                                          _ip(perm), _ip(cs), cs.shape[0], w, b, nd,
                                          _stream(stream)), ws, "csph_bin")
     return key[:n].to(torch.int64) & 0xFFFFFFFF, perm[:n], cs
@@ -301,7 +308,7 @@ def csph_rates(state: State, params: Params, t: float = 0.0, ws: Optional[Worksp
     sig = torch.empty(n, dtype=torch.float64, device=dev) if want_signal else None
     cnt = torch.empty(n, dtype=torch.int32, device=dev) if want_count else None
     nonphys = torch.zeros(1, dtype=torch.int64, device=dev)
-    ro = N.CsphRatesOut(*[_dp(out[k]) for k in ("drho", "dvx", "dvy", "dvz", "dE")])
+    ro = _rates_struct(out)
     s = state.c()
     p = params.c()
     status = _with_ws(lambda w, b, nd: L.csph_rates(C.byref(s), C.byref(p), float(t), ro,
@@ -467,7 +474,7 @@ GRAD_FIELDS = ("x", "y", "z", "vx", "vy", "vz", "rho", "E")
 
 
 def _grad_struct(g: Dict[str, torch.Tensor]) -> N.CsphGrad:
-    return N.CsphGrad(*[_dp(g[k]) for k in GRAD_FIELDS])
+    return N.CsphGrad.from_buffer_copy(_PACK8.pack(*[_dp(g[k]) for k in GRAD_FIELDS]))
 
 
 def zeros_grad(n: int, device="cuda") -> Dict[str, torch.Tensor]:
@@ -487,7 +494,7 @@ def csph_rates_vjp(state: State, params: Params, cot: Dict[str, torch.Tensor],
         g_state = zeros_grad(state.n, dev)
     if g_eos is None:
         g_eos = torch.zeros(2 * len(params.eos), dtype=torch.float64, device=dev)
-    a = N.CsphRatesOut(*[_dp(cot[k]) for k in ("drho", "dvx", "dvy", "dvz", "dE")])
+    a = _rates_struct(cot)
     s = state.c()
     p = params.c()
     gs = _grad_struct(g_state)
@@ -585,12 +592,6 @@ class BalanceParams:
                                    float(self.dsh))
 
 
-def _u32p(t):
-    if t is not None:
-        assert t.dtype == torch.int32 and t.is_contiguous() and t.is_cuda
-    return _ptr(t, C.c_uint32)
-
-
 def adjacency_matrix(bits: torch.Tensor, K: int) -> torch.Tensor:
     """Unpack the K x ceil(K/32) word bit matrix into a bool [K, K] tensor (host copy)."""
     w = bits.view(K, -1).cpu().to(torch.int64) & 0xFFFFFFFF
@@ -618,7 +619,7 @@ def csph_balance_stats(x, y, z, owner, sites: torch.Tensor, dsh: float,
                adjacency=torch.empty(K, (K + 31) // 32, dtype=torch.int32, device=dev))
     _with_ws(lambda p, b, nd: L.csph_balance_stats(
         _dp(x), _dp(y), _dp(z), n, _ip(owner), _ip(nbr_count), _dp(sites), K, float(dsh),
-        _lp(out["particles"]), _lp(out["pairs"]), _dp(out["centre"]), _u32p(out["adjacency"]),
+        _lp(out["particles"]), _lp(out["pairs"]), _dp(out["centre"]), _ip(out["adjacency"]),
         p, b, nd, _stream(stream)), ws, "csph_balance_stats")
     return out
 
@@ -635,7 +636,7 @@ def csph_balance_move(sites: torch.Tensor, stats: Dict[str, torch.Tensor], bp: B
     ms = torch.empty(1, dtype=torch.float64, device=sites.device)
     p = bp.c()
     st = L.csph_balance_move(_dp(sites), K, _lp(loads.contiguous()), _dp(stats["centre"]),
-                             _u32p(stats["adjacency"]), C.byref(p), _dp(new), _dp(ms),
+                             _ip(stats["adjacency"]), C.byref(p), _dp(new), _dp(ms),
                              _stream(stream))
     N.check(st, "csph_balance_move")
     return new, ms
