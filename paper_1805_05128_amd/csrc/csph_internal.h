@@ -17,7 +17,7 @@ constexpr int kReduceBlocks = 1024;   // partial-reduction blocks (bounds, total
 constexpr int kScanItems = 8;
 constexpr int kScanTile = kBlock * kScanItems;
 constexpr int kMaxSites = 1024;       // Voronoi generators held in LDS (36 B each)
-constexpr int kMaxBalanceSites = 512; // balancer generators held in LDS (84 B each)
+constexpr int kMaxBalanceSites = 512; // balancer generators held in LDS (84 B each, and a bit a pair)
 constexpr int kXcd = 8;               // accelerator dies; workgroups go to them round robin
 constexpr int kSlabShift = 4;         // cell order: y-slabs of 16 rows (see cell_key)
 constexpr int kVlChunk = 8;           // Verlet-list entries per lane-owned 32-byte chunk

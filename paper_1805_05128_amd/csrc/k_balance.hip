@@ -10,22 +10,32 @@
 //     generator l lies within D^sh of the k|l bisector plane marks (k, l) and
 //     (l, k) in a K x K bit matrix (the same FP64 expressions as the CPU
 //     reference, no contraction, so the bits are exact).
-// Move (one workgroup, one thread per generator): two-body displacement
+// Move (one wave per generator): two-body displacement
 // (eq. BalancingOffset), three-body rotations about the circumcentre of each
 // triplet of mutually touching subdomains (eqs. BalancingOffsetPlusRot,
 // BalancingOffsetRot) with the shift capped at D^sh, and the cumulative
 // movement (eq. TotalOffset); the sum of |g' - g| (eq. VDConvergence) is
 // reduced in a fixed order.
 #include "csph_internal.h"
+#include "nearest.h"
 
 namespace csph {
 
-// defined with the Voronoi and binning kernels
-__global__ void k_zero_u64(unsigned long long *p, int count);
-__global__ void k_fill_i32(int32_t *p, int32_t v, int64_t count);
-
 constexpr double kFix = 4294967296.0;  // 2^32: fixed-point scale of the centre sums
 constexpr double kFixMax = 72057594037927936.0;  // 2^56: per-particle bound (|x - g| < 2^24)
+
+// below this every wave's sum over kNearTile particles fits 63 bits
+constexpr double kFixWave = 9007199254740992.0;  // 2^53
+
+// Words of the touching pairs a > b of K subdomains, one bit each.  A workgroup gathers them in
+// LDS and adds them to the matrix at its end: set in memory by the lanes that find them, a few
+// words (and the loads that look whether a bit is there already) took 0.45 ms of the 0.48 ms of
+// 2.9 M particles.
+__host__ __device__ constexpr int tri_words(int K) { return (K * (K - 1) / 2 + 31) / 32; }
+
+__device__ __forceinline__ double norm2(double x, double y, double z) {
+    return __dadd_rn(__dadd_rn(__dmul_rn(x, x), __dmul_rn(y, y)), __dmul_rn(z, z));
+}
 
 // 128-bit two's-complement accumulator {lo, hi}: add a signed 64-bit value.
 __device__ __forceinline__ void add128(unsigned long long *lo, unsigned long long *hi, long long v) {
@@ -49,6 +59,7 @@ __global__ __launch_bounds__(kBlock) void k_balance_stats(
     unsigned long long *s_hi = s_lo + 3 * K;                             // 3K
     unsigned long long *s_pairs = s_hi + 3 * K;                          // K
     unsigned int *s_part = (unsigned int *)(s_pairs + K);                // K
+    uint32_t *s_tri = s_part + K;                                        // tri_words(K)
     for (int k = threadIdx.x; k < 3 * K; k += kBlock) {
         gs[k] = sites[k];
         s_lo[k] = 0ull;
@@ -58,89 +69,103 @@ __global__ __launch_bounds__(kBlock) void k_balance_stats(
         s_pairs[k] = 0ull;
         s_part[k] = 0u;
     }
+    for (int q = threadIdx.x; q < tri_words(K); q += kBlock) s_tri[q] = 0u;
     __syncthreads();
     const double lim = 4.0 * (dsh * dsh);
-    // wave-uniform grid-stride loop: every lane of a wave takes part in the shuffles
-    for (int64_t base = (int64_t)blockIdx.x * kBlock; base < n;
-         base += (int64_t)gridDim.x * kBlock) {
-        const int64_t i = base + threadIdx.x;
-        const int kr = i < n ? owner[i] : -1;
-        const bool ok = kr >= 0 && kr < K;
-        const int k = ok ? kr : 0;
-        double p[3] = {0.0, 0.0, 0.0};
-        long long v[3] = {0, 0, 0};
-        unsigned long long pc = 0ull;
-        if (ok) {
-            p[0] = x[i];
-            p[1] = y[i];
-            p[2] = z[i];
+    const NearTiles run = near_tiles(n);
+    for (int64_t tile = run.at; tile < run.end; ++tile) {
+        const int64_t i0 = tile * kNearTile + (threadIdx.x & 63);
+        LaneParticles<kNearPer> w;
+        int k[kNearPer];
+        long long v[kNearPer][3];
+        unsigned long long pc[kNearPer];
+        bool any = false, large = false;
+#pragma unroll
+        for (int q = 0; q < kNearPer; ++q) {
+            const int64_t i = i0 + 64 * q;
+            const int kr = i < n ? owner[i] : -1;
+            w.on[q] = kr >= 0 && kr < K;
+            any = any || w.on[q];
+            k[q] = w.on[q] ? kr : 0;
+            w.p[q][0] = w.on[q] ? x[i] : 0.0;
+            w.p[q][1] = w.on[q] ? y[i] : 0.0;
+            w.p[q][2] = w.on[q] ? z[i] : 0.0;
+            pc[q] = w.on[q] && nbr_count ? (unsigned long long)nbr_count[i] : 0ull;
 #pragma unroll
             for (int d = 0; d < 3; ++d) {
-                // |x - g| < 2^24: the value and any 64 of them fit in 63 bits
-                const double f = fmin(fmax((p[d] - gs[3 * k + d]) * kFix, -kFixMax), kFixMax);
-                v[d] = __double2ll_rn(f);
+                const double f =
+                    fmin(fmax((w.p[q][d] - gs[3 * k[q] + d]) * kFix, -kFixMax), kFixMax);
+                v[q][d] = __double2ll_rn(f);
+                large = large || (w.on[q] && fabs(f) >= kFixWave);
             }
-            pc = nbr_count ? (unsigned long long)nbr_count[i] : 0ull;
         }
-        const unsigned long long okm = __ballot(ok);
-        if (okm == 0ull) continue;
-        const int lead = __ffsll(okm) - 1;
-        const int k0 = __shfl(k, lead, 64);
-        if (__all(!ok || k == k0)) {
-            // particles are in cell order, so a wave mostly shares one owner: sum the wave
-            // in registers (exact integers; lanes without a particle add zeros) and let one
-            // lane add the totals
-            long long w0 = v[0], w1 = v[1], w2 = v[2];
-            unsigned long long wp = pc;
-            for (int o = 32; o > 0; o >>= 1) {
-                w0 += __shfl_xor(w0, o, 64);
-                w1 += __shfl_xor(w1, o, 64);
-                w2 += __shfl_xor(w2, o, 64);
-                wp += __shfl_xor(wp, o, 64);
-            }
-            if ((int)(threadIdx.x & 63) == lead) {
-                atomicAdd(&s_part[k0], (unsigned)__popcll(okm));
-                if (nbr_count) atomicAdd(&s_pairs[k0], wp);
-                add128(&s_lo[3 * k0], &s_hi[3 * k0], w0);
-                add128(&s_lo[3 * k0 + 1], &s_hi[3 * k0 + 1], w1);
-                add128(&s_lo[3 * k0 + 2], &s_hi[3 * k0 + 2], w2);
-            }
-        } else if (ok) {
-            atomicAdd(&s_part[k], 1u);
-            if (nbr_count) atomicAdd(&s_pairs[k], pc);
+        if (!__any(any)) continue;
+        bool on[kNearPer];
 #pragma unroll
-            for (int d = 0; d < 3; ++d) add128(&s_lo[3 * k + d], &s_hi[3 * k + d], v[d]);
+        for (int q = 0; q < kNearPer; ++q) on[q] = w.on[q];
+        // the wave's sums per owner (exact integers), added by one lane
+        if (!__any(large))
+            for_owners<kNearPer>(on, k, [&](int k0, const bool(&mine)[kNearPer], int count) {
+                unsigned long long sp = 0, sv[3] = {0, 0, 0};
+#pragma unroll
+                for (int q = 0; q < kNearPer; ++q) {
+                    sp += mine[q] ? pc[q] : 0ull;
+#pragma unroll
+                    for (int d = 0; d < 3; ++d)
+                        sv[d] += mine[q] ? (unsigned long long)v[q][d] : 0ull;
+                }
+                if (nbr_count) sp = wave_all_sum(sp);
+#pragma unroll
+                for (int d = 0; d < 3; ++d) sv[d] = wave_all_sum(sv[d]);
+                if ((threadIdx.x & 63) == 0) {
+                    atomicAdd(&s_part[k0], (unsigned)count);
+                    if (nbr_count) atomicAdd(&s_pairs[k0], sp);
+#pragma unroll
+                    for (int d = 0; d < 3; ++d)
+                        add128(&s_lo[3 * k0 + d], &s_hi[3 * k0 + d], (long long)sv[d]);
+                }
+            });
+#pragma unroll
+        for (int q = 0; q < kNearPer; ++q) {
+            if (!on[q]) continue;
+            atomicAdd(&s_part[k[q]], 1u);
+            if (nbr_count) atomicAdd(&s_pairs[k[q]], pc[q]);
+#pragma unroll
+            for (int d = 0; d < 3; ++d) add128(&s_lo[3 * k[q] + d], &s_hi[3 * k[q] + d], v[q][d]);
         }
-        if (!ok) continue;
         if (K > 1) {
             // nearest other generator (ties to the smaller index) and the owner's distance
-            double d2o = 0.0, bd = INFINITY;
-            int best = -1;
-            for (int l = 0; l < K; ++l) {
-                const double ex = p[0] - gs[3 * l], ey = p[1] - gs[3 * l + 1],
-                             ez = p[2] - gs[3 * l + 2];
-                const double d2 = __dadd_rn(__dadd_rn(__dmul_rn(ex, ex), __dmul_rn(ey, ey)),
-                                            __dmul_rn(ez, ez));
-                if (l == k) {
-                    d2o = d2;
-                } else if (d2 < bd) {
-                    bd = d2;
-                    best = l;
-                }
+            double bd[kNearPer];
+            int best[kNearPer];
+#pragma unroll
+            for (int q = 0; q < kNearPer; ++q) {
+                bd[q] = INFINITY;
+                best[q] = -1;
             }
-            if (best < 0) continue;  // no finite distance to another generator
-            const double gx = gs[3 * best] - gs[3 * k], gy = gs[3 * best + 1] - gs[3 * k + 1],
-                         gz = gs[3 * best + 2] - gs[3 * k + 2];
-            const double gg = __dadd_rn(__dadd_rn(__dmul_rn(gx, gx), __dmul_rn(gy, gy)),
-                                        __dmul_rn(gz, gz));
-            const double q = __dsub_rn(bd, d2o);
-            if (__dmul_rn(q, q) < __dmul_rn(lim, gg)) {
-                uint32_t *w1 = adj + (size_t)k * W + (best >> 5);
-                const uint32_t b1 = 1u << (best & 31);
-                if (!(*w1 & b1)) atomicOr(w1, b1);
-                uint32_t *w2 = adj + (size_t)best * W + (k >> 5);
-                const uint32_t b2 = 1u << (k & 31);
-                if (!(*w2 & b2)) atomicOr(w2, b2);
+            near_sites<true, kNearPer>(gs, K, w, [&](int l) {
+                const double gx = gs[3 * l], gy = gs[3 * l + 1], gz = gs[3 * l + 2];
+#pragma unroll
+                for (int q = 0; q < kNearPer; ++q) {
+                    const double d2 = norm2(w.p[q][0] - gx, w.p[q][1] - gy, w.p[q][2] - gz);
+                    if (l != k[q] && d2 < bd[q]) {
+                        bd[q] = d2;
+                        best[q] = l;
+                    }
+                }
+            });
+#pragma unroll
+            for (int q = 0; q < kNearPer; ++q) {
+                // best < 0: no finite distance to another generator
+                const int a = k[q], b = best[q] < 0 ? a : best[q];
+                const double d2o = norm2(w.p[q][0] - gs[3 * a], w.p[q][1] - gs[3 * a + 1],
+                                         w.p[q][2] - gs[3 * a + 2]);
+                const double gg = norm2(gs[3 * b] - gs[3 * a], gs[3 * b + 1] - gs[3 * a + 1],
+                                        gs[3 * b + 2] - gs[3 * a + 2]);
+                const double u = __dsub_rn(bd[q], d2o);
+                if (!w.on[q] || best[q] < 0 || !(__dmul_rn(u, u) < __dmul_rn(lim, gg))) continue;
+                const int hi = max(a, b), bit = hi * (hi - 1) / 2 + min(a, b);
+                const uint32_t m = 1u << (bit & 31);
+                if (!(s_tri[bit >> 5] & m)) atomicOr(&s_tri[bit >> 5], m);
             }
         }
     }
@@ -148,6 +173,18 @@ __global__ __launch_bounds__(kBlock) void k_balance_stats(
     for (int k = threadIdx.x; k < K; k += kBlock) {
         if (s_part[k]) atomicAdd(&g_part[k], (unsigned long long)s_part[k]);
         if (s_pairs[k]) atomicAdd(&g_pairs[k], s_pairs[k]);
+    }
+    for (int q = threadIdx.x; q < tri_words(K); q += kBlock) {
+        for (uint32_t m = s_tri[q]; m; m &= m - 1) {
+            // bit t is the pair a > b with t = a (a - 1) / 2 + b
+            const int t = 32 * q + __ffs(m) - 1;
+            int a = (int)(0.5f * (1.0f + sqrtf(1.0f + 8.0f * (float)t)));
+            while (a * (a - 1) / 2 > t) --a;
+            while (a * (a + 1) / 2 <= t) ++a;
+            const int b = t - a * (a - 1) / 2;
+            atomicOr(adj + (size_t)a * W + (b >> 5), 1u << (b & 31));
+            atomicOr(adj + (size_t)b * W + (a >> 5), 1u << (a & 31));
+        }
     }
     for (int k = threadIdx.x; k < 3 * K; k += kBlock) {
         const unsigned long long lo = s_lo[k], hi = s_hi[k];
@@ -208,76 +245,137 @@ __device__ V3 rotate(V3 v, V3 u, double a) {
     return c * v + s * cross(u, v) + (dot(u, v) * (1.0 - c)) * u;
 }
 
-__device__ __forceinline__ bool touch(const uint32_t *adj, int W, int a, int b) {
-    return (adj[(size_t)a * W + (b >> 5)] >> (b & 31)) & 1u;
-}
-
-__global__ __launch_bounds__(1024) void k_balance_move(
+// One wave moves generator k = blockIdx.x.  A lane takes one neighbour l, then one triplet
+// (l, m), at a time; the terms of up to 64 of them are then added in the order of (l, m), so the
+// sums are those of a plain loop.  With a thread per generator the whole move was the chain of
+// the longest generator's ~40 triplets, a few microseconds each (64 generators: 120 -> 13 us,
+// and 5 us for the sum of the moves).
+__global__ __launch_bounds__(64) void k_balance_move(
     const double *__restrict__ sites, int K, int W, const int64_t *__restrict__ loads,
     const double *__restrict__ centre, const uint32_t *__restrict__ adj, double sigma,
-    double theta, double gamma, double dsh, double *__restrict__ out, double *__restrict__ move_sum) {
+    double theta, double gamma, double dsh, double *__restrict__ out) {
     extern __shared__ double sm[];
     double *sg = sm;                         // 3K generators
     double *sL = sg + 3 * K;                 // K loads
-    uint32_t *sa = (uint32_t *)(sL + K);     // K x W adjacency words
-    __shared__ double red[1024];
-    for (int q = threadIdx.x; q < 3 * K; q += blockDim.x) sg[q] = sites[q];
-    for (int q = threadIdx.x; q < K; q += blockDim.x) sL[q] = (double)loads[q];
-    for (int q = threadIdx.x; q < K * W; q += blockDim.x) sa[q] = adj[q];
+    double *term = sL + K;                   // 64 terms of 3
+    uint32_t *sa = (uint32_t *)(term + 192); // K x W adjacency words
+    const int k = blockIdx.x, lane = threadIdx.x;
+    for (int q = lane; q < 3 * K; q += 64) sg[q] = sites[q];
+    for (int q = lane; q < K; q += 64) sL[q] = (double)loads[q];
+#pragma unroll 8
+    for (int q = lane; q < K * W; q += 64) sa[q] = adj[q];
     __syncthreads();
-    const int k = threadIdx.x;
-    double mv = 0.0;
-    if (k < K) {
-        const V3 gk{sg[3 * k], sg[3 * k + 1], sg[3 * k + 2]};
-        const double Lk = sL[k];
-        const uint32_t *rk = sa + (size_t)k * W;
-        V3 two{0.0, 0.0, 0.0}, three{0.0, 0.0, 0.0};
-        for (int wl = 0; wl < W; ++wl) {
-            for (uint32_t bl = rk[wl] & ~(wl == (k >> 5) ? (1u << (k & 31)) : 0u); bl;
-                 bl &= bl - 1) {
-                const int l = wl * 32 + __ffs(bl) - 1;
-                const V3 gl{sg[3 * l], sg[3 * l + 1], sg[3 * l + 2]};
-                const double Ll = sL[l];
-                const V3 gkl = gk - gl;
-                const double nd = sqrt(dot(gkl, gkl));
-                if (Lk + Ll != 0.0 && nd != 0.0)
-                    two = two + (dsh * (Lk - Ll) / (Lk + Ll) / nd) * gkl;
-                // m > l touching both k and l: the intersection of rows k and l
-                const uint32_t *rl = sa + (size_t)l * W;
-                for (int wm = l >> 5; wm < W; ++wm) {
-                    uint32_t bm = rk[wm] & rl[wm];
-                    if (wm == (l >> 5)) bm &= ~((2u << (l & 31)) - 1u);  // m > l
-                    if (wm == (k >> 5)) bm &= ~(1u << (k & 31));         // m != k
-                    for (; bm; bm &= bm - 1) {
-                        const int m = wm * 32 + __ffs(bm) - 1;
-                        const V3 gm{sg[3 * m], sg[3 * m + 1], sg[3 * m + 2]};
-                        const double Lm = sL[m];
-                        const double S = Lk + Ll + Lm;
-                        // circumcentre of the triangle (g_k, g_l, g_m)
-                        const V3 a = gl - gk, b = gm - gk;
-                        const V3 nrm = cross(a, b);
-                        const double n2 = dot(nrm, nrm);
-                        if (S == 0.0 || !(n2 > 1e-24 * dot(a, a) * dot(b, b))) continue;
-                        const V3 o = gk + (0.5 / n2) * cross(dot(a, a) * b - dot(b, b) * a, nrm);
-                        const V3 ck = gk - o, cl = gl - o, cm = gm - o;
-                        const V3 axl = cross(ck, cl), axm = cross(ck, cm);
-                        if (dot(axl, axl) == 0.0 || dot(axm, axm) == 0.0) continue;
-                        const double al = (M_PI / 3.0) * (Ll - Lk) / S;
-                        const double am = (M_PI / 3.0) * (Lm - Lk) / S;
-                        three = three + (rotate(rotate(ck, axl, al), axm, am) - ck);
-                    }
+    const V3 gk{sg[3 * k], sg[3 * k + 1], sg[3 * k + 2]};
+    const double Lk = sL[k];
+    const uint32_t *rk = sa + (size_t)k * W;
+    // adds the first `count` lanes' terms to sum in lane order (the same in every lane)
+    auto add_terms = [&](V3 &sum, const V3 &t, bool counts, int count) {
+        term[3 * lane] = t.x;
+        term[3 * lane + 1] = t.y;
+        term[3 * lane + 2] = t.z;
+        const unsigned long long m = __ballot(counts);
+        __syncthreads();
+        for (int q = 0; q < count; ++q) {
+            if (!((m >> q) & 1ull)) continue;
+            sum = sum + V3{term[3 * q], term[3 * q + 1], term[3 * q + 2]};
+        }
+        __syncthreads();
+    };
+    V3 two{0.0, 0.0, 0.0}, three{0.0, 0.0, 0.0};
+    int myl = 0, mym = 0, queued = 0;
+    auto flush_two = [&]() {
+        V3 t{0.0, 0.0, 0.0};
+        bool counts = false;
+        if (lane < queued) {
+            const V3 gl{sg[3 * myl], sg[3 * myl + 1], sg[3 * myl + 2]};
+            const double Ll = sL[myl];
+            const V3 gkl = gk - gl;
+            const double nd = sqrt(dot(gkl, gkl));
+            counts = Lk + Ll != 0.0 && nd != 0.0;
+            if (counts) t = (dsh * (Lk - Ll) / (Lk + Ll) / nd) * gkl;
+        }
+        add_terms(two, t, counts, queued);
+        queued = 0;
+    };
+    auto flush_three = [&]() {
+        V3 t{0.0, 0.0, 0.0};
+        bool counts = false;
+        if (lane < queued) {
+            const V3 gl{sg[3 * myl], sg[3 * myl + 1], sg[3 * myl + 2]};
+            const V3 gm{sg[3 * mym], sg[3 * mym + 1], sg[3 * mym + 2]};
+            const double Ll = sL[myl], Lm = sL[mym];
+            const double S = Lk + Ll + Lm;
+            // circumcentre of the triangle (g_k, g_l, g_m)
+            const V3 a = gl - gk, b = gm - gk;
+            const V3 nrm = cross(a, b);
+            const double n2 = dot(nrm, nrm);
+            if (S != 0.0 && n2 > 1e-24 * dot(a, a) * dot(b, b)) {
+                const V3 o = gk + (0.5 / n2) * cross(dot(a, a) * b - dot(b, b) * a, nrm);
+                const V3 ck = gk - o, cl = gl - o, cm = gm - o;
+                const V3 axl = cross(ck, cl), axm = cross(ck, cm);
+                counts = dot(axl, axl) != 0.0 && dot(axm, axm) != 0.0;
+                if (counts) {
+                    const double al = (M_PI / 3.0) * (Ll - Lk) / S;
+                    const double am = (M_PI / 3.0) * (Lm - Lk) / S;
+                    t = rotate(rotate(ck, axl, al), axm, am) - ck;
                 }
             }
         }
-        const double nt = sqrt(dot(three, three));
-        if (nt > dsh) three = (dsh / nt) * three;
-        const V3 dg = (1.0 - sigma) * two + sigma * three;
-        const V3 rc{centre[3 * k], centre[3 * k + 1], centre[3 * k + 2]};
-        const V3 g2 = (1.0 - theta) * (gk + gamma * dg) + theta * rc;
+        add_terms(three, t, counts, queued);
+        queued = 0;
+    };
+    // the wave hands out neighbours, then triplets, in order (wave-uniform loops)
+    auto each_neighbour = [&](auto &&f) {
+        for (int wl = 0; wl < W; ++wl)
+            for (uint32_t bl = __builtin_amdgcn_readfirstlane(rk[wl]) &
+                               ~(wl == (k >> 5) ? (1u << (k & 31)) : 0u);
+                 bl; bl &= bl - 1)
+                f(wl * 32 + __ffs(bl) - 1);
+    };
+    each_neighbour([&](int l) {
+        if (lane == queued) myl = l;
+        if (++queued == 64) flush_two();
+    });
+    if (queued) flush_two();
+    each_neighbour([&](int l) {
+        // m > l touching both k and l: the intersection of rows k and l
+        const uint32_t *rl = sa + (size_t)l * W;
+        for (int wm = l >> 5; wm < W; ++wm) {
+            uint32_t bm = __builtin_amdgcn_readfirstlane(rk[wm] & rl[wm]);
+            if (wm == (l >> 5)) bm &= ~((2u << (l & 31)) - 1u);  // m > l
+            if (wm == (k >> 5)) bm &= ~(1u << (k & 31));         // m != k
+            for (; bm; bm &= bm - 1) {
+                if (lane == queued) {
+                    myl = l;
+                    mym = wm * 32 + __ffs(bm) - 1;
+                }
+                if (++queued == 64) flush_three();
+            }
+        }
+    });
+    if (queued) flush_three();
+    const double nt = sqrt(dot(three, three));
+    if (nt > dsh) three = (dsh / nt) * three;
+    const V3 dg = (1.0 - sigma) * two + sigma * three;
+    const V3 rc{centre[3 * k], centre[3 * k + 1], centre[3 * k + 2]};
+    const V3 g2 = (1.0 - theta) * (gk + gamma * dg) + theta * rc;
+    if (lane == 0) {
         out[3 * k] = g2.x;
         out[3 * k + 1] = g2.y;
         out[3 * k + 2] = g2.z;
-        const V3 d = g2 - gk;
+    }
+}
+
+// sum_k |g'_k - g_k| in a fixed tree (one workgroup of a power of two >= K threads).
+__global__ __launch_bounds__(1024) void k_balance_moved(const double *__restrict__ sites, int K,
+                                                        const double *__restrict__ out,
+                                                        double *__restrict__ move_sum) {
+    __shared__ double red[1024];
+    const int k = threadIdx.x;
+    double mv = 0.0;
+    if (k < K) {
+        const V3 d = V3{out[3 * k], out[3 * k + 1], out[3 * k + 2]} -
+                     V3{sites[3 * k], sites[3 * k + 1], sites[3 * k + 2]};
         mv = sqrt(dot(d, d));
     }
     red[threadIdx.x] = mv;
@@ -300,15 +398,12 @@ hipError_t launch_balance_stats(const double *x, const double *y, const double *
     unsigned long long *g_part = (unsigned long long *)ws;   // K
     unsigned long long *g_pairs = g_part + K;                // K
     unsigned long long *g_sum = g_pairs + K;                 // 6K: lo[3K], hi[3K]
-    const int nz = 8 * K;
-    k_zero_u64<<<(unsigned)((nz + kBlock - 1) / kBlock), kBlock, 0, st>>>(g_part, nz);
-    const int na = K * W;
-    k_fill_i32<<<(unsigned)((na + kBlock - 1) / kBlock), kBlock, 0, st>>>((int32_t *)adj, 0, na);
+    launch_zero2(g_part, 16 * K, adj, K * W, st);
     if (n > 0) {
-        int64_t want = (n + kBlock - 1) / kBlock;
-        unsigned nb = (unsigned)(want > kReduceBlocks ? kReduceBlocks : want);
-        size_t shm = (size_t)K * (3 * sizeof(double) + 7 * sizeof(unsigned long long) +
-                                  sizeof(unsigned int));
+        const unsigned nb = near_blocks(n, kReduceBlocks);
+        const size_t shm = (size_t)K * (3 * sizeof(double) + 7 * sizeof(unsigned long long) +
+                                        sizeof(unsigned int)) +
+                           sizeof(uint32_t) * tri_words(K);
         k_balance_stats<<<nb, kBlock, shm, st>>>(x, y, z, n, owner, nbr_count, sites, K, W, dsh,
                                                  g_part, g_pairs, g_sum, adj);
     }
@@ -322,12 +417,13 @@ hipError_t launch_balance_move(const double *sites, int K, const int64_t *loads,
                                double theta, double gamma, double dsh, double *out,
                                double *move_sum, hipStream_t st) {
     const int W = (K + 31) / 32;
-    // one thread per generator, rounded up to whole waves (block sums in a fixed tree)
+    // the sum's threads: one per generator, rounded up to whole waves
     int nt = 64;
     while (nt < K) nt *= 2;
-    const size_t shm = sizeof(double) * 4 * (size_t)K + sizeof(uint32_t) * (size_t)K * W;
-    k_balance_move<<<1, nt, shm, st>>>(sites, K, W, loads, centre, adj, sigma, theta, gamma, dsh,
-                                       out, move_sum);
+    const size_t shm = sizeof(double) * (4 * (size_t)K + 192) + sizeof(uint32_t) * (size_t)K * W;
+    k_balance_move<<<(unsigned)K, 64, shm, st>>>(sites, K, W, loads, centre, adj, sigma, theta,
+                                                 gamma, dsh, out);
+    k_balance_moved<<<1, nt, 0, st>>>(sites, K, out, move_sum);
     return hipGetLastError();
 }
 

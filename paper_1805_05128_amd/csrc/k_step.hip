@@ -8,6 +8,7 @@
 // caller's dt.  Totals use double-double (TwoSum) accumulation in a fixed
 // reduction tree, so they are reproducible run to run.
 #include "csph_internal.h"
+#include "nearest.h"
 
 namespace csph {
 
@@ -146,11 +147,12 @@ struct KeptDev {
 
 // With VORO the kernel also assigns each particle's new position to its Voronoi generator
 // (eq. VoronoiDefinition: FP64 argmin of ((dx dx) + (dy dy)) + (dz dz) without contraction,
-// k scanned upwards with a strict comparison, so a tie keeps the smaller k) and counts
-// particles and pairs per generator, as k_voronoi does: the VALU-bound scan overlaps the
-// memory-bound update.  The generators come in the kernels' axes (x and y exchanged when the
-// library hands the kernels the caller's y as x), which leaves every squared distance
-// unchanged (the sum of the x and y terms is commutative).
+// k scanned upwards with a strict comparison, so a tie keeps the smaller k, over the generators
+// near the wave: nearest.h) and counts particles and pairs per generator, as k_voronoi does.
+// The generators come in the kernels' axes (x and y exchanged when the library hands the
+// kernels the caller's y as x), which leaves every squared distance unchanged (the sum of the x
+// and y terms is commutative).
+template <bool VORO>
 __global__ __launch_bounds__(kBlock) void k_integrate(int64_t n, State9 s, Rates5 r,
                                                       const unsigned long long *dtmin, double cfl,
                                                       double dt_in, WallDev wall, PerDev per,
@@ -161,7 +163,7 @@ __global__ __launch_bounds__(kBlock) void k_integrate(int64_t n, State9 s, Rates
     double *gs = vsm;                                                   // 3K
     unsigned long long *hq = (unsigned long long *)(vsm + 3 * vo.K);    // K
     unsigned int *hp = (unsigned int *)(hq + vo.K);                     // K
-    if (vo.K > 0) {
+    if (VORO) {
         for (int k = threadIdx.x; k < vo.K; k += kBlock) {
             gs[3 * k] = vo.sites[3 * k + vo.ax[0]];
             gs[3 * k + 1] = vo.sites[3 * k + vo.ax[1]];
@@ -176,67 +178,67 @@ __global__ __launch_bounds__(kBlock) void k_integrate(int64_t n, State9 s, Rates
     DD acc[5];
     for (int k = 0; k < 5; ++k) acc[k] = DD{0.0, 0.0};
     unsigned long long npairs = 0;
-    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * kBlock) {
-        if (lg.pairs) npairs += (unsigned long long)lg.cnt[i];
-        double vx = s.f[3][i] + dt * r.f[1][i];
-        double vy = s.f[4][i] + dt * r.f[2][i];
-        double vz = s.f[5][i] + dt * r.f[3][i];
-        double E = s.f[7][i] + dt * r.f[4][i];
-        double rho = s.f[6][i] + dt * r.f[0][i];
-        double y = s.f[1][i] + dt * vy;
-        reflect(wall, yw, y, vy, E);
-        double x = s.f[0][i] + dt * vx, z = s.f[2][i] + dt * vz;
-        if (per.mask) {  // after the reflection, as the wall's axis is never periodic
-            x = wrap_axis(per, 0, x);
-            y = wrap_axis(per, 1, y);
-            z = wrap_axis(per, 2, z);
-        }
-        const int64_t to = ko.perm ? (int64_t)ko.perm[i] : i;
-        double *const *const out = ko.perm ? ko.f : s.f;
-        out[0][to] = x;
-        out[1][to] = y;
-        out[2][to] = z;
-        if (vo.K > 0) {
-            int best = 0;
-            double bd = INFINITY;
-            for (int k = 0; k < vo.K; ++k) {
-                const double dx = x - gs[3 * k], dy = y - gs[3 * k + 1], dz = z - gs[3 * k + 2];
-                const double d2 = ((dx * dx) + (dy * dy)) + (dz * dz);
-                if (d2 < bd) {
-                    bd = d2;
-                    best = k;
-                }
+    // wave-uniform grid-stride loop (VORO: every lane takes part in the wave's reductions)
+    for (int64_t i0 = (int64_t)blockIdx.x * kBlock + (threadIdx.x & ~63u); i0 < n;
+         i0 += (int64_t)gridDim.x * kBlock) {
+        const int64_t i = i0 + (threadIdx.x & 63);
+        const bool on = i < n;
+        double x = 0.0, y = 0.0, z = 0.0;
+        if (on) {
+            if (lg.pairs) npairs += (unsigned long long)lg.cnt[i];
+            double vx = s.f[3][i] + dt * r.f[1][i];
+            double vy = s.f[4][i] + dt * r.f[2][i];
+            double vz = s.f[5][i] + dt * r.f[3][i];
+            double E = s.f[7][i] + dt * r.f[4][i];
+            double rho = s.f[6][i] + dt * r.f[0][i];
+            y = s.f[1][i] + dt * vy;
+            reflect(wall, yw, y, vy, E);
+            x = s.f[0][i] + dt * vx;
+            z = s.f[2][i] + dt * vz;
+            if (per.mask) {  // after the reflection, as the wall's axis is never periodic
+                x = wrap_axis(per, 0, x);
+                y = wrap_axis(per, 1, y);
+                z = wrap_axis(per, 2, z);
             }
-            vo.owner[vo.owner_at ? vo.owner_at[i] : (int)i] = best;
-            atomicAdd(&hp[best], 1u);
-            atomicAdd(&hq[best], (unsigned long long)vo.cnt[i]);
+            const int64_t to = ko.perm ? (int64_t)ko.perm[i] : i;
+            double *const *const out = ko.perm ? ko.f : s.f;
+            out[0][to] = x;
+            out[1][to] = y;
+            out[2][to] = z;
+            out[3][to] = vx;
+            out[4][to] = vy;
+            out[5][to] = vz;
+            out[6][to] = rho;
+            out[7][to] = E;
+            double m = s.f[8][i];
+            if (ko.perm) {
+                if (ko.f[8]) ko.f[8][to] = m;
+                if (ko.mat_to) ko.mat_to[to] = ko.mat[i];
+                if (ko.d_to) ko.d_to[to] = ko.d[i];
+                if (ko.id_to) ko.id_to[to] = ko.id[i];
+                if (ko.cnt_to) ko.cnt_to[to] = ko.cnt[i];
+            }
+            acc[0] = dd_add1(acc[0], m);
+            acc[1] = dd_add1(acc[1], m * vx);
+            acc[2] = dd_add1(acc[2], m * vy);
+            acc[3] = dd_add1(acc[3], m * vz);
+            acc[4] = dd_add1(acc[4], m * E);
         }
-        out[3][to] = vx;
-        out[4][to] = vy;
-        out[5][to] = vz;
-        out[6][to] = rho;
-        out[7][to] = E;
-        double m = s.f[8][i];
-        if (ko.perm) {
-            if (ko.f[8]) ko.f[8][to] = m;
-            if (ko.mat_to) ko.mat_to[to] = ko.mat[i];
-            if (ko.d_to) ko.d_to[to] = ko.d[i];
-            if (ko.id_to) ko.id_to[to] = ko.id[i];
-            if (ko.cnt_to) ko.cnt_to[to] = ko.cnt[i];
+        if (VORO) {
+            const LaneParticles<1> w{{on}, {{x, y, z}}};
+            const int32_t c[1] = {on && vo.site_pairs ? vo.cnt[i] : 0};
+            int best[1];
+            nearest_site<1>(gs, vo.K, w, best);
+            if (on) vo.owner[vo.owner_at ? vo.owner_at[i] : (int)i] = best[0];
+            count_owners<1>(w.on, best, vo.site_pairs != nullptr, c, hp, hq);
         }
-        acc[0] = dd_add1(acc[0], m);
-        acc[1] = dd_add1(acc[1], m * vx);
-        acc[2] = dd_add1(acc[2], m * vy);
-        acc[3] = dd_add1(acc[3], m * vz);
-        acc[4] = dd_add1(acc[4], m * E);
     }
     block_totals(acc, part);
     if (lg.pairs) {  // integer sums: exact in any order
         for (int o = 32; o > 0; o >>= 1) npairs += __shfl_xor(npairs, o, 64);
         if ((threadIdx.x & 63) == 0 && npairs) atomicAdd(lg.pairs, npairs);
     }
-    if (vo.K > 0) {  // the reduction above ended with a barrier: every count is in LDS
+    if (VORO) {  // the reduction above ended with a barrier: every count is in LDS
         for (int k = threadIdx.x; k < vo.K; k += kBlock) {
             if (hp[k]) atomicAdd(&vo.site_part[k], (unsigned long long)hp[k]);
             if (hq[k] && vo.site_pairs) atomicAdd(&vo.site_pairs[k], hq[k]);
@@ -358,8 +360,7 @@ hipError_t launch_integrate(int64_t n, double *const st8[9], const Ws &w, double
     size_t shm = 0;
     if (vo && vo->K > 0) {
         v = *vo;
-        launch_fill_u64(v.site_part, 0ull, v.K, st);
-        if (v.site_pairs) launch_fill_u64(v.site_pairs, 0ull, v.K, st);
+        launch_zero2(v.site_part, 2 * v.K, v.site_pairs, 2 * v.K, st);
         shm = (size_t)v.K * (3 * sizeof(double) + sizeof(unsigned long long) + sizeof(unsigned));
     }
     const ListGate g = lg ? *lg : ListGate{nullptr, nullptr, nullptr, nullptr};
@@ -379,8 +380,12 @@ hipError_t launch_integrate(int64_t n, double *const st8[9], const Ws &w, double
         k.cnt_to = ko->nbr_count;
     }
     int nb = integrate_blocks(n);
-    k_integrate<<<nb, kBlock, shm, st>>>(n, s, r, w.dtmin, cfl, dt_in, wall, per, v, g, k,
-                                         w.tot_part);
+    if (v.K > 0)
+        k_integrate<true><<<nb, kBlock, shm, st>>>(n, s, r, w.dtmin, cfl, dt_in, wall, per, v, g,
+                                                   k, w.tot_part);
+    else
+        k_integrate<false><<<nb, kBlock, 0, st>>>(n, s, r, w.dtmin, cfl, dt_in, wall, per, v, g,
+                                                  k, w.tot_part);
     return hipGetLastError();
 }
 

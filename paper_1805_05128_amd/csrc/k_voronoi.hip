@@ -1,16 +1,29 @@
 // Voronoi ownership (eq. VoronoiDefinition, sec. 3.1) and per-site load
 // counts.  Generators sit in LDS; each particle takes the FP64 argmin of
 // its squared distance in a fixed operation order without contraction,
-// scanning k upwards with a strict comparison so a tie keeps the smaller k.
-// Counts are integers (LDS atomics per block, then one global atomic per
-// site and block), hence exact and order independent.
+// scanning k upwards with a strict comparison so a tie keeps the smaller k,
+// over the generators that can be nearest to some particle of its wave
+// (nearest.h).  Counts are integers (wave sums, LDS atomics per block, then one
+// global atomic per site and block), hence exact and order independent.
 #include "csph_internal.h"
+#include "nearest.h"
 
 namespace csph {
 
-__global__ __launch_bounds__(kBlock) void k_zero_u64(unsigned long long *p, int count) {
-    int i = blockIdx.x * kBlock + threadIdx.x;
-    if (i < count) p[i] = 0ull;
+__global__ __launch_bounds__(kBlock) void k_zero2(uint32_t *a, int64_t na, uint32_t *b,
+                                                  int64_t nb) {
+    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (i < na) a[i] = 0u;
+    if (i < nb) b[i] = 0u;
+}
+
+hipError_t launch_zero2(void *a, int64_t na, void *b, int64_t nb, hipStream_t st) {
+    if (!b) nb = 0;
+    const int64_t len = na > nb ? na : nb;
+    if (len <= 0) return hipSuccess;
+    k_zero2<<<(unsigned)((len + kBlock - 1) / kBlock), kBlock, 0, st>>>((uint32_t *)a, na,
+                                                                        (uint32_t *)b, nb);
+    return hipGetLastError();
 }
 
 __global__ __launch_bounds__(kBlock) void k_voronoi(const double *__restrict__ x,
@@ -31,22 +44,26 @@ __global__ __launch_bounds__(kBlock) void k_voronoi(const double *__restrict__ x
         hq[k] = 0ull;
     }
     __syncthreads();
-    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * kBlock) {
-        double xi = x[i], yi = y[i], zi = z[i];
-        int best = 0;
-        double bd = INFINITY;
-        for (int k = 0; k < K; ++k) {
-            double dx = xi - gs[3 * k], dy = yi - gs[3 * k + 1], dz = zi - gs[3 * k + 2];
-            double d2 = ((dx * dx) + (dy * dy)) + (dz * dz);
-            if (d2 < bd) {
-                bd = d2;
-                best = k;
-            }
+    const NearTiles mine = near_tiles(n);
+    for (int64_t tile = mine.at; tile < mine.end; ++tile) {
+        const int64_t i0 = tile * kNearTile + (threadIdx.x & 63);
+        LaneParticles<kNearPer> w;
+        int32_t c[kNearPer];
+        int best[kNearPer];
+#pragma unroll
+        for (int q = 0; q < kNearPer; ++q) {
+            const int64_t i = i0 + 64 * q;
+            w.on[q] = i < n;
+            w.p[q][0] = w.on[q] ? x[i] : 0.0;
+            w.p[q][1] = w.on[q] ? y[i] : 0.0;
+            w.p[q][2] = w.on[q] ? z[i] : 0.0;
+            c[q] = nbr_count && w.on[q] ? nbr_count[i] : 0;
         }
-        owner[i] = best;
-        atomicAdd(&hp[best], 1u);
-        if (nbr_count) atomicAdd(&hq[best], (unsigned long long)nbr_count[i]);
+        nearest_site<kNearPer>(gs, K, w, best);
+#pragma unroll
+        for (int q = 0; q < kNearPer; ++q)
+            if (w.on[q]) owner[i0 + 64 * q] = best[q];
+        count_owners<kNearPer>(w.on, best, nbr_count != nullptr, c, hp, hq);
     }
     __syncthreads();
     for (int k = threadIdx.x; k < K; k += kBlock) {
@@ -58,15 +75,9 @@ __global__ __launch_bounds__(kBlock) void k_voronoi(const double *__restrict__ x
 hipError_t launch_voronoi(const double *x, const double *y, const double *z, int64_t n,
                           const double *sites, int K, const int32_t *nbr_count, int32_t *owner,
                           int64_t *site_particles, int64_t *site_pairs, hipStream_t st) {
-    unsigned zb = (unsigned)((K + kBlock - 1) / kBlock);
-    k_zero_u64<<<zb, kBlock, 0, st>>>((unsigned long long *)site_particles, K);
-    if (site_pairs) k_zero_u64<<<zb, kBlock, 0, st>>>((unsigned long long *)site_pairs, K);
+    launch_zero2(site_particles, 2 * K, site_pairs, 2 * K, st);
     if (n > 0) {
-        int64_t want = (n + kBlock - 1) / kBlock;
-        // 4 096 workgroups (16 waves per CU): 0.33 ms on the porous shock, against 0.37 ms with
-        // 1 024; more add same-address count atomics without gaining occupancy
-        constexpr int64_t kVoronoiBlocks = 4096;
-        unsigned nb = (unsigned)(want > kVoronoiBlocks ? kVoronoiBlocks : want);
+        const unsigned nb = near_blocks(n, kReduceBlocks);
         size_t shm = (size_t)K * (3 * sizeof(double) + sizeof(unsigned long long) + sizeof(unsigned));
         k_voronoi<<<nb, kBlock, shm, st>>>(x, y, z, n, sites, K, site_pairs ? nbr_count : nullptr,
                                            owner, (unsigned long long *)site_particles,
