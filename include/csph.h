@@ -242,6 +242,16 @@ csph_status csph_neighbors(const csph_state *s, const csph_params *p, int64_t *o
                            int32_t *idx, int64_t idx_cap, int64_t *nnz /* host */, void *ws,
                            size_t ws_bytes, size_t *ws_needed, csph_stream stream);
 
+/* csph_neighbors in one call where the pair count is not known beforehand: once the rows are
+ * counted, alloc(nnz, ctx) is called on the calling thread (no exception may leave it) and
+ * returns the device memory of at least nnz int32 for them.  NULL (with nnz > 0) ends the call
+ * with CSPH_ECAPACITY, offsets and *nnz filled. */
+typedef int32_t *(*csph_idx_alloc)(int64_t nnz, void *ctx);
+csph_status csph_neighbors_alloc(const csph_state *s, const csph_params *p, int64_t *offsets,
+                                 csph_idx_alloc alloc, void *ctx, int64_t *nnz /* host */,
+                                 void *ws, size_t ws_bytes, size_t *ws_needed,
+                                 csph_stream stream);
+
 /* Rates of every particle at time t (t places the piston only), in the
  * input order: for each i and j in N(i), e = (r_j - r_i)/|r_j - r_i|,
  * v_L = v_i.e, v_R = v_j.e, acoustic Riemann solution

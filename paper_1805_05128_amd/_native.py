@@ -57,6 +57,10 @@ class CsphGrid(C.Structure):
                 ("key_mode", C.c_int32), ("pad", C.c_int32), ("nkey", C.c_int64)]
 
 
+# csph_idx_alloc: (nnz, ctx) -> device address
+IdxAlloc = C.CFUNCTYPE(C.c_void_p, C.c_int64, C.c_void_p)
+
+
 class CsphRatesOut(C.Structure):
     _fields_ = [(k, _dp) for k in ("drho", "dvx", "dvy", "dvz", "dE")]
 
@@ -123,6 +127,9 @@ def load():
     L.csph_neighbors.restype = C.c_int32
     L.csph_neighbors.argtypes = [C.POINTER(CsphState), C.POINTER(CsphParams), _lp, _ip,
                                  C.c_int64, _lp, vp, sz, szp, vp]
+    L.csph_neighbors_alloc.restype = C.c_int32
+    L.csph_neighbors_alloc.argtypes = [C.POINTER(CsphState), C.POINTER(CsphParams), _lp,
+                                       IdxAlloc, vp, _lp, vp, sz, szp, vp]
     L.csph_rates.restype = C.c_int32
     L.csph_rates.argtypes = [C.POINTER(CsphState), C.POINTER(CsphParams), C.c_double,
                              CsphRatesOut, _dp, _ip, _lp, vp, sz, szp, vp]

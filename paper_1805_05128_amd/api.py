@@ -284,13 +284,26 @@ def csph_neighbors(state: State, params: Params, ws: Optional[Workspace] = None,
     s = state.c()
     p = params.c()
     nnz = C.c_int64(0)
-    _with_ws(lambda w, b, nd: L.csph_neighbors(C.byref(s), C.byref(p), _lp(off), None, 0,
-                                               C.byref(nnz), w, b, nd, _stream(stream)), ws,
-             "csph_neighbors(count)")
-    idx = torch.empty(max(nnz.value, 1), dtype=torch.int32, device=state["x"].device)
-    _with_ws(lambda w, b, nd: L.csph_neighbors(C.byref(s), C.byref(p), _lp(off), _ip(idx),
-                                               idx.shape[0], C.byref(nnz), w, b, nd,
-                                               _stream(stream)), ws, "csph_neighbors")
+    dev, got = state["x"].device, []
+
+    @N.IdxAlloc
+    def alloc(count, ctx):  # the rows' memory, once they are counted
+        try:
+            got.append(torch.empty(max(count, 1), dtype=torch.int32, device=dev))
+            return got[-1].data_ptr()
+        except BaseException as e:  # raised below: it must not pass through the C call
+            got.append(e)
+            return None
+
+    try:
+        _with_ws(lambda w, b, nd: L.csph_neighbors_alloc(C.byref(s), C.byref(p), _lp(off), alloc,
+                                                         None, C.byref(nnz), w, b, nd,
+                                                         _stream(stream)), ws, "csph_neighbors")
+    except Exception:
+        if got and isinstance(got[-1], BaseException):
+            raise got[-1]
+        raise
+    idx = got[-1]
     return off, idx[:nnz.value]
 
 

@@ -667,6 +667,61 @@ static csph_status step_impl(const csph_state *s_in, csph_state *s_out, const cs
                              const VoroArgs *va = nullptr, const csph_grid *mesh = nullptr,
                              int64_t *outside = nullptr);
 
+// The neighbour export: the counts and offsets, then the rows into what idx_of gives for their
+// number (null: none wanted; *r set: refused).
+template <typename F>
+static csph_status neighbors_impl(const csph_state *s, const csph_params *p, int64_t *offsets,
+                                  int64_t *nnz, void *ws, size_t ws_bytes, size_t *ws_needed,
+                                  csph_stream stream, F &&idx_of) {
+    g_err[0] = 0;
+    if (!s || s->n < 0 || s->n >= INT32_MAX || !offsets || !nnz ||
+        (s->n > 0 && (!s->x || !s->y || !s->z)))
+        return fail(CSPH_EINVAL, "bad arguments");
+    csph_status r = check_params(p, s->n > 0, s->d);
+    if (r) return r;
+    hipStream_t st = (hipStream_t)stream;
+    int64_t n = s->n;
+    csph_grid g;
+    double dmax, ymin;
+    csph_params pn0 = *p;  // N(i) has no mirror partners: no wall
+    pn0.wall = 0;
+    p = &pn0;
+    // positions in the kernels' axes (N(i) does not depend on them)
+    const csph_state sv = kernel_view(*s, kernel_axes(p));
+    r = make_grid(sv.x, sv.y, sv.z, s->d, n, p, ws, ws_bytes, st, &g, &dmax, &ymin, true);
+    if (r) return r;
+    PairConst pc = pair_const(p, dmax);
+    // thirds of the cells where the workspace holds them; one too short for the mesh asked for
+    // is told the size that holds them
+    csph_grid fine = g;
+    if (refine_grid(&fine, n, pc.H) &&
+        (ws_bytes >= ws_layout(nullptr, nullptr, n, fine.ncell) ||
+         ws_bytes < ws_layout(nullptr, nullptr, n, g.ncell)))
+        g = fine;
+    r = need_ws(ws_bytes, n, g.ncell, ws_needed);
+    if (r) return r;
+    Ws w;
+    ws_layout(&w, ws, n, g.ncell);
+    GridDev gd = grid_dev(g, true, ymin);
+    const double *dd = p->h_mode == CSPH_H_PAIR ? s->d : nullptr;
+    ProfScope pn(CSPH_PROF_NEIGHBORS, st);
+    CSPH_HIP(launch_bin(sv.x, sv.y, sv.z, n, gd, w, w.perm, nullptr, w.cs, st));
+    CSPH_HIP(launch_gather_pos(n, w.perm, sv.x, sv.y, sv.z, dd, w, st));
+    CSPH_HIP(launch_nbr_count(n, gd, pc, w.srt[0], w.srt[1], w.srt[2], w.srt_d, w.cs, w.perm,
+                              w.cnt, st));
+    pn.stop();
+    CSPH_HIP((launch_scan_exclusive<int32_t, int64_t>(w.cnt, offsets, n, w.scan_tmp, st)));
+    unsigned long long total = 0;
+    r = word_to_host((const unsigned long long *)(offsets + n), &total, st);
+    if (r) return r;
+    *nnz = (int64_t)total;
+    int32_t *const idx = idx_of((int64_t)total, &r);
+    if (r || !idx) return r;
+    CSPH_HIP(launch_nbr_fill(n, gd, pc, w.srt[0], w.srt[1], w.srt[2], w.srt_d, w.cs, w.perm,
+                             offsets, idx, st));
+    return CSPH_OK;
+}
+
 }  // namespace csph
 
 using namespace csph;
@@ -743,54 +798,28 @@ csph_status csph_bin(const double *x, const double *y, const double *z, int64_t 
 csph_status csph_neighbors(const csph_state *s, const csph_params *p, int64_t *offsets,
                            int32_t *idx, int64_t idx_cap, int64_t *nnz, void *ws, size_t ws_bytes,
                            size_t *ws_needed, csph_stream stream) {
+    return neighbors_impl(s, p, offsets, nnz, ws, ws_bytes, ws_needed, stream,
+                          [&](int64_t total, csph_status *r) {
+                              if (idx && idx_cap < total)
+                                  *r = fail(CSPH_ECAPACITY, "idx needs %lld entries",
+                                            (long long)total);
+                              return idx;
+                          });
+}
+
+csph_status csph_neighbors_alloc(const csph_state *s, const csph_params *p, int64_t *offsets,
+                                 csph_idx_alloc alloc, void *ctx, int64_t *nnz, void *ws,
+                                 size_t ws_bytes, size_t *ws_needed, csph_stream stream) {
     g_err[0] = 0;
-    if (!s || s->n < 0 || s->n >= INT32_MAX || !offsets || !nnz ||
-        (s->n > 0 && (!s->x || !s->y || !s->z)))
-        return fail(CSPH_EINVAL, "bad arguments");
-    csph_status r = check_params(p, s->n > 0, s->d);
-    if (r) return r;
-    hipStream_t st = (hipStream_t)stream;
-    int64_t n = s->n;
-    csph_grid g;
-    double dmax, ymin;
-    csph_params pn0 = *p;  // N(i) has no mirror partners: no wall
-    pn0.wall = 0;
-    p = &pn0;
-    // positions in the kernels' axes (N(i) does not depend on them)
-    const csph_state sv = kernel_view(*s, kernel_axes(p));
-    r = make_grid(sv.x, sv.y, sv.z, s->d, n, p, ws, ws_bytes, st, &g, &dmax, &ymin, true);
-    if (r) return r;
-    PairConst pc = pair_const(p, dmax);
-    // thirds of the cells where the workspace holds them; one too short for the mesh asked for
-    // is told the size that holds them
-    csph_grid fine = g;
-    if (refine_grid(&fine, n, pc.H) &&
-        (ws_bytes >= ws_layout(nullptr, nullptr, n, fine.ncell) ||
-         ws_bytes < ws_layout(nullptr, nullptr, n, g.ncell)))
-        g = fine;
-    r = need_ws(ws_bytes, n, g.ncell, ws_needed);
-    if (r) return r;
-    Ws w;
-    ws_layout(&w, ws, n, g.ncell);
-    GridDev gd = grid_dev(g, true, ymin);
-    const double *dd = p->h_mode == CSPH_H_PAIR ? s->d : nullptr;
-    ProfScope pn(CSPH_PROF_NEIGHBORS, st);
-    CSPH_HIP(launch_bin(sv.x, sv.y, sv.z, n, gd, w, w.perm, nullptr, w.cs, st));
-    CSPH_HIP(launch_gather_pos(n, w.perm, sv.x, sv.y, sv.z, dd, w, st));
-    CSPH_HIP(launch_nbr_count(n, gd, pc, w.srt[0], w.srt[1], w.srt[2], w.srt_d, w.cs, w.perm,
-                              w.cnt, st));
-    pn.stop();
-    CSPH_HIP((launch_scan_exclusive<int32_t, int64_t>(w.cnt, offsets, n, w.scan_tmp, st)));
-    int64_t total = 0;
-    CSPH_HIP(hipMemcpyAsync(&total, offsets + n, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-    CSPH_HIP(hipStreamSynchronize(st));
-    *nnz = total;
-    if (!idx) return CSPH_OK;
-    if (idx_cap < total)
-        return fail(CSPH_ECAPACITY, "idx needs %lld entries", (long long)total);
-    CSPH_HIP(launch_nbr_fill(n, gd, pc, w.srt[0], w.srt[1], w.srt[2], w.srt_d, w.cs, w.perm,
-                             offsets, idx, st));
-    return CSPH_OK;
+    if (!alloc) return fail(CSPH_EINVAL, "alloc must not be NULL");
+    return neighbors_impl(s, p, offsets, nnz, ws, ws_bytes, ws_needed, stream,
+                          [&](int64_t total, csph_status *r) {
+                              int32_t *const idx = alloc(total, ctx);
+                              if (!idx && total > 0)
+                                  *r = fail(CSPH_ECAPACITY, "no memory for idx: %lld entries",
+                                            (long long)total);
+                              return idx;
+                          });
 }
 
 csph_status csph_rates(const csph_state *s, const csph_params *p, double t, csph_rates_out out,
