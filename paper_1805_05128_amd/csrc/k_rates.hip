@@ -757,54 +757,59 @@ struct Rates32 {
         const float ay0 = IMG && !GHOST ? amy : a.y;
         const int cy0 = IMG && !GHOST ? tm.cy : t.cy;
         const uint32_t tag = (GHOST ? 1u : 0u) | (IMG ? (uint32_t)im << 1 : 0u);
-        walk_rows(cs, g, st, on, [&](int oy, int yy, int oz, int j0, int len) {
+        walk_rows<true>(cs, g, st, on, [&](int oy, int yy, int oz, int j0, int len) {
             // i's offsets from the row's cell origin (rows counted from i's own cell)
             const float az = fmaf(-Df, (float)oz, az0);
             const float ay = fmaf(-Df, (float)(yy - cy0), ay0);
-            const bool centre = !GHOST && !IMG && oy == 0 && oz == 0;  // the row i lies in
-            const int jlast = len > 0 ? j0 + len - 1 : 0;
-            int k = 0;
-            do {
-                // the slots' records from j0 + k on, the start clamped to the row's last
-                // record: every load then reads a finite record (a lane with nothing left to
-                // pop reads the slot written last), up to kUS - 1 past the row, which the zero
-                // records the pack appends after the n records keep in bounds
-                const uint32_t jb = (uint32_t)min(j0 + k, jlast) * (uint32_t)sizeof(float4);
-                const float4 *Ab = (const float4 *)((const char *)A + jb);
-                const float *Db = PAIR ? (const float *)((const char *)d32 + (jb >> 2)) : nullptr;
-                float4 aj[kUS];
+            // pair-h walks have few, short rows, which the extra part of i's row would cost
+            // more than the comparisons (6.3 M particles: 1 658 against 1 648 us a step)
+            const bool cmp_self = PAIR && !GHOST && !IMG && oy == 0 && oz == 0;
+            around_self<!PAIR && !GHOST && !IMG>(oy, oz, self16, j0, len, [&](int j0, int len) {
+                const int jlast = len > 0 ? j0 + len - 1 : 0;
+                int k = 0;
+                do {
+                    // the slots' records from j0 + k on, the start clamped to the row's last
+                    // record: every load then reads a finite record (a lane with nothing left to
+                    // pop reads the slot written last), up to kUS - 1 past the row, which the zero
+                    // records the pack appends after the n records keep in bounds
+                    const uint32_t jb = (uint32_t)min(j0 + k, jlast) * (uint32_t)sizeof(float4);
+                    const float4 *Ab = (const float4 *)((const char *)A + jb);
+                    const float *Db =
+                        PAIR ? (const float *)((const char *)d32 + (jb >> 2)) : nullptr;
+                    float4 aj[kUS];
 #pragma unroll
-                for (int u = 0; u < kUS; ++u) aj[u] = Ab[u];
+                    for (int u = 0; u < kUS; ++u) aj[u] = Ab[u];
 #pragma unroll
-                for (int u = 0; u < kUS; ++u) {
-                    const float dx = fmaf(aj[u].w - cx0, Df, aj[u].x) - ax0;
-                    float dy = aj[u].y - ay;
-                    const float dz = aj[u].z - az;
-                    if (GHOST) dy = fmaf(2.0f, wd, -dy);
-                    const float r2 = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
-                    float hj = hi;
-                    if (PAIR) {
-                        const float Hj = fmaf(kd, Db[u], kdi);
-                        hj = Hj * Hj;
+                    for (int u = 0; u < kUS; ++u) {
+                        const float dx = fmaf(aj[u].w - cx0, Df, aj[u].x) - ax0;
+                        float dy = aj[u].y - ay;
+                        const float dz = aj[u].z - az;
+                        if (GHOST) dy = fmaf(2.0f, wd, -dy);
+                        const float r2 = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
+                        float hj = hi;
+                        if (PAIR) {
+                            const float Hj = fmaf(kd, Db[u], kdi);
+                            hj = Hj * Hj;
+                        }
+                        // the entry's record offset (16 j for a slot that can be accepted); one
+                        // select per slot: the tests combine as lane masks
+                        const uint32_t jo = jb + (uint32_t)(u * sizeof(float4));
+                        bool acc = (k + u < len) & (r2 < hj);
+                        if (cmp_self) acc = acc & (jo != self16);
+                        slot(qw) = make_float4(dx, dy, dz, __uint_as_float(jo | tag));
+                        qw += acc ? kSlot : 0;
                     }
-                    // the entry's record offset (16 j for a slot that can be accepted); one
-                    // select per slot: the tests combine as lane masks
-                    const uint32_t jo = jb + (uint32_t)(u * sizeof(float4));
-                    bool acc = (k + u < len) & (r2 < hj);
-                    if (centre) acc = acc & (jo != self16);
-                    slot(qw) = make_float4(dx, dy, dz, __uint_as_float(jo | tag));
-                    qw += acc ? kSlot : 0;
-                }
-                // two pops per trigger: some lane holds kQ - 1 entries, most lanes several
-                if (__any(qw - qr > (kQ - kUS) * kSlot)) {
-                    do {
-                        drain<MIR, ZS>();
-                        drain<MIR, ZS>();
-                        settle();
-                    } while (__any(qw - qr > (kQ - kUS) * kSlot));
-                }
-                k += kUS;
-            } while (__any(k < len));
+                    // two pops per trigger: some lane holds kQ - 1 entries, most lanes several
+                    if (__any(qw - qr > (kQ - kUS) * kSlot)) {
+                        do {
+                            drain<MIR, ZS>();
+                            drain<MIR, ZS>();
+                            settle();
+                        } while (__any(qw - qr > (kQ - kUS) * kSlot));
+                    }
+                    k += kUS;
+                } while (__any(k < len));
+            });
         });
     }
 

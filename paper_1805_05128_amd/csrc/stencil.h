@@ -205,10 +205,22 @@ __device__ __forceinline__ float plane_rem(const GridDev &g, const Stencil &t, b
     return on && (unsigned)zz < (unsigned)g.dz ? t.w2 - gz * gz : -1.0f;
 }
 
+// floor(v) as an integer.  ONE (here and in row_range): as one instruction, and so the chord's
+// half-width, for the FP32 kernel; the FP64 kernels, short of registers, spilled more with them
+// (51 k particles' step VJP 157 -> 162 us).
+template <bool ONE>
+__device__ __forceinline__ int floor_i(float v) {
+    if (!ONE) return (int)floorf(v);
+    int r;
+    asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(r) : "v"(v));
+    return r;
+}
+
 // Candidate range [j0, j0+len) of row (yy, zz), `key` its first cell's: the cells of the row
 // within the chord the support sphere cuts through it.  Branch-free per lane; a row off the
 // mesh or missing the sphere gets len = 0, and when it does so for every lane of the wave the
 // chord and the cell-range loads are skipped (and false returned).
+template <bool ONE = false>
 __device__ __forceinline__ bool row_range(const int32_t *__restrict__ cs, const GridDev &g,
                                           const Stencil &t, float rem_z, int oy, int yy,
                                           uint32_t key, int &j0, int &len) {
@@ -220,9 +232,10 @@ __device__ __forceinline__ bool row_range(const int32_t *__restrict__ cs, const 
     if (!__any(ok)) return false;
     // chord half-width; v_sqrt_f32 (1 ulp) is ample under the margins (a lane that is not ok may
     // take the root of a negative number: it is given an empty range below)
-    const float hw = __builtin_amdgcn_sqrtf(rem) * 1.0001f + 1e-3f;
-    const int xa = max(t.cx + (int)floorf(t.fx - hw), 0);
-    const int xb = min(t.cx + (int)floorf(t.fx + hw), g.dx - 1);
+    const float root = __builtin_amdgcn_sqrtf(rem);
+    const float hw = ONE ? fmaf(root, 1.0001f, 1e-3f) : root * 1.0001f + 1e-3f;
+    const int xa = max(t.cx + floor_i<ONE>(t.fx - hw), 0);
+    const int xb = min(t.cx + floor_i<ONE>(t.fx + hw), g.dx - 1);
     ok = ok && xb >= xa;
     // 64-bit addresses: a mesh may have 2e9 cells
     const uint32_t ia = ok ? key + (uint32_t)xa : 0u, ib = ok ? key + (uint32_t)xb + 1u : 0u;
@@ -251,7 +264,7 @@ constexpr int kRecPad = 2;
 // anew where some lane enters another slab, since its three 32-bit products issue at a
 // quarter of the rate; the z gap is squared once per plane, and a plane off every lane's mesh
 // or sphere is left out.
-template <typename F>
+template <bool ONE = false, typename F>
 __device__ __forceinline__ void walk_rows(const int32_t *__restrict__ cs, const GridDev &g,
                                           const Stencil &t, bool on, F &&row) {
     for (int oz = -t.R; oz <= t.R; ++oz) {
@@ -262,11 +275,35 @@ __device__ __forceinline__ void walk_rows(const int32_t *__restrict__ cs, const 
         uint32_t key = cell_key(g, 0, yy, zz);
         for (int oy = -t.R;;) {
             int j0, len;
-            if (row_range(cs, g, t, rem_z, oy, yy, key, j0, len)) row(oy, yy, oz, j0, len);
+            if (row_range<ONE>(cs, g, t, rem_z, oy, yy, key, j0, len)) row(oy, yy, oz, j0, len);
             if (++oy > t.R) break;
             ++yy;
             key = __any((yy & g.ymask) == 0) ? cell_key(g, 0, yy, zz) : key + (uint32_t)g.dx;
         }
+    }
+}
+
+// Calls part(j0, len) for a row's candidates, len <= 0 where a lane has none.  The row i itself
+// lies in (CENTRE: one row of the walk is it; self16 = 16 i) is taken in two parts, before and
+// after i, which spares every candidate of every row the comparison with i (3 of 51 vector
+// instructions per three candidates; with the one-instruction floor, 589 824 particles with
+// periodic sides 471 -> 466 us a step, 11.7 M 6 756 -> 6 732 us).
+template <bool CENTRE, typename F>
+__device__ __forceinline__ void around_self(int oy, int oz, uint32_t self16, int j0, int len,
+                                            F &&part) {
+    const bool centre = CENTRE && (oy | oz) == 0;
+    int after = 0;  // candidates after i
+    if (centre) {
+        const int self = (int)(self16 >> 4);
+        after = len > 0 ? j0 + len - self - 1 : 0;
+        len = len > 0 ? self - j0 : 0;
+        asm volatile("" : "+v"(after), "+v"(len));  // a branch, not selects in every row
+    }
+    for (bool again = centre;; again = false) {
+        part(j0, len);
+        if (!again) break;
+        len = after;
+        j0 = (int)(self16 >> 4) + 1;
     }
 }
 
