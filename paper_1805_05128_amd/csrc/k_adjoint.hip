@@ -580,18 +580,32 @@ __global__ __launch_bounds__(kBlock, WALL ? 2 : PER ? 3 : 4) void k_vjp64(int64_
 __global__ __launch_bounds__(kBlock) void k_eos_grad_final(const double *__restrict__ part,
                                                            int64_t nblocks, int nk,
                                                            double *__restrict__ g_eos) {
-    __shared__ double sh[kBlock];
-    for (int k = 0; k < nk; ++k) {
-        double acc = 0.0;
-        for (int64_t b = threadIdx.x; b < nblocks; b += kBlock) acc += part[b * 2 * CSPH_MAX_EOS + k];
-        sh[threadIdx.x] = acc;
-        __syncthreads();
-        for (int w = kBlock / 2; w > 0; w >>= 1) {
-            if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-            __syncthreads();
+    // a wave a sum: entry t of the tree adds the blocks t, t + kBlock, ..., then entries 128, 64,
+    // 32, .. 1 apart, the last six levels between the lanes
+    const int lane = threadIdx.x & 63;
+    for (int k = threadIdx.x >> 6; k < nk; k += kBlock / 64) {
+        double a[kBlock / 64];
+#pragma unroll
+        for (int q = 0; q < kBlock / 64; ++q) a[q] = 0.0;
+        constexpr int kAhead = 4;  // loads of an entry in flight
+        for (int64_t b0 = 0; b0 < nblocks; b0 += kAhead * kBlock) {
+            double v[kAhead][kBlock / 64];
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u)
+#pragma unroll
+                for (int q = 0; q < kBlock / 64; ++q) {
+                    const int64_t b = b0 + u * kBlock + 64 * q + lane;
+                    v[u][q] = part[(b < nblocks ? b : 0) * 2 * CSPH_MAX_EOS + k];
+                }
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u)
+#pragma unroll
+                for (int q = 0; q < kBlock / 64; ++q)
+                    if (b0 + u * kBlock + 64 * q + lane < nblocks) a[q] += v[u][q];
         }
-        if (threadIdx.x == 0) g_eos[k] += sh[0];
-        __syncthreads();
+        double s = (a[0] + a[2]) + (a[1] + a[3]);
+        for (int w = 32; w > 0; w >>= 1) s += __shfl_down(s, w, 64);
+        if (lane == 0) g_eos[k] += s;
     }
 }
 

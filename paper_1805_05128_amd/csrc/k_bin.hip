@@ -10,6 +10,7 @@
 // order by (key, input index) whatever order the atomics ran in.
 #include "csph_internal.h"
 #include "hostsync.h"
+#include "wave.h"
 
 namespace csph {
 
@@ -23,13 +24,48 @@ constexpr int kSmallN = kSmallPer * kSmallBlock;
 
 // ---------------------------------------------------------------- reductions
 
+// (a wave's reduction, every lane active: within rows of 16 lanes without LDS, whose six
+// dependent exchanges a value were most of a reduction's time)
 __device__ __forceinline__ double wave_min(double v) {
-    for (int o = 32; o > 0; o >>= 1) v = fmin(v, __shfl_xor(v, o, 64));
-    return v;
+    v = fmin(v, row_ror<8>(v));
+    v = fmin(v, row_ror<4>(v));
+    v = fmin(v, row_ror<2>(v));
+    v = fmin(v, row_ror<1>(v));
+    v = fmin(v, __shfl_xor(v, 16, 64));
+    return fmin(v, __shfl_xor(v, 32, 64));
 }
-__device__ __forceinline__ double wave_max(double v) {
-    for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
-    return v;
+__device__ __forceinline__ double wave_max(double v) { return -wave_min(-v); }
+
+// The bounds of the thread's particles i0, i0 + stride, ... below n, U of them in flight.
+template <int U>
+__device__ __forceinline__ void thread_bounds(const double *__restrict__ x,
+                                              const double *__restrict__ y,
+                                              const double *__restrict__ z,
+                                              const double *__restrict__ d, int64_t i0,
+                                              int64_t stride, int64_t n, double (&v)[7]) {
+    for (; i0 < n; i0 += U * stride) {
+        double a[U], b[U], c[U], e[U];
+#pragma unroll
+        for (int q = 0; q < U; ++q) {  // past the end: the thread's first particle again
+            const int64_t i = i0 + q * stride < n ? i0 + q * stride : i0;
+            a[q] = x[i];
+            b[q] = y[i];
+            c[q] = z[i];
+            e[q] = d ? d[i] : 0.0;
+        }
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            v[0] = fmin(v[0], a[q]); v[1] = fmin(v[1], b[q]); v[2] = fmin(v[2], c[q]);
+            v[3] = fmax(v[3], a[q]); v[4] = fmax(v[4], b[q]); v[5] = fmax(v[5], c[q]);
+            v[6] = fmax(v[6], e[q]);
+        }
+    }
+}
+
+// Workgroups of the bounds: four particles a thread, kReduceBlocks at most.
+static int bounds_blocks(int64_t n) {
+    const int64_t want = (n + 4 * kBlock - 1) / (4 * kBlock);
+    return (int)(want < 1 ? 1 : (want > kReduceBlocks ? kReduceBlocks : want));
 }
 
 // part[b*8 + {0..6}] = min x, min y, min z, max x, max y, max z, max d.
@@ -39,13 +75,8 @@ __global__ __launch_bounds__(kBlock) void k_bounds(const double *__restrict__ x,
                                                    const double *__restrict__ d, int64_t n,
                                                    double *__restrict__ part) {
     double v[7] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY, 0.0};
-    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * kBlock) {
-        double a = x[i], b = y[i], c = z[i];
-        v[0] = fmin(v[0], a); v[1] = fmin(v[1], b); v[2] = fmin(v[2], c);
-        v[3] = fmax(v[3], a); v[4] = fmax(v[4], b); v[5] = fmax(v[5], c);
-        if (d) v[6] = fmax(v[6], d[i]);
-    }
+    thread_bounds<4>(x, y, z, d, (int64_t)blockIdx.x * kBlock + threadIdx.x,
+                     (int64_t)gridDim.x * kBlock, n, v);
     __shared__ double sh[kBlock / 64][7];
     int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     for (int k = 0; k < 7; ++k) {
@@ -64,9 +95,13 @@ __global__ __launch_bounds__(kBlock) void k_bounds(const double *__restrict__ x,
 __global__ __launch_bounds__(kBlock) void k_bounds_final(const double *__restrict__ part,
                                                          int nblocks, double *__restrict__ out) {
     double v[7] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY, 0.0};
-    for (int b = threadIdx.x; b < nblocks; b += kBlock)
+#pragma unroll
+    for (int q = 0; q < kReduceBlocks / kBlock; ++q) {  // past the end: the first block again
+        const int b = (int)threadIdx.x + q * kBlock < nblocks ? (int)threadIdx.x + q * kBlock : 0;
+#pragma unroll
         for (int k = 0; k < 7; ++k)
             v[k] = k < 3 ? fmin(v[k], part[b * 8 + k]) : fmax(v[k], part[b * 8 + k]);
+    }
     __shared__ double sh[kBlock / 64][7];
     int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     for (int k = 0; k < 7; ++k) {
@@ -114,9 +149,13 @@ __global__ __launch_bounds__(kBlock) void k_bounds_final_host(const double *__re
                                                               HostBounds *hb,
                                                               unsigned long long seq) {
     double v[7] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY, 0.0};
-    for (int b = threadIdx.x; b < nblocks; b += kBlock)
+#pragma unroll
+    for (int q = 0; q < kReduceBlocks / kBlock; ++q) {  // past the end: the first block again
+        const int b = (int)threadIdx.x + q * kBlock < nblocks ? (int)threadIdx.x + q * kBlock : 0;
+#pragma unroll
         for (int k = 0; k < 7; ++k)
             v[k] = k < 3 ? fmin(v[k], part[b * 8 + k]) : fmax(v[k], part[b * 8 + k]);
+    }
     bounds_to_host<kBlock / 64>(v, out, hb, seq);
 }
 
@@ -129,23 +168,7 @@ __global__ __launch_bounds__(kSmallBlock) void k_bounds_small(const double *__re
                                                               HostBounds *hb,
                                                               unsigned long long seq) {
     double v[7] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY, 0.0};
-    for (int i0 = threadIdx.x; i0 < n; i0 += 4 * kSmallBlock) {
-        double a[4], b[4], c[4], e[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {  // past the end: the thread's first particle again
-            const int i = i0 + q * kSmallBlock < n ? i0 + q * kSmallBlock : i0;
-            a[q] = x[i];
-            b[q] = y[i];
-            c[q] = z[i];
-            e[q] = d ? d[i] : 0.0;
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            v[0] = fmin(v[0], a[q]); v[1] = fmin(v[1], b[q]); v[2] = fmin(v[2], c[q]);
-            v[3] = fmax(v[3], a[q]); v[4] = fmax(v[4], b[q]); v[5] = fmax(v[5], c[q]);
-            v[6] = fmax(v[6], e[q]);
-        }
-    }
+    thread_bounds<8>(x, y, z, d, threadIdx.x, kSmallBlock, n, v);
     bounds_to_host<kSmallBlock / 64>(v, out, hb, seq);
 }
 
@@ -156,8 +179,7 @@ hipError_t launch_bounds_host(const double *x, const double *y, const double *z,
         k_bounds_small<<<1, kSmallBlock, 0, st>>>(x, y, z, d, (int)n, out, hb, seq);
         return hipGetLastError();
     }
-    int64_t want = (n + kBlock - 1) / kBlock;
-    int nb = (int)(want < 1 ? 1 : (want > kReduceBlocks ? kReduceBlocks : want));
+    const int nb = bounds_blocks(n);
     k_bounds<<<nb, kBlock, 0, st>>>(x, y, z, d, n, part);
     k_bounds_final_host<<<1, kBlock, 0, st>>>(part, nb, out, hb, seq);
     return hipGetLastError();
@@ -180,8 +202,7 @@ hipError_t launch_word_host(const unsigned long long *src, unsigned long long *s
 
 hipError_t launch_bounds(const double *x, const double *y, const double *z, const double *d,
                          int64_t n, double *part, double *out, hipStream_t st) {
-    int64_t want = (n + kBlock - 1) / kBlock;
-    int nb = (int)(want < 1 ? 1 : (want > kReduceBlocks ? kReduceBlocks : want));
+    const int nb = bounds_blocks(n);
     k_bounds<<<nb, kBlock, 0, st>>>(x, y, z, d, n, part);
     k_bounds_final<<<1, kBlock, 0, st>>>(part, nb, out);
     return hipGetLastError();
@@ -432,12 +453,14 @@ __global__ __launch_bounds__(kSmallBlock) void k_bin_small(
     const double *__restrict__ x, const double *__restrict__ y, const double *__restrict__ z,
     int n, GridDev g, int nkey, int32_t *__restrict__ perm, uint32_t *__restrict__ key_out,
     int32_t *__restrict__ cs, ClearWords w) {
-    __shared__ uint32_t hist[kSmallKeys / 2];  // counts, then cell starts, as 16-bit halves
+    // counts, then cell starts, as 16-bit halves
+    __shared__ __align__(16) uint32_t hist[kSmallKeys / 2];
     __shared__ uint16_t seg[kSmallN];          // particles by cell, in atomic order
     __shared__ int lds[kSmallBlock / 64 + 1];
     uint16_t *const start = (uint16_t *)hist;
     const int tid = threadIdx.x;
-    for (int k = tid; k < kSmallKeys / 2; k += kSmallBlock) hist[k] = 0u;
+    for (int k = tid; k < kSmallKeys / 8; k += kSmallBlock)
+        ((uint4 *)hist)[k] = make_uint4(0u, 0u, 0u, 0u);
     if (tid < w.n) *w.p[tid] = w.v[tid];
     __syncthreads();
     uint32_t key[kSmallPer];
@@ -470,13 +493,13 @@ __global__ __launch_bounds__(kSmallBlock) void k_bin_small(
     }
     __syncthreads();
     // exclusive scan: each thread's run of 16 keys, then the workgroup's
-    const int k0 = tid * (kSmallKeys / kSmallBlock);
-    int c[kSmallKeys / kSmallBlock], sum = 0;
+    static_assert(kSmallKeys == 16 * kSmallBlock, "16 keys a thread, eight to a vector");
+    uint4 *const own = (uint4 *)hist + 2 * tid;
+    const uint4 c0 = own[0], c1 = own[1];
+    uint32_t c[8] = {c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w};
+    int sum = 0;
 #pragma unroll
-    for (int k = 0; k < kSmallKeys / kSmallBlock; ++k) {
-        c[k] = start[k0 + k];
-        sum += c[k];
-    }
+    for (int k = 0; k < 8; ++k) sum += (int)(c[k] & 0xffffu) + (int)(c[k] >> 16);
     int inc = sum;
     for (int o = 1; o < 64; o <<= 1) {
         const int v = __shfl_up(inc, o, 64);
@@ -487,13 +510,18 @@ __global__ __launch_bounds__(kSmallBlock) void k_bin_small(
     int run = inc - sum;
     for (int q = 0; q < (tid >> 6); ++q) run += lds[q];
 #pragma unroll
-    for (int k = 0; k < kSmallKeys / kSmallBlock; ++k) {
-        start[k0 + k] = (uint16_t)run;  // the thread's own keys only; n <= 16 384
-        if (k0 + k <= nkey) cs[k0 + k] = run;
-        run += c[k];
+    for (int k = 0; k < 8; ++k) {  // the thread's own keys; starts below n <= 16 384
+        const uint32_t first = (uint32_t)run;
+        run += (int)(c[k] & 0xffffu);
+        const uint32_t second = (uint32_t)run;
+        run += (int)(c[k] >> 16);
+        c[k] = first | second << 16;
     }
-    if (tid == 0) cs[nkey] = n;
+    own[0] = make_uint4(c[0], c[1], c[2], c[3]);
+    own[1] = make_uint4(c[4], c[5], c[6], c[7]);
     __syncthreads();
+    for (int k = tid; k < nkey; k += kSmallBlock) cs[k] = start[k];
+    if (tid == 0) cs[nkey] = n;
 #pragma unroll
     for (int q = 0; q < kSmallPer; ++q) {
         const int i = q * kSmallBlock + tid;

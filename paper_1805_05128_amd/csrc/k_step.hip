@@ -92,31 +92,37 @@ __device__ __forceinline__ double wrap_axis(const PerDev &p, int a, double v) {
     return v;
 }
 
-// The workgroup's double-double sums (m, m vx, m vy, m vz, m E) reduced in a fixed tree into
-// part[block * 10 ..] as (hi, lo) pairs; ends with a barrier.
-__device__ __forceinline__ void block_totals(const DD acc[5], double *__restrict__ part) {
+// The workgroup's five double-double sums in a fixed tree (pairs 128, 64, 32, .. 1 apart):
+// wave k % 4 adds up sum k, the last six levels between its lanes, so that one barrier replaces
+// eight; out(k, sum) in lane 0 of that wave.  Every thread's values are in LDS, and what it did
+// before is seen by the workgroup, once the barrier is passed.
+template <typename F>
+__device__ __forceinline__ void block_dd_sums(const DD acc[5], F &&out) {
     __shared__ double sh[2][5][kBlock];
     for (int k = 0; k < 5; ++k) {
         sh[0][k][threadIdx.x] = acc[k].hi;
         sh[1][k][threadIdx.x] = acc[k].lo;
     }
     __syncthreads();
-    for (int w = kBlock / 2; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) {
-            for (int k = 0; k < 5; ++k) {
-                DD a{sh[0][k][threadIdx.x], sh[1][k][threadIdx.x]};
-                DD b{sh[0][k][threadIdx.x + w], sh[1][k][threadIdx.x + w]};
-                DD c = dd_add(a, b);
-                sh[0][k][threadIdx.x] = c.hi;
-                sh[1][k][threadIdx.x] = c.lo;
-            }
-        }
-        __syncthreads();
+    static_assert(kBlock == 256, "four entries a lane");
+    const int lane = threadIdx.x & 63;
+    for (int k = threadIdx.x >> 6; k < 5; k += kBlock / 64) {
+        DD a[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) a[q] = DD{sh[0][k][64 * q + lane], sh[1][k][64 * q + lane]};
+        DD s = dd_add(dd_add(a[0], a[2]), dd_add(a[1], a[3]));
+        for (int w = 32; w > 0; w >>= 1)
+            s = dd_add(s, DD{__shfl_down(s.hi, w, 64), __shfl_down(s.lo, w, 64)});
+        if (lane == 0) out(k, s);
     }
-    if (threadIdx.x < 5) {
-        part[blockIdx.x * 10 + 2 * threadIdx.x] = sh[0][threadIdx.x][0];
-        part[blockIdx.x * 10 + 2 * threadIdx.x + 1] = sh[1][threadIdx.x][0];
-    }
+}
+
+// The sums (m, m vx, m vy, m vz, m E) into part[block * 10 ..] as (hi, lo) pairs.
+__device__ __forceinline__ void block_totals(const DD acc[5], double *__restrict__ part) {
+    block_dd_sums(acc, [&](int k, const DD &s) {
+        part[blockIdx.x * 10 + 2 * k] = s.hi;
+        part[blockIdx.x * 10 + 2 * k + 1] = s.lo;
+    });
 }
 
 // The piston's reflection of a new position (normal axis y in the kernels' axes) in the
@@ -426,35 +432,28 @@ __global__ __launch_bounds__(kBlock) void k_finish(const double *__restrict__ pa
                                                    double dt_in, double *t, double *dt_used,
                                                    double *totals, Ax3 ax, ListGate lg) {
     if (lg.gate && *lg.gate == 0) return;
-    __shared__ double sh[2][5][kBlock];
     DD acc[5];
     for (int k = 0; k < 5; ++k) acc[k] = DD{0.0, 0.0};
-    for (int b = threadIdx.x; b < nblocks; b += kBlock)
-        for (int k = 0; k < 5; ++k) acc[k] = dd_add(acc[k], DD{part[b * 10 + 2 * k], part[b * 10 + 2 * k + 1]});
-    for (int k = 0; k < 5; ++k) {
-        sh[0][k][threadIdx.x] = acc[k].hi;
-        sh[1][k][threadIdx.x] = acc[k].lo;
+    // every partial sum asked for before the first is added
+    DD in[kReduceBlocks / kBlock][5];
+#pragma unroll
+    for (int q = 0; q < kReduceBlocks / kBlock; ++q) {
+        const int b = (int)threadIdx.x + q * kBlock < nblocks ? (int)threadIdx.x + q * kBlock : 0;
+#pragma unroll
+        for (int k = 0; k < 5; ++k) in[q][k] = DD{part[b * 10 + 2 * k], part[b * 10 + 2 * k + 1]};
     }
-    __syncthreads();
-    for (int w = kBlock / 2; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) {
-            for (int k = 0; k < 5; ++k) {
-                DD a{sh[0][k][threadIdx.x], sh[1][k][threadIdx.x]};
-                DD bb{sh[0][k][threadIdx.x + w], sh[1][k][threadIdx.x + w]};
-                DD c = dd_add(a, bb);
-                sh[0][k][threadIdx.x] = c.hi;
-                sh[1][k][threadIdx.x] = c.lo;
-            }
-        }
-        __syncthreads();
-    }
-    if (threadIdx.x < 5 && totals) {
-        // sums k = 1, 2, 3 are the momenta along the state's x, y, z arrays, which are the
-        // caller's axes ax.k[0], ax.k[1], ax.k[2]
-        const int k = threadIdx.x, o = (k >= 1 && k <= 3) ? 1 + ax.k[k - 1] : k;
-        totals[2 * o] = sh[0][k][0];
-        totals[2 * o + 1] = sh[1][k][0];
-    }
+#pragma unroll
+    for (int q = 0; q < kReduceBlocks / kBlock; ++q)
+        if ((int)threadIdx.x + q * kBlock < nblocks)
+            for (int k = 0; k < 5; ++k) acc[k] = dd_add(acc[k], in[q][k]);
+    if (totals)
+        block_dd_sums(acc, [&](int k, const DD &s) {
+            // sums k = 1, 2, 3 are the momenta along the state's x, y, z arrays, which are the
+            // caller's axes ax.k[0], ax.k[1], ax.k[2]
+            const int o = (k >= 1 && k <= 3) ? 1 + ax.k[k - 1] : k;
+            totals[2 * o] = s.hi;
+            totals[2 * o + 1] = s.lo;
+        });
     if (threadIdx.x == 0) {
         double dt = step_dt(dtmin, cfl, dt_in);
         if (dt_used) *dt_used = dt;

@@ -11,6 +11,7 @@
 #pragma once
 
 #include "csph_internal.h"
+#include "wave.h"
 
 namespace csph {
 
@@ -22,11 +23,6 @@ constexpr int kNearMin = 12;
 // cell row's worth and its neighbours).
 constexpr int kNearPer = 4;
 constexpr int kNearTile = 64 * kNearPer;
-
-template <int N>
-__device__ __forceinline__ int row_ror(int v) {  // from the lane N places on, in its 16 lanes
-    return __builtin_amdgcn_mov_dpp(v, 0x120 + N, 0xf, 0xf, true);
-}
 
 // Minimum of a wave's 64 integers (every lane active); the result is wave-uniform.
 __device__ __forceinline__ int wave_all_min(int v) {
