@@ -254,6 +254,8 @@ struct VjpWalk {
     VjpAcc acc, accm;  // accm: the pairs (j, image of i), in the image's q
     int qw = 0, qr = 0;
     int sub = 0, ls = 0;  // SPLIT: the lane's share of i, log2 of the lanes per particle
+    int2 *lay;            // few_images: the wave's layout
+    int list = 0;         // few_images: byte offset of the lane's list
 
     __device__ __forceinline__ uint32_t &slot(int q) {
         return *(uint32_t *)(qb + (((q & (kQ - 1)) * (kBlock * 4)) | lane4));
@@ -261,10 +263,13 @@ struct VjpWalk {
 
     // every lane pops its next partner, if it has one, and decides its membership exactly
     // ((sx, sy, sz): the walk's periodic shift k L, 0 off the periodic walks)
-    template <bool GHOST, bool ZS>
-    __device__ __forceinline__ void drain(double sx, double sy, double sz) {
+    // (LISTED: from the list few_images made, entry 0 at counter q0)
+    template <bool GHOST, bool ZS, bool LISTED = false>
+    __device__ __forceinline__ void drain(double sx, double sy, double sz, int q0 = 0) {
         const bool has = qr < qw;
-        const uint32_t jo = has ? slot(qr) : 0u;
+        const uint32_t e = LISTED ? *(const uint32_t *)(qb + list + (has ? qr - q0 : 0) * 4)
+                                  : slot(qr);
+        const uint32_t jo = has ? e : 0u;
         qr += has ? 1 : 0;
         const double4 aj = in.A.at(jo), bj = in.B.at(jo), dj = in.Dw.at(jo);
         const double2 zj = *(const double2 *)((const char *)in.C + jo);
@@ -374,13 +379,49 @@ struct VjpWalk {
         asm volatile("" : "+v"(qr));
     }
 
+    // The walk around a periodic image that few of the wave's lanes have (mask who), stencil st,
+    // the image's record in am: see few_candidates.  False, with nothing popped, when its room is
+    // too short.  207 360 particles, two axes periodic: 472 -> 448 us a step VJP.
+    template <bool GHOST, bool ZS>
+    __device__ __forceinline__ bool few_images(const Stencil &st, unsigned long long who, int cy0,
+                                               double sx, double sy, double sz) {
+        const int lane = (lane4 >> 2) & 63;
+        // the wave's part of ring row k is the list of its k-th such particle
+        int found = 0, first = lane4 & ~255;
+        for (; who; who &= who - 1, first += kBlock * 4) {
+            const int l = __ffsll(who) - 1;
+            const FewCentre c{lane_of(st, l), lane_of(am.x, l), lane_of(am.y, l),
+                              lane_of(am.z, l), lane_of(am.w, l), GHOST ? lane_of(wd, l) : 0.f,
+                              PAIR ? lane_of(kdi, l) : 0.f, lane_of(cy0, l)};
+            const int cnt = few_candidates<PAIR, GHOST, false>(
+                cs, g, in.F, in.d32, c, Df, hi32, kd, lay, lane,
+                [&](int at, uint32_t jb, float, float, float) {
+                    *(uint32_t *)(qb + first + at * 4) = jb;
+                });
+            if (cnt < 0) return false;
+            if (lane == l) {
+                found = cnt;
+                list = first;
+            }
+        }
+        wave_fence();
+        const int q0 = qr;  // the rings are empty
+        qw += found;
+        while (__any(qr < qw)) {
+            drain<GHOST, ZS, true>(sx, sy, sz, q0);
+            settle<GHOST>();
+        }
+        return true;
+    }
+
     // the walks around the periodic images of point (x_i, py, z_i) (i, or its mirror image) for
     // the lanes in `on`, stencil base st
     template <bool GHOST, bool ZS>
     __device__ __forceinline__ void images(const Stencil &base, bool on, double py, int cy0) {
         for (int m = 1; m < 8; ++m) {
             const bool onm = on && (nf & m) == m;
-            if (!__any(onm)) continue;
+            const unsigned long long who = __ballot(onm);
+            if (!who) continue;
             const double sx = image_shift(pc, nf, m, 0), sy = image_shift(pc, nf, m, 1),
                          sz = image_shift(pc, nf, m, 2);
             const double px = ai.x + sx, pz = ai.z + sz;
@@ -389,7 +430,10 @@ struct VjpWalk {
             am.y = m & 2 && !GHOST ? (float)(py + sy - (g.oy + (double)sm.cy * g.cell)) : a32.y;
             am.z = m & 4 ? (float)(pz - (g.oz + (double)sm.cz * g.cell)) : a32.z;
             am.w = (float)sm.cx;
-            walk<GHOST, true, ZS>(sm, onm, GHOST ? cy0 : sm.cy, sx, sy, sz);
+            const int cyi = GHOST ? cy0 : sm.cy;
+            if (!SPLIT && __popcll(who) <= kFew && few_images<GHOST, ZS>(sm, who, cyi, sx, sy, sz))
+                continue;
+            walk<GHOST, true, ZS>(sm, onm, cyi, sx, sy, sz);
         }
         am = a32;
     }
@@ -417,7 +461,9 @@ __global__ __launch_bounds__(kBlock, WALL ? 2 : PER ? 3 : 4) void k_vjp64(int64_
                                                   const int32_t *__restrict__ cs, GridDev g,
                                                   PairConst pc, EosDev eos, int n_eos,
                                                   VjpWall wl, int ls) {
+    static_assert(kFew == kQ && kFewList == 64, "the lists take the place of a wave's rings");
     __shared__ int qj[kQ][kBlock];
+    __shared__ int2 lay[PER && !SPLIT ? kBlock / 64 : 1][PER && !SPLIT ? kLay : 1];
     const int tid = threadIdx.x;
     const int64_t blk = xcd_block_upto(blockIdx.x, gridDim.x, 256);  // as the FP64 rate kernel
     int64_t s = blk * kBlock + tid;
@@ -436,6 +482,7 @@ __global__ __launch_bounds__(kBlock, WALL ? 2 : PER ? 3 : 4) void k_vjp64(int64_
     k.pc = pc;
     k.wl = wl;
     k.qb = (char *)&qj[0][0];
+    k.lay = lay[PER && !SPLIT ? tid >> 6 : 0];
     k.lane4 = tid * (int)sizeof(int);
     k.self16 = (uint32_t)s * 16u;
     k.live = live;

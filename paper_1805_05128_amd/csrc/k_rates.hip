@@ -276,16 +276,20 @@ struct Rates64 {
     // a mirror image, bits 1-3 the periodic image mask.  cnt: the exact members popped, |N(i)|
     int qw = 0, qr = 0, cnt = 0;
     int sub = 0, ls = 0;  // SPLIT: the lane's share of i, log2 of the lanes per particle
+    int2 *lay;            // few_images: the wave's layout
+    int list = 0;         // few_images: byte offset of the lane's list
 
     __device__ __forceinline__ uint32_t &slot(int q) {
         return *(uint32_t *)(qb + (((q & (kQ - 1)) * kSlot64) | lane4));
     }
 
     // every lane pops its next partner, if it has one; MIR: the wave may hold mirror entries
-    template <bool MIR, bool ZS>
-    __device__ __forceinline__ void drain() {
+    // (LISTED: from the list few_images made, entry 0 at counter q0)
+    template <bool MIR, bool ZS, bool LISTED = false>
+    __device__ __forceinline__ void drain(int q0 = 0) {
         const bool has = qr < qw;
-        const uint32_t e = slot(qr);
+        const uint32_t e = LISTED ? *(const uint32_t *)(qb + list + (has ? qr - q0 : 0) * 4)
+                                  : slot(qr);
         qr += has ? 1 : 0;
         const uint32_t jo = has ? (MIR ? e & ~15u : e) : 0u;
         const bool ghost = MIR && (e & 1u);
@@ -393,12 +397,51 @@ struct Rates64 {
             walk_rows(cs, g, st, on, row);
     }
 
+    // The walk around image im where few of the wave's lanes have it (mask who): see
+    // few_candidates.  False, with nothing popped, when its room is too short.  Without a wall
+    // only: its kernels spilled more and lost 1.5 % (FP32: 0.6 %).  327 680 particles, two axes
+    // periodic: 454 -> 427 us a step.
+    template <bool ZS>
+    __device__ __forceinline__ bool few_images(unsigned long long who) {
+        while (__any(qr < qw)) drain<true, ZS>();
+        const int lane = (lane4 >> 2) & 63;
+        const uint32_t tag = (uint32_t)im << 1;
+        // the wave's part of ring row k is the list of its k-th such particle
+        int found = 0, first = lane4 & ~255;
+        for (; who; who &= who - 1, first += kSlot64) {
+            const int l = __ffsll(who) - 1;
+            FewCentre c{lane_of(tm, l), lane_of(amx, l), lane_of(amy, l), lane_of(amz, l),
+                        lane_of(cxm, l), 0.f, PAIR ? lane_of(kdi, l) : 0.f, 0};
+            c.cy0 = c.st.cy;
+            const int cnt = few_candidates<PAIR, false, false>(
+                cs, g, F, d32, c, Df, hi32, kd, lay, lane,
+                [&](int at, uint32_t jb, float, float, float) {
+                    *(uint32_t *)(qb + first + at * 4) = jb | tag;
+                });
+            if (cnt < 0) return false;
+            if (lane == l) {
+                found = cnt;
+                list = first;
+            }
+        }
+        wave_fence();
+        const int q0 = qr;  // the rings are empty
+        qw += found;
+        while (__any(qr < qw)) {
+            drain<true, ZS, true>(q0);
+            settle();
+        }
+        return true;
+    }
+
     // the walks around every periodic image some lane of the wave has (GHOST: around the
     // images of its mirror image)
     template <bool GHOST, bool ZS>
     __device__ __forceinline__ void images() {
         for (int m = 1; m < 8; ++m) {
-            if (!__any(live && (!GHOST || near_wall) && (nf & m) == m)) continue;
+            const unsigned long long who =
+                __ballot(live && (!GHOST || near_wall) && (nf & m) == m);
+            if (!who) continue;
             im = m;
             const double px = a.x + image_shift(pc, nf, m, 0);
             const double py = (GHOST ? 2.0 * yw - a.y : a.y) + image_shift(pc, nf, m, 1);
@@ -408,6 +451,7 @@ struct Rates64 {
             amy = m & 2 ? (float)(py - (g.oy + (double)tm.cy * g.cell)) : a32.y;
             amz = m & 4 ? (float)(pz - (g.oz + (double)tm.cz * g.cell)) : a32.z;
             cxm = (float)tm.cx;
+            if (!SPLIT && !WALL && __popcll(who) <= kFew && few_images<ZS>(who)) continue;
             pass<GHOST, true, ZS, true>();
         }
     }
@@ -486,9 +530,13 @@ __global__ __launch_bounds__(kRate64Block, 4) void k_rates64(int64_t n, Split4 A
                                                     double t_host, RateOut o, int want_dt,
                                                     VList vl, int ls) {
     if (LIST && vl.gate && *vl.gate == 0) return;
+    static_assert(kFew == kQ && kFewList == 64, "the lists take the place of a wave's rings");
     __shared__ int qj[kQ][kRate64Block];
+    constexpr bool few = PER && !SPLIT && !WALL;
+    __shared__ int2 lay[few ? kRate64Block / 64 : 1][few ? kLay : 1];
     Rates64<PAIR, WALL, PER, SPLIT> k;
     k.qb = (char *)&qj[0][0];
+    k.lay = lay[few ? threadIdx.x >> 6 : 0];
     k.d32 = d32;
     k.lane4 = threadIdx.x * (int)sizeof(int);
     k.A = A;
@@ -639,11 +687,7 @@ __device__ __forceinline__ bool member64(double ex, double ey, double ez, double
     return ((ex * ex) + (ey * ey)) + (ez * ez) < H2;
 }
 
-// few_images: the lanes' lists take the rings' place, the layout 1 KB beside them (17 waves' LDS
-// fit a CU, its registers 16).
-constexpr int kFew = 8;        // particles whose images are walked by the whole wave
-constexpr int kFewList = kRing / (kFew * (int)sizeof(float4));  // 64 partners each
-constexpr int kLay = 128;      // candidates
+static_assert(kFew * kFewList * (int)sizeof(float4) == kRing, "the lists take the rings' place");
 
 template <bool PAIR, bool WALL, bool LIST, bool PER>
 struct Rates32 {
@@ -837,93 +881,27 @@ struct Rates32 {
         cxm = (float)tm.cx;
     }
 
-    // The walk around image im where few of the wave's lanes have it (mask who, kFew at most): a
-    // row of cells along a periodic axis holds a few particles near each end, and the ~45
-    // stencil rows walked in lock step for those lanes alone took a quarter of the wave's time.
-    // For each of those particles the lanes take a row each, lay the rows' candidates end to end
-    // and test one each; the accepted ones are listed in the order of the rows, the one in which
-    // the lock-step walk queues them, and popped by the particle's own lane: the sums keep their
-    // bits.  False, with nothing popped, when the candidates are too many for the layout.
+    // The walk around image im where few of the wave's lanes have it (mask who): see
+    // few_candidates.  False, with nothing popped, when its room is too short.
     // 589 824 particles, two axes periodic, mixed: 458 -> 400 us a step.
-    template <bool GHOST, bool ZS>
+    template <bool ZS>
     __device__ __forceinline__ bool few_images(unsigned long long who) {
         while (__any(qr != qw)) drain<true, ZS>();
         const int lane = lane16 >> 4;
-        const unsigned long long below = (1ull << lane) - 1ull;
-        const uint32_t tag = (GHOST ? 1u : 0u) | (uint32_t)im << 1;
-        const int W = 2 * t.R + 1;
-        const float iw = 1.0f / (float)W;
+        const uint32_t tag = (uint32_t)im << 1;
         int found = 0, first = 0;  // the lane's partners; the list's byte offset
-        auto of = [](int v, int l) { return __builtin_amdgcn_readlane(v, l); };
-        auto off = [](float v, int l) {
-            return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
-        };
         for (; who; who &= who - 1, first += kFewList * (int)sizeof(float4)) {
             const int l = __ffsll(who) - 1;
-            Stencil st = tm;
-            st.cx = of(tm.cx, l);
-            st.cy = of(tm.cy, l);
-            st.cz = of(tm.cz, l);
-            st.fx = off(tm.fx, l);
-            st.fy = off(tm.fy, l);
-            st.fz = off(tm.fz, l);
-            const float ax0 = off(amx, l), az0 = off(amz, l), cx0 = off(cxm, l);
-            const float ay0 = off(GHOST ? a.y : amy, l), wl = GHOST ? off(wd, l) : 0.f;
-            const float kl = PAIR ? off(kdi, l) : 0.f;
-            const int cy0 = GHOST ? of(t.cy, l) : st.cy;
-            int total = 0;
-            wave_fence();  // the layout is read before it is written again
-            for (int q0 = 0; q0 < W * W; q0 += 64) {
-                const int q = q0 + lane;
-                const int iz = (int)(((float)q + 0.5f) * iw);  // q / W (as walk_rows_split)
-                const int oz = iz - st.R, oy = q - iz * W - st.R;
-                const int yy = st.cy + oy, zz = st.cz + oz;
-                int j0, len;
-                if (!row_range<true>(cs, g, st, plane_rem(g, st, q < W * W, oz, zz), oy, yy,
-                                     cell_key(g, 0, yy, zz), j0, len))
-                    continue;
-                int end = max(len, 0);  // candidates of the rows up to the lane's
-                len = end;
-                for (int o = 1; o < 64; o <<= 1) {
-                    const int p = __shfl_up(end, o, 64);
-                    if (lane >= o) end += p;
-                }
-                const int all = __builtin_amdgcn_readlane(end, 63);
-                if (total + all > kLay) return false;
-                for (int k = 0; __any(k < len); ++k)
-                    if (k < len) lay[total + end - len + k] = make_int2(j0 + k, q);
-                total += all;
-            }
-            wave_fence();
-            int cnt = 0;
-            for (int c0 = 0; c0 < total; c0 += 64) {
-                const bool there = c0 + lane < total;
-                const int2 e = lay[there ? c0 + lane : 0];
-                const int iz = (int)(((float)e.y + 0.5f) * iw);
-                const int oz = iz - st.R, oy = e.y - iz * W - st.R;
-                const uint32_t jb = (uint32_t)e.x * (uint32_t)sizeof(float4);
-                const float4 aj = *(const float4 *)((const char *)A + jb);
-                const float az = fmaf(-Df, (float)oz, az0);
-                const float ay = fmaf(-Df, (float)(st.cy + oy - cy0), ay0);
-                const float dx = fmaf(aj.w - cx0, Df, aj.x) - ax0;
-                float dy = aj.y - ay;
-                const float dz = aj.z - az;
-                if (GHOST) dy = fmaf(2.0f, wl, -dy);
-                const float r2 = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
-                float hj = hi;
-                if (PAIR) {
-                    const float Hj = fmaf(kd, d32[e.x], kl);
-                    hj = Hj * Hj;
-                }
-                const bool acc = there & (r2 < hj);
-                const unsigned long long hit = __ballot(acc);
-                const int at = cnt + __popcll(hit & below);
-                cnt += __popcll(hit);
-                if (cnt > kFewList) return false;
-                if (acc)
+            FewCentre c{lane_of(tm, l), lane_of(amx, l), lane_of(amy, l), lane_of(amz, l),
+                        lane_of(cxm, l), 0.f, PAIR ? lane_of(kdi, l) : 0.f, 0};
+            c.cy0 = c.st.cy;
+            const int cnt = few_candidates<PAIR, false, true>(
+                cs, g, A, d32, c, Df, hi, kd, lay, lane,
+                [&](int at, uint32_t jb, float dx, float dy, float dz) {
                     *(float4 *)(qb + first + at * (int)sizeof(float4)) =
                         make_float4(dx, dy, dz, __uint_as_float(jb | tag));
-            }
+                });
+            if (cnt < 0) return false;
             if (lane == l) {
                 found = cnt;
                 list = first;
@@ -947,7 +925,7 @@ struct Rates32 {
                 __ballot(live && (!GHOST || near_wall) && (nf & m) == m);
             if (!who) continue;
             set_image<GHOST>(m);
-            if (__popcll(who) <= kFew && few_images<GHOST, ZS>(who)) continue;
+            if (!WALL && __popcll(who) <= kFew && few_images<ZS>(who)) continue;
             pass<GHOST, true, ZS, true>();
         }
     }
@@ -1028,7 +1006,7 @@ __global__ __launch_bounds__(kRate32Block, 4) void k_rates32(int64_t n, const fl
                                                     VList vl) {
     if (LIST && vl.gate && *vl.gate == 0) return;
     __shared__ float4 qd[kQ][kRate32Block];
-    __shared__ int2 lay[PER ? kLay : 1];
+    __shared__ int2 lay[PER && !WALL ? kLay : 1];
     // finite placeholder offsets for lanes that pop from an empty ring
 #pragma unroll
     for (int q = 0; q < kQ; ++q) qd[q][threadIdx.x] = make_float4(0.f, 0.f, 0.f, 0.f);

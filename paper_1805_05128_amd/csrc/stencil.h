@@ -357,4 +357,106 @@ __device__ __forceinline__ void walk_rows_split(const int32_t *__restrict__ cs, 
     }
 }
 
+// ---------------------------------------------------------------- few lanes' images
+//
+// The walk around a periodic image that few of a wave's lanes have (kFew at most): a row of cells
+// along a periodic axis holds a few particles near each end, and the ~45 stencil rows walked in
+// lock step for those lanes alone took a quarter of the FP32 kernel's time.  For each of those
+// particles the lanes take a row each, lay the rows' candidates end to end and test one each; the
+// accepted ones are listed in the order of the rows, the one in which the lock-step walk queues
+// them, and popped by the particle's own lane: the sums keep their bits.
+constexpr int kFew = 8;       // particles whose images are walked by the whole wave
+constexpr int kFewList = 64;  // partners each; the lists take the place of the wave's rings
+constexpr int kLay = 128;     // candidates laid out, 8 bytes each
+
+// One such particle (wave-uniform): the stencil around its image (ghost: around its mirror
+// image's), its offsets and cell as the lock-step walk has them, the wall's distance, its part of
+// the pair-h bound.
+struct FewCentre {
+    Stencil st;
+    float ax, ay, az, cx, wl, kl;
+    int cy0;
+};
+
+__device__ __forceinline__ int lane_of(int v, int l) { return __builtin_amdgcn_readlane(v, l); }
+__device__ __forceinline__ float lane_of(float v, int l) {
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+}
+// Lane l's stencil.
+__device__ __forceinline__ Stencil lane_of(Stencil st, int l) {
+    st.cx = lane_of(st.cx, l);
+    st.cy = lane_of(st.cy, l);
+    st.cz = lane_of(st.cz, l);
+    st.fx = lane_of(st.fx, l);
+    st.fy = lane_of(st.fy, l);
+    st.fz = lane_of(st.fz, l);
+    return st;
+}
+
+// Calls emit(at, record offset, dx, dy, dz), at = 0, 1, .., for the candidates within the FP32
+// bound, at most kFewList; returns their number, or -1 when there are more of them, or of the
+// candidates, than fit.  Every lane of the wave calls it.
+template <bool PAIR, bool GHOST, bool ONE, typename E>
+__device__ __forceinline__ int few_candidates(const int32_t *__restrict__ cs, const GridDev &g,
+                                              const float4 *__restrict__ rec,
+                                              const float *__restrict__ d32, const FewCentre &c,
+                                              float Df, float hi, float kd, int2 *lay, int lane,
+                                              E &&emit) {
+    const unsigned long long below = (1ull << lane) - 1ull;
+    const int W = 2 * c.st.R + 1;
+    const float iw = 1.0f / (float)W;
+    int total = 0;
+    wave_fence();  // the layout is read before it is written again
+    for (int q0 = 0; q0 < W * W; q0 += 64) {
+        const int q = q0 + lane;
+        const int iz = (int)(((float)q + 0.5f) * iw);  // q / W (as walk_rows_split)
+        const int oz = iz - c.st.R, oy = q - iz * W - c.st.R;
+        const int yy = c.st.cy + oy, zz = c.st.cz + oz;
+        int j0, len;
+        if (!row_range<ONE>(cs, g, c.st, plane_rem(g, c.st, q < W * W, oz, zz), oy, yy,
+                            cell_key(g, 0, yy, zz), j0, len))
+            continue;
+        len = max(len, 0);
+        int end = len;  // candidates of the rows up to the lane's
+        for (int o = 1; o < 64; o <<= 1) {
+            const int p = __shfl_up(end, o, 64);
+            if (lane >= o) end += p;
+        }
+        const int all = __builtin_amdgcn_readlane(end, 63);
+        if (total + all > kLay) return -1;
+        for (int k = 0; __any(k < len); ++k)
+            if (k < len) lay[total + end - len + k] = make_int2(j0 + k, q);
+        total += all;
+    }
+    wave_fence();
+    int cnt = 0;
+    for (int c0 = 0; c0 < total; c0 += 64) {
+        const bool there = c0 + lane < total;
+        const int2 e = lay[there ? c0 + lane : 0];
+        const int iz = (int)(((float)e.y + 0.5f) * iw);
+        const int oz = iz - c.st.R, oy = e.y - iz * W - c.st.R;
+        const uint32_t jb = (uint32_t)e.x * (uint32_t)sizeof(float4);
+        const float4 aj = *(const float4 *)((const char *)rec + jb);
+        const float az = fmaf(-Df, (float)oz, c.az);
+        const float ay = fmaf(-Df, (float)(c.st.cy + oy - c.cy0), c.ay);
+        const float dx = fmaf(aj.w - c.cx, Df, aj.x) - c.ax;
+        float dy = aj.y - ay;
+        const float dz = aj.z - az;
+        if (GHOST) dy = fmaf(2.0f, c.wl, -dy);
+        const float r2 = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
+        float hj = hi;
+        if (PAIR) {
+            const float Hj = fmaf(kd, d32[e.x], c.kl);
+            hj = Hj * Hj;
+        }
+        const bool acc = there & (r2 < hj);
+        const unsigned long long hit = __ballot(acc);
+        const int at = cnt + __popcll(hit & below);
+        cnt += __popcll(hit);
+        if (cnt > kFewList) return -1;
+        if (acc) emit(at, jb, dx, dy, dz);
+    }
+    return cnt;
+}
+
 }  // namespace csph
