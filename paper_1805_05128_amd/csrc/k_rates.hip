@@ -206,7 +206,7 @@ __device__ __forceinline__ void pair64(bool use, double dx, double dy, double dz
                                        double &aE, double &sig) {
 #pragma clang fp contract(fast)
     // (a lane without a partner may hold r2 = 0: kept finite)
-    const double ir = rsqrt64(fmax(r2, 1e-290));
+    const double ir = rsqrt64(use ? r2 : 1.0);
     const double r = r2 * ir;
     const double q = r * invH;
     const double a1 = 1.0 - q;
@@ -643,8 +643,9 @@ __device__ __forceinline__ void pair32(bool use, float dx, float dy, float dz, f
                                        float invH, float dwch, float &ar, float &avx, float &avy,
                                        float &avz, float &aE, float &sig) {
     // dwch = (210/pi)/H^5, so that dW/dr = -dwch r (1 - r/H)^3
-    // (a lane without a partner may hold r2 = 0: kept finite)
-    const float ir = __builtin_amdgcn_rsqf(fmax_nonneg(r2, 1e-37f));
+    // (a lane without a partner may hold r2 = 0, and v_rsq_f32 takes a subnormal one for 0: both
+    // kept finite by FLT_MIN, which leaves every other r2 as it is)
+    const float ir = __builtin_amdgcn_rsqf(fmax_nonneg(r2, 1.17549435e-38f));
     const float r = r2 * ir;
     const float a1 = fmaf(-r, invH, 1.0f);
     const float dWr = -(use ? dwch : 0.0f) * r * (a1 * a1 * a1);
