@@ -8,6 +8,7 @@
 // particle sums its own partners (gather), so no floating-point atomics are
 // used and results do not depend on scheduling.
 #include "csph_internal.h"
+#include "ring.h"
 #include "stencil.h"
 
 namespace csph {
@@ -690,8 +691,10 @@ __device__ __forceinline__ bool member64(double ex, double ey, double ez, double
 
 static_assert(kFew * kFewList * (int)sizeof(float4) == kRing, "the lists take the rings' place");
 
+// The ring counters (RingCount) advance one ring row per entry: a slot's address is the counter
+// masked to the ring, or'ed with the lane's offset.
 template <bool PAIR, bool WALL, bool LIST, bool PER>
-struct Rates32 {
+struct Rates32 : RingCount<kSlot, kRing> {
     const float4 *__restrict__ A;
     const float4 *__restrict__ B;
     const float4 *__restrict__ Cz;
@@ -718,11 +721,6 @@ struct Rates32 {
     Stencil tm;
     float amx = 0.f, amy = 0.f, amz = 0.f, cxm = 0.f;
     float ar = 0.f, avx = 0.f, avy = 0.f, avz = 0.f, aE = 0.f, sig = 0.f;
-    // ring write and read counters in bytes, advancing one ring row (kSlot) per entry: a
-    // slot's address is the counter masked to the ring, or'ed with the lane's offset;
-    // unsigned, so that the fill level qw - qr stays exact if the counters wrap
-    unsigned qw = 0, qr = 0;
-    int drop = 0, ghosts = 0;
     int2 *lay;     // few_images: candidates laid out (kLay)
     int list = 0;  // few_images: byte offset of the lane's list
 
@@ -796,9 +794,6 @@ struct Rates32 {
                        "+v"(drop), "+v"(qr));
     }
 
-    // |N(i)|: the entries queued less the mirror entries and those the FP64 test turned down
-    __device__ __forceinline__ int count() const { return (int)(qw / kSlot) - ghosts - drop; }
-
     // flat loop as in the FP64 kernel.  IMG: the walk around image point im of i (or of its
     // mirror image), offsets relative to that point's cells; the wall axis y is never periodic,
     // so a mirror walk keeps i's own y offsets.
@@ -860,7 +855,9 @@ struct Rates32 {
                             drain<MIR, ZS>();
                             drain<MIR, ZS>();
                             settle();
+                            popped(2);
                         } while (__any(qw - qr > (kQ - kUS) * kSlot));
+                        settle_counters();
                     }
                     k += kUS;
                 } while (__any(k < len));
@@ -955,7 +952,8 @@ struct Rates32 {
     }
 
     // Verlet-list walk: exact FP64 membership from the FP64 positions; the ring takes
-    // the FP32 offsets (mirrored for flagged entries)
+    // the FP32 offsets (mirrored for flagged entries).  (A list of as many entries as would ask
+    // for settled counters, among as many particles, is larger than any memory.)
     template <bool ZS>
     __device__ __forceinline__ void pass_list(const int32_t *__restrict__ lst, int len,
                                               int64_t nl) {
