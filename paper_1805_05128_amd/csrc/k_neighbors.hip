@@ -36,27 +36,43 @@ hipError_t launch_gather_pos(int64_t n, const int32_t *perm, const double *x, co
     return hipGetLastError();
 }
 
-// In-place heapsort of a[0..c) ascending (a max-heap, then the maximum moved to the end).
-__device__ __forceinline__ void sift_down(int32_t *a, int root, int end) {
-    const int v = a[root];
-    for (;;) {
-        int ch = 2 * root + 1;
-        if (ch >= end) break;
-        if (ch + 1 < end && a[ch + 1] > a[ch]) ++ch;
-        if (a[ch] <= v) break;
-        a[root] = a[ch];
-        root = ch;
-    }
-    a[root] = v;
+// A wave's stores to memory seen by its own later loads, whichever lane made them.
+__device__ __forceinline__ void wave_memory_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
 
-__device__ void heap_sort(int32_t *a, int c) {
-    for (int r = c / 2 - 1; r >= 0; --r) sift_down(a, r, c);
-    for (int e = c - 1; e > 0; --e) {
-        const int t = a[0];
-        a[0] = a[e];
-        a[e] = t;
-        sift_down(a, 0, e);
+// a[0..c) sorted ascending in place by one wave, every lane taking part: runs of k/2 are merged
+// into runs of k, k = 2, 4, .., by Batcher's bitonic network in the form whose first exchange
+// pairs a run's entry with the mirrored one of its neighbour, so that every exchange puts the
+// smaller value first and a pair that reaches past the end has nothing to exchange.
+// O(c log^2 c / 64) with kInFlight pairs a lane at once.
+__device__ void wave_sort(int32_t *a, int c, int lane) {
+    constexpr int kInFlight = 4;
+    auto exchange = [&](int sh, bool mirror) {  // pairs (lo, hi) in blocks of 2 << sh entries
+        const int j = 1 << sh;
+        for (int t0 = lane; (t0 >> sh) << (sh + 1) < c; t0 += 64 * kInFlight) {
+            int lo[kInFlight], hi[kInFlight], x[kInFlight], y[kInFlight];
+#pragma unroll
+            for (int u = 0; u < kInFlight; ++u) {
+                const int t = t0 + 64 * u, o = t & (j - 1), base = (t >> sh) << (sh + 1);
+                lo[u] = base + o;
+                hi[u] = mirror ? base + 2 * j - 1 - o : base + j + o;
+                x[u] = hi[u] < c ? a[lo[u]] : 0;
+                y[u] = hi[u] < c ? a[hi[u]] : 0;
+            }
+#pragma unroll
+            for (int u = 0; u < kInFlight; ++u)
+                if (x[u] > y[u]) {
+                    a[lo[u]] = y[u];
+                    a[hi[u]] = x[u];
+                }
+        }
+        wave_memory_fence();
+    };
+    for (int sh = 0; (1 << sh) < c; ++sh) {
+        exchange(sh, true);
+        for (int q = sh - 1; q >= 0; --q) exchange(q, false);
     }
 }
 
@@ -72,7 +88,11 @@ constexpr int kNbrWaves = kBlock / 64;
 constexpr int kNbrList = 1024;     // candidates laid out at once
 constexpr int kNbrShort = 32;      // longest row its own lane lays out
 constexpr int kNbrBatch = 4;       // 64-candidate tests in flight
-constexpr int kNbrCap = 512;       // neighbours ranked in LDS; a longer row is heap-sorted
+// Neighbours ranked in LDS, O(c^2 / 64); a longer row is sorted in memory by the wave, O(c log^2 c
+// / 64).  83 248 particles: rows up to 322 ranked 0.70 ms, sorted 0.76; up to 431 1.08 and 0.93;
+// up to 534 1.47 and 1.41; up to 721 sorted 2.9 ms, where a heap sort by one lane a row, 63
+// waiting, took 29 ms.  A list of 1 024 costs occupancy: 3.5 ms.
+constexpr int kNbrCap = 512;
 
 template <bool PAIR, bool FILL, bool PER>
 __global__ __launch_bounds__(kBlock) void k_nbr(int64_t n, GridDev g, PairConst pc,
@@ -220,10 +240,9 @@ __global__ __launch_bounds__(kBlock) void k_nbr(int64_t n, GridDev g, PairConst 
             }
             idx[wpos + place] = v;
         }
-    } else {  // the wave's stores reach lane 0, which sorts the row, O(c log c)
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-        if (lane == 0) heap_sort(idx + wpos, cnt);
+    } else {
+        wave_memory_fence();
+        wave_sort(idx + wpos, cnt, lane);
     }
 }
 
