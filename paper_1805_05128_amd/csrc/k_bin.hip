@@ -14,13 +14,17 @@
 
 namespace csph {
 
-// Small sets (kSmallN particles at most; binning also fewer than kSmallKeys keys, and no more than
-// 64 particles to a key on average, since a particle's place in its cell takes a look at each of
-// the cell's others): one workgroup finds the bounds, and one bins, since at this size the chain
-// of launches, ~4 us each, takes longer than the work.
+// Small sets (kSmallN particles at most; binning also fewer than kSmallKeys keys): one workgroup
+// finds the bounds, and one bins, since at this size the chain of launches, ~4 us each, takes
+// longer than the work.  A particle's place in its cell takes a look at each of the cell's others,
+// n n / keys looks in an even set: the one workgroup bins up to kSmallLooks of them.  Ten
+// binnings in a row, one workgroup against the launches: 8 192 particles at 24 a key 306 against
+// 360 us, at 38 380 and 360; 12 000 at 9 304 and 380, at 23 415, at 35 516; 16 384 at 8 339 and 371,
+// at 32 600; 4 096 at 64 292.
 constexpr int kSmallBlock = 1024;
 constexpr int kSmallPer = 16;  // particles and keys a thread
 constexpr int kSmallN = kSmallPer * kSmallBlock;
+constexpr int64_t kSmallLooks = 1 << 18;
 
 // ---------------------------------------------------------------- reductions
 
@@ -448,17 +452,34 @@ __global__ __launch_bounds__(kBlock) void k_cell_rank(const uint32_t *__restrict
 // word, whose atomics also rank the particles in their cells), its scan, the cell segments and
 // the places in them, all in LDS.  Seven launches became one; a 13 824-particle binning took
 // ~17 us of kernels in ~30 us of launches.
+//
+// A particle's place in its cell is the number of the cell's particles with a smaller index: a
+// look at each of them.  Where a cell holds more than kSmallCell, the particles of such cells are
+// first put in order of their rounds (index / kSmallBlock) by counts per cell and round, and look
+// at those of their own round only, eight to a load where there are more than kSmallRow.  16 382
+// particles over 8 000 cells: spread 0.037 ms; 120 cells of 130 0.060, 32 of 511 0.094, 16 000 in
+// one 0.37; by looks at the whole cell 0.134, 0.71 and 12.0, by the launches above 0.055, 0.095
+// and 1.52.  (Cells of 64: 0.068 by rounds, 0.063 by looks eight to a load, which every set's
+// larger code pays for.)
 constexpr int kSmallKeys = 16 * 1024;
+constexpr int kSmallRow = 32;
+constexpr int kSmallCellLog = 6;
+constexpr int kSmallCell = 1 << kSmallCellLog;
 __global__ __launch_bounds__(kSmallBlock) void k_bin_small(
     const double *__restrict__ x, const double *__restrict__ y, const double *__restrict__ z,
     int n, GridDev g, int nkey, int32_t *__restrict__ perm, uint32_t *__restrict__ key_out,
     int32_t *__restrict__ cs, ClearWords w) {
     // counts, then cell starts, as 16-bit halves
     __shared__ __align__(16) uint32_t hist[kSmallKeys / 2];
-    __shared__ uint16_t seg[kSmallN];          // particles by cell, in atomic order
+    __shared__ __align__(16) uint16_t seg[kSmallN];  // particles by cell, in atomic order
     __shared__ int lds[kSmallBlock / 64 + 1];
+    // crowded cells' counts, then offsets, by round: those of number start / kSmallCell, which no two
+    // of them share
+    __shared__ int turn[kSmallN / kSmallCell][kSmallPer];
+    __shared__ int crowded;
     uint16_t *const start = (uint16_t *)hist;
     const int tid = threadIdx.x;
+    if (tid == 0) crowded = 0;
     for (int k = tid; k < kSmallKeys / 8; k += kSmallBlock)
         ((uint4 *)hist)[k] = make_uint4(0u, 0u, 0u, 0u);
     if (tid < w.n) *w.p[tid] = w.v[tid];
@@ -508,17 +529,21 @@ __global__ __launch_bounds__(kSmallBlock) void k_bin_small(
     if ((tid & 63) == 63) lds[tid >> 6] = inc;
     __syncthreads();
     int run = inc - sum;
+    int most = 0;
     for (int q = 0; q < (tid >> 6); ++q) run += lds[q];
 #pragma unroll
     for (int k = 0; k < 8; ++k) {  // the thread's own keys; starts below n <= 16 384
+        const int n0 = (int)(c[k] & 0xffffu), n1 = (int)(c[k] >> 16);
+        most = max(most, max(n0, n1));
         const uint32_t first = (uint32_t)run;
-        run += (int)(c[k] & 0xffffu);
+        run += n0;
         const uint32_t second = (uint32_t)run;
-        run += (int)(c[k] >> 16);
+        run += n1;
         c[k] = first | second << 16;
     }
     own[0] = make_uint4(c[0], c[1], c[2], c[3]);
     own[1] = make_uint4(c[4], c[5], c[6], c[7]);
+    if (most > kSmallCell) crowded = 1;
     __syncthreads();
     for (int k = tid; k < nkey; k += kSmallBlock) cs[k] = start[k];
     if (tid == 0) cs[nkey] = n;
@@ -528,15 +553,84 @@ __global__ __launch_bounds__(kSmallBlock) void k_bin_small(
         if (i >= n) break;
         seg[start[key[q]] + rank[q]] = (uint16_t)i;
     }
+    const auto cell_of = [&](int q, int &a, int &b) {
+        a = start[key[q]];
+        b = (int)key[q] + 1 < kSmallKeys ? start[key[q] + 1] : n;
+    };
+    __syncthreads();
+    if (!crowded) {
+#pragma unroll
+        for (int q = 0; q < kSmallPer; ++q) {
+            const int i = q * kSmallBlock + tid;
+            if (i >= n) break;
+            int a, b;
+            cell_of(q, a, b);
+            int r = 0;
+            for (int t = a; t < b; ++t) r += (int)seg[t] < i ? 1 : 0;
+            perm[a + r] = i;
+        }
+        return;
+    }
+    // the particles of seg[a..b) with an index below i
+    const auto smaller = [&](int a, int b, int i) {
+        int r = 0, t = a;
+        if (b - a > kSmallRow) {
+            for (; t & 7; ++t) r += (int)seg[t] < i ? 1 : 0;
+            for (; t + 8 <= b; t += 8) {
+                const uint4 v = *(const uint4 *)(seg + t);
+                const uint32_t h[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    r += ((int)(h[u] & 0xffffu) < i ? 1 : 0) + ((int)(h[u] >> 16) < i ? 1 : 0);
+            }
+        }
+        for (; t < b; ++t) r += (int)seg[t] < i ? 1 : 0;
+        return r;
+    };
+    constexpr int kTurns = kSmallN / kSmallCell * kSmallPer;
+    int *const all = &turn[0][0];
+    for (int k = tid; k < kTurns; k += kSmallBlock) all[k] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kSmallPer; ++q) {
+        int a, b;
+        if (q * kSmallBlock + tid >= n) break;
+        cell_of(q, a, b);
+        if (b - a > kSmallCell) rank[q] = atomicAdd(&turn[a >> kSmallCellLog][q], 1);
+    }
+    __syncthreads();
+    static_assert(kSmallPer == 16 && kSmallBlock % 16 == 0, "a cell's rounds in 16 lanes");
+    for (int k = tid; k < kTurns; k += kSmallBlock) {
+        const int count = all[k];
+        int upto = count;
+        for (int o = 1; o < 16; o <<= 1) {
+            const int v = __shfl_up(upto, o, 16);
+            if ((tid & 15) >= o) upto += v;
+        }
+        all[k] = upto - count;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kSmallPer; ++q) {
+        int a, b;
+        const int i = q * kSmallBlock + tid;
+        if (i >= n) break;
+        cell_of(q, a, b);
+        if (b - a > kSmallCell) seg[a + turn[a >> kSmallCellLog][q] + rank[q]] = (uint16_t)i;
+    }
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < kSmallPer; ++q) {
         const int i = q * kSmallBlock + tid;
         if (i >= n) break;
-        const int a = start[key[q]], b = (int)key[q] + 1 < kSmallKeys ? start[key[q] + 1] : n;
-        int r = 0;
-        for (int t = a; t < b; ++t) r += (int)seg[t] < i ? 1 : 0;
-        perm[a + r] = i;
+        int a, b;
+        cell_of(q, a, b);
+        if (b - a > kSmallCell) {  // those of its round
+            const int *const off = turn[a >> kSmallCellLog];
+            if (q + 1 < kSmallPer) b = a + off[q + 1];
+            a += off[q];
+        }
+        perm[a + smaller(a, b, i)] = i;
     }
 }
 
@@ -549,7 +643,7 @@ hipError_t launch_bin(const double *x, const double *y, const double *z, int64_t
     const BinCheck c = chk ? *chk : BinCheck{nullptr, nullptr, 0, {0, 0, 0}, {0, 0, 0}};
     const ClearWords cw = words ? *words : ClearWords{};
     const int64_t ncell = g.nkey;  // keys (cells, or the Morton key space)
-    if (n > 0 && n <= kSmallN && ncell < kSmallKeys && n <= 64 * ncell && !chk) {
+    if (n > 0 && n <= kSmallN && ncell < kSmallKeys && n * n <= kSmallLooks * ncell && !chk) {
         k_bin_small<<<1, kSmallBlock, 0, st>>>(x, y, z, (int)n, g, (int)ncell, perm, key_out,
                                                cell_start, cw);
         return hipGetLastError();
