@@ -353,6 +353,7 @@ struct VoroDev {
     const int32_t *owner_at;
     const int32_t *cnt;
     unsigned long long *site_part, *site_pairs;
+    int bounds_from;  // near_min (nearest.h), set by launch_integrate
 };
 // A Verlet-list step's gate and counters: the update does nothing while *gate == 0; otherwise
 // it adds sum_i cnt[i] to *pairs and the finishing kernel adds 1 to *steps.

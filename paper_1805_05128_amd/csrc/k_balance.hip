@@ -24,7 +24,7 @@ namespace csph {
 constexpr double kFix = 4294967296.0;  // 2^32: fixed-point scale of the centre sums
 constexpr double kFixMax = 72057594037927936.0;  // 2^56: per-particle bound (|x - g| < 2^24)
 
-// below this every wave's sum over kNearTile particles fits 63 bits
+// below this every wave's sum over 64 kNearPer particles fits 63 bits
 constexpr double kFixWave = 9007199254740992.0;  // 2^53
 
 // Words of the touching pairs a > b of K subdomains, one bit each.  A workgroup gathers them in
@@ -47,10 +47,11 @@ __device__ __forceinline__ void add128(unsigned long long *lo, unsigned long lon
     if (h) atomicAdd(hi, h);
 }
 
+template <int NP>
 __global__ __launch_bounds__(kBlock) void k_balance_stats(
     const double *__restrict__ x, const double *__restrict__ y, const double *__restrict__ z,
     int64_t n, const int32_t *__restrict__ owner, const int32_t *__restrict__ nbr_count,
-    const double *__restrict__ sites, int K, int W, double dsh,
+    const double *__restrict__ sites, int K, int W, int bounds_from, double dsh,
     unsigned long long *__restrict__ g_part, unsigned long long *__restrict__ g_pairs,
     unsigned long long *__restrict__ g_sum, uint32_t *__restrict__ adj) {
     extern __shared__ double smem[];
@@ -72,16 +73,16 @@ __global__ __launch_bounds__(kBlock) void k_balance_stats(
     for (int q = threadIdx.x; q < tri_words(K); q += kBlock) s_tri[q] = 0u;
     __syncthreads();
     const double lim = 4.0 * (dsh * dsh);
-    const NearTiles run = near_tiles(n);
+    const NearTiles run = near_tiles<NP>(n);
     for (int64_t tile = run.at; tile < run.end; ++tile) {
-        const int64_t i0 = tile * kNearTile + (threadIdx.x & 63);
-        LaneParticles<kNearPer> w;
-        int k[kNearPer];
-        long long v[kNearPer][3];
-        unsigned long long pc[kNearPer];
+        const int64_t i0 = tile * (64 * NP) + (threadIdx.x & 63);
+        LaneParticles<NP> w;
+        int k[NP];
+        long long v[NP][3];
+        unsigned long long pc[NP];
         bool any = false, large = false;
 #pragma unroll
-        for (int q = 0; q < kNearPer; ++q) {
+        for (int q = 0; q < NP; ++q) {
             const int64_t i = i0 + 64 * q;
             const int kr = i < n ? owner[i] : -1;
             w.on[q] = kr >= 0 && kr < K;
@@ -100,15 +101,15 @@ __global__ __launch_bounds__(kBlock) void k_balance_stats(
             }
         }
         if (!__any(any)) continue;
-        bool on[kNearPer];
+        bool on[NP];
 #pragma unroll
-        for (int q = 0; q < kNearPer; ++q) on[q] = w.on[q];
+        for (int q = 0; q < NP; ++q) on[q] = w.on[q];
         // the wave's sums per owner (exact integers), added by one lane
         if (!__any(large))
-            for_owners<kNearPer>(on, k, [&](int k0, const bool(&mine)[kNearPer], int count) {
+            for_owners<NP>(on, k, [&](int k0, const bool(&mine)[NP], int count) {
                 unsigned long long sp = 0, sv[3] = {0, 0, 0};
 #pragma unroll
-                for (int q = 0; q < kNearPer; ++q) {
+                for (int q = 0; q < NP; ++q) {
                     sp += mine[q] ? pc[q] : 0ull;
 #pragma unroll
                     for (int d = 0; d < 3; ++d)
@@ -126,7 +127,7 @@ __global__ __launch_bounds__(kBlock) void k_balance_stats(
                 }
             });
 #pragma unroll
-        for (int q = 0; q < kNearPer; ++q) {
+        for (int q = 0; q < NP; ++q) {
             if (!on[q]) continue;
             atomicAdd(&s_part[k[q]], 1u);
             if (nbr_count) atomicAdd(&s_pairs[k[q]], pc[q]);
@@ -135,17 +136,16 @@ __global__ __launch_bounds__(kBlock) void k_balance_stats(
         }
         if (K > 1) {
             // nearest other generator (ties to the smaller index) and the owner's distance
-            double bd[kNearPer];
-            int best[kNearPer];
+            double bd[NP];
+            int best[NP];
 #pragma unroll
-            for (int q = 0; q < kNearPer; ++q) {
+            for (int q = 0; q < NP; ++q) {
                 bd[q] = INFINITY;
                 best[q] = -1;
             }
-            near_sites<true, kNearPer>(gs, K, w, [&](int l) {
-                const double gx = gs[3 * l], gy = gs[3 * l + 1], gz = gs[3 * l + 2];
+            near_sites<true, NP>(gs, K, bounds_from, w, [&](int l, double gx, double gy, double gz) {
 #pragma unroll
-                for (int q = 0; q < kNearPer; ++q) {
+                for (int q = 0; q < NP; ++q) {
                     const double d2 = norm2(w.p[q][0] - gx, w.p[q][1] - gy, w.p[q][2] - gz);
                     if (l != k[q] && d2 < bd[q]) {
                         bd[q] = d2;
@@ -154,7 +154,7 @@ __global__ __launch_bounds__(kBlock) void k_balance_stats(
                 }
             });
 #pragma unroll
-            for (int q = 0; q < kNearPer; ++q) {
+            for (int q = 0; q < NP; ++q) {
                 // best < 0: no finite distance to another generator
                 const int a = k[q], b = best[q] < 0 ? a : best[q];
                 const double d2o = norm2(w.p[q][0] - gs[3 * a], w.p[q][1] - gs[3 * a + 1],
@@ -174,17 +174,18 @@ __global__ __launch_bounds__(kBlock) void k_balance_stats(
         if (s_part[k]) atomicAdd(&g_part[k], (unsigned long long)s_part[k]);
         if (s_pairs[k]) atomicAdd(&g_pairs[k], s_pairs[k]);
     }
-    for (int q = threadIdx.x; q < tri_words(K); q += kBlock) {
-        for (uint32_t m = s_tri[q]; m; m &= m - 1) {
-            // bit t is the pair a > b with t = a (a - 1) / 2 + b
-            const int t = 32 * q + __ffs(m) - 1;
-            int a = (int)(0.5f * (1.0f + sqrtf(1.0f + 8.0f * (float)t)));
-            while (a * (a - 1) / 2 > t) --a;
-            while (a * (a + 1) / 2 <= t) ++a;
-            const int b = t - a * (a - 1) / 2;
-            atomicOr(adj + (size_t)a * W + (b >> 5), 1u << (b & 31));
-            atomicOr(adj + (size_t)b * W + (a >> 5), 1u << (a & 31));
-        }
+    // the lower triangle, a word (a, w) of 32 pairs b < a at a time (bits a (a - 1) / 2 + 32 w on),
+    // where the matrix lacks some: every workgroup of scattered particles meets every pair, and an
+    // atomic a pair took most of 378 us for 1 M of them and 16 generators (47 us now)
+    for (int q = threadIdx.x; q < K * W; q += kBlock) {
+        const int a = q / W, b0 = 32 * (q - a * W), t = a * (a - 1) / 2 + b0;
+        if (b0 >= a) continue;
+        const int word = t >> 5, sh = t & 31;
+        uint32_t m = s_tri[word] >> sh;
+        if (sh && word + 1 < tri_words(K)) m |= s_tri[word + 1] << (32 - sh);
+        if (a - b0 < 32) m &= (1u << (a - b0)) - 1u;
+        if (m & ~__hip_atomic_load(&adj[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+            atomicOr(&adj[q], m);
     }
     for (int k = threadIdx.x; k < 3 * K; k += kBlock) {
         const unsigned long long lo = s_lo[k], hi = s_hi[k];
@@ -202,8 +203,16 @@ __global__ __launch_bounds__(kBlock) void k_balance_finish(
     const double *__restrict__ sites, int K, const unsigned long long *__restrict__ g_part,
     const unsigned long long *__restrict__ g_pairs, const unsigned long long *__restrict__ g_sum,
     int64_t *__restrict__ site_particles, int64_t *__restrict__ site_pairs,
-    double *__restrict__ centre) {
+    double *__restrict__ centre, uint32_t *__restrict__ adj, int W) {
     const int k = blockIdx.x * kBlock + threadIdx.x;
+    if (k < K * W) {  // the touching pairs' upper triangle: word (a, w) holds b = 32 w on, b < a
+        const int a = k / W, b0 = 32 * (k - a * W);
+        uint32_t m = b0 < a ? __hip_atomic_load(&adj[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                            : 0u;
+        if (a - b0 < 32) m &= b0 < a ? (1u << (a - b0)) - 1u : 0u;
+        for (; m; m &= m - 1)
+            atomicOr(&adj[(size_t)(b0 + __ffs(m) - 1) * W + (a >> 5)], 1u << (a & 31));
+    }
     if (k >= K) return;
     const unsigned long long np = g_part[k];
     if (site_particles) site_particles[k] = (int64_t)np;
@@ -400,15 +409,15 @@ hipError_t launch_balance_stats(const double *x, const double *y, const double *
     unsigned long long *g_sum = g_pairs + K;                 // 6K: lo[3K], hi[3K]
     launch_zero2(g_part, 16 * K, adj, K * W, st);
     if (n > 0) {
-        const unsigned nb = near_blocks(n, kReduceBlocks);
+        const unsigned nb = near_blocks(n, near_per(n), kReduceBlocks);
         const size_t shm = (size_t)K * (3 * sizeof(double) + 7 * sizeof(unsigned long long) +
                                         sizeof(unsigned int)) +
                            sizeof(uint32_t) * tri_words(K);
-        k_balance_stats<<<nb, kBlock, shm, st>>>(x, y, z, n, owner, nbr_count, sites, K, W, dsh,
-                                                 g_part, g_pairs, g_sum, adj);
+        (near_per(n) == 1 ? k_balance_stats<1> : k_balance_stats<kNearPer>)<<<nb, kBlock, shm, st>>>(
+            x, y, z, n, owner, nbr_count, sites, K, W, near_min(n), dsh, g_part, g_pairs, g_sum, adj);
     }
-    k_balance_finish<<<(unsigned)((K + kBlock - 1) / kBlock), kBlock, 0, st>>>(
-        sites, K, g_part, g_pairs, g_sum, site_particles, site_pairs, centre);
+    k_balance_finish<<<(unsigned)((K * W + kBlock - 1) / kBlock), kBlock, 0, st>>>(
+        sites, K, g_part, g_pairs, g_sum, site_particles, site_pairs, centre, adj, W);
     return hipGetLastError();
 }
 

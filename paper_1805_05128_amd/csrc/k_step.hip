@@ -234,7 +234,7 @@ __global__ __launch_bounds__(kBlock) void k_integrate(int64_t n, State9 s, Rates
             const LaneParticles<1> w{{on}, {{x, y, z}}};
             const int32_t c[1] = {on && vo.site_pairs ? vo.cnt[i] : 0};
             int best[1];
-            nearest_site<1>(gs, vo.K, w, best);
+            nearest_site<1>(gs, vo.K, vo.bounds_from, w, best);
             if (on) vo.owner[vo.owner_at ? vo.owner_at[i] : (int)i] = best[0];
             count_owners<1>(w.on, best, vo.site_pairs != nullptr, c, hp, hq);
         }
@@ -366,6 +366,7 @@ hipError_t launch_integrate(int64_t n, double *const st8[9], const Ws &w, double
     size_t shm = 0;
     if (vo && vo->K > 0) {
         v = *vo;
+        v.bounds_from = near_min(n);
         launch_zero2(v.site_part, 2 * v.K, v.site_pairs, 2 * v.K, st);
         shm = (size_t)v.K * (3 * sizeof(double) + sizeof(unsigned long long) + sizeof(unsigned));
     }

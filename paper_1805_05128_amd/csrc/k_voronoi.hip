@@ -26,10 +26,12 @@ hipError_t launch_zero2(void *a, int64_t na, void *b, int64_t nb, hipStream_t st
     return hipGetLastError();
 }
 
+template <int NP>
 __global__ __launch_bounds__(kBlock) void k_voronoi(const double *__restrict__ x,
                                                     const double *__restrict__ y,
                                                     const double *__restrict__ z, int64_t n,
                                                     const double *__restrict__ sites, int K,
+                                                    int bounds_from,
                                                     const int32_t *__restrict__ nbr_count,
                                                     int32_t *__restrict__ owner,
                                                     unsigned long long *__restrict__ site_part,
@@ -44,14 +46,14 @@ __global__ __launch_bounds__(kBlock) void k_voronoi(const double *__restrict__ x
         hq[k] = 0ull;
     }
     __syncthreads();
-    const NearTiles mine = near_tiles(n);
+    const NearTiles mine = near_tiles<NP>(n);
     for (int64_t tile = mine.at; tile < mine.end; ++tile) {
-        const int64_t i0 = tile * kNearTile + (threadIdx.x & 63);
-        LaneParticles<kNearPer> w;
-        int32_t c[kNearPer];
-        int best[kNearPer];
+        const int64_t i0 = tile * (64 * NP) + (threadIdx.x & 63);
+        LaneParticles<NP> w;
+        int32_t c[NP];
+        int best[NP];
 #pragma unroll
-        for (int q = 0; q < kNearPer; ++q) {
+        for (int q = 0; q < NP; ++q) {
             const int64_t i = i0 + 64 * q;
             w.on[q] = i < n;
             w.p[q][0] = w.on[q] ? x[i] : 0.0;
@@ -59,11 +61,11 @@ __global__ __launch_bounds__(kBlock) void k_voronoi(const double *__restrict__ x
             w.p[q][2] = w.on[q] ? z[i] : 0.0;
             c[q] = nbr_count && w.on[q] ? nbr_count[i] : 0;
         }
-        nearest_site<kNearPer>(gs, K, w, best);
+        nearest_site<NP>(gs, K, bounds_from, w, best);
 #pragma unroll
-        for (int q = 0; q < kNearPer; ++q)
+        for (int q = 0; q < NP; ++q)
             if (w.on[q]) owner[i0 + 64 * q] = best[q];
-        count_owners<kNearPer>(w.on, best, nbr_count != nullptr, c, hp, hq);
+        count_owners<NP>(w.on, best, nbr_count != nullptr, c, hp, hq);
     }
     __syncthreads();
     for (int k = threadIdx.x; k < K; k += kBlock) {
@@ -77,11 +79,11 @@ hipError_t launch_voronoi(const double *x, const double *y, const double *z, int
                           int64_t *site_particles, int64_t *site_pairs, hipStream_t st) {
     launch_zero2(site_particles, 2 * K, site_pairs, 2 * K, st);
     if (n > 0) {
-        const unsigned nb = near_blocks(n, kReduceBlocks);
+        const unsigned nb = near_blocks(n, near_per(n), kReduceBlocks);
         size_t shm = (size_t)K * (3 * sizeof(double) + sizeof(unsigned long long) + sizeof(unsigned));
-        k_voronoi<<<nb, kBlock, shm, st>>>(x, y, z, n, sites, K, site_pairs ? nbr_count : nullptr,
-                                           owner, (unsigned long long *)site_particles,
-                                           (unsigned long long *)site_pairs);
+        (near_per(n) == 1 ? k_voronoi<1> : k_voronoi<kNearPer>)<<<nb, kBlock, shm, st>>>(
+            x, y, z, n, sites, K, near_min(n), site_pairs ? nbr_count : nullptr, owner,
+            (unsigned long long *)site_particles, (unsigned long long *)site_pairs);
     }
     return hipGetLastError();
 }

@@ -13,16 +13,28 @@
 #include "csph_internal.h"
 #include "wave.h"
 
+#include <climits>
+#include <type_traits>
+
 namespace csph {
 
-// Below this many generators the bounds (about as much work as scanning 8 of them) are left out.
+// Generators from which on a pass over n particles takes the bounds: below kNearMin they (about as
+// much work as scanning 8 generators) are left out, and so they are where the chip has a wave a SIMD
+// at most, whose time goes with the length of its chain (5 000 particles in cell order, 512
+// generators: ownership 44 us with the bounds, 31 without).
 constexpr int kNearMin = 12;
+constexpr int64_t kNearFew = 1 << 16;
+inline int near_min(int64_t n) { return n <= kNearFew ? INT_MAX : kNearMin; }
 
 // Particles a lane holds in the passes over particles alone: the box, the bounds and the sums
 // below are paid once per 256 consecutive particles, whose box is hardly larger than 64's (a
 // cell row's worth and its neighbours).
+// In smaller sets, a particle each: up to kNearOne that leaves the chip's 4 096 waves a tile each at
+// most.  Ownership by 512 generators, one against four a lane: 100 000 particles 46 and 86 us,
+// 260 000 75 (scattered) or 65 and 89 or 86, 500 000 161 or 116 and 123 or 105.
 constexpr int kNearPer = 4;
-constexpr int kNearTile = 64 * kNearPer;
+constexpr int64_t kNearOne = 1 << 18;
+inline int near_per(int64_t n) { return n <= kNearOne ? 1 : kNearPer; }
 
 // Minimum of a wave's 64 integers (every lane active); the result is wave-uniform.
 __device__ __forceinline__ int wave_all_min(int v) {
@@ -63,10 +75,10 @@ struct LaneParticles {
     double p[NP][3];
 };
 
-// Calls each(k), k ascending and wave-uniform, for every generator that can be the nearest
+// Calls each(k, its x, y, z), k ascending and wave-uniform, for every generator that can be the nearest
 // (SECOND: the nearest but for one that the particle leaves out) of some particle of the wave;
 // now and then a k comes twice in a row.  gs: the generators (3 K doubles, LDS).  Every lane of
-// the wave calls it, and each(k) runs in every lane.
+// the wave calls it, and each runs in every lane.  bounds_from: near_min of the pass.
 //
 // The bounds are FP32 with margins: a coordinate rounds by 2^-24 of itself and is widened by
 // 2^-22, the squared bounds by 1e-5 (their few roundings are below 1e-6) and 1e-36 (underflow).
@@ -74,47 +86,13 @@ struct LaneParticles {
 // a NaN coordinate is left out of the box (its particle has no nearest generator) and a NaN
 // bound admits its generator.
 template <bool SECOND, int NP, typename F>
-__device__ __forceinline__ void near_sites(const double *gs, int K, const LaneParticles<NP> &w,
-                                           F &&each) {
-    if (K < kNearMin) {
-        for (int k = 0; k < K; ++k) each(k);
-        return;
-    }
+__device__ __forceinline__ void near_sites(const double *gs, int K, int bounds_from,
+                                           const LaneParticles<NP> &w, F &&each) {
     constexpr float kWide = 2.384185791015625e-7f;  // 2^-22
-    float lo[3], hi[3];
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        float l = INFINITY, h = INFINITY;  // minima of x and of -x
-#pragma unroll
-        for (int q = 0; q < NP; ++q) {
-            const float p = (float)w.p[q][a], e = fabsf(p) * kWide;
-            const float pl = p - e, ph = -p - e;  // NaN where p is NaN or an infinity of that side
-            l = w.on[q] && pl < l ? pl : l;
-            h = w.on[q] && ph < h ? ph : h;
-        }
-        lo[a] = wave_all_min(l);
-        hi[a] = -wave_all_min(h);
-    }
     const int lane = threadIdx.x & 63;
-    float m1 = INFINITY, m2 = INFINITY;  // the lane's smallest (and second) upper bounds
-    for (int l = lane; l < K; l += 64) {
-        float d2 = 0.0f;
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            const float g = (float)gs[3 * l + a];
-            const float f = fmaxf(hi[a] - g, g - lo[a]) + fabsf(g) * kWide;
-            d2 += f * f;
-        }
-        if (SECOND && d2 < m2) m2 = d2 < m1 ? m1 : d2;
-        if (d2 < m1) m1 = d2;
-    }
-    float thr = wave_all_min(m1);
-    if (SECOND) {  // the smallest left when one lane gives up that minimum
-        const int f = __ffsll((unsigned long long)__ballot(m1 == thr)) - 1;
-        thr = wave_all_min(lane == f ? m2 : m1);
-    }
-    thr = thr * (1.0f + 1e-5f) + 1e-36f;
-    for (int l0 = 0; l0 < K; l0 += 64) {
+    float lo[3], hi[3], thr = 0.0f;
+    // the generators l0 + lane that the bounds admit
+    auto admitted = [&](int l0) {
         const int l = l0 + lane;
         bool in = l < K;
         if (in) {
@@ -127,30 +105,89 @@ __device__ __forceinline__ void near_sites(const double *gs, int K, const LanePa
             }
             in = !(d2 * (1.0f - 1e-5f) > thr);
         }
+        return (unsigned long long)__ballot(in);
+    };
+    bool all = K < bounds_from;
+    if (!all) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            float l = INFINITY, h = INFINITY;  // minima of x and of -x
+#pragma unroll
+            for (int q = 0; q < NP; ++q) {
+                const float p = (float)w.p[q][a], e = fabsf(p) * kWide;
+                const float pl = p - e, ph = -p - e;  // NaN where p is NaN or an infinity of that side
+                l = w.on[q] && pl < l ? pl : l;
+                h = w.on[q] && ph < h ? ph : h;
+            }
+            lo[a] = wave_all_min(l);
+            hi[a] = -wave_all_min(h);
+        }
+        float m1 = INFINITY, m2 = INFINITY;  // the lane's smallest (and second) upper bounds
+        for (int l = lane; l < K; l += 64) {
+            float d2 = 0.0f;
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                const float g = (float)gs[3 * l + a];
+                const float f = fmaxf(hi[a] - g, g - lo[a]) + fabsf(g) * kWide;
+                d2 += f * f;
+            }
+            if (SECOND && d2 < m2) m2 = d2 < m1 ? m1 : d2;
+            if (d2 < m1) m1 = d2;
+        }
+        thr = wave_all_min(m1);
+        if (SECOND) {  // the smallest left when one lane gives up that minimum
+            const int f = __ffsll((unsigned long long)__ballot(m1 == thr)) - 1;
+            thr = wave_all_min(lane == f ? m2 : m1);
+        }
+        thr = thr * (1.0f + 1e-5f) + 1e-36f;
+        // scattered particles admit nearly all generators (the first 64 tell): the plain loop, with
+        // more LDS reads ahead, is the faster one (3 M such, 512 generators: 595 against 649 us)
+        all = 8 * __popcll(admitted(0)) > 7 * min(K, 64);
+    }
+    // B generators at a time, their LDS reads ahead of the comparisons
+    auto in_turn = [&](auto width, int k0) {
+        constexpr int B = decltype(width)::value;
+        double g[B][3];
+#pragma unroll
+        for (int u = 0; u < B; ++u)
+#pragma unroll
+            for (int a = 0; a < 3; ++a) g[u][a] = gs[3 * (k0 + u) + a];
+#pragma unroll
+        for (int u = 0; u < B; ++u) each(k0 + u, g[u][0], g[u][1], g[u][2]);
+    };
+    if (all) {
+        constexpr int B = NP == 1 ? 8 : 4;
+        int k = 0;
+        for (; k + B <= K; k += B) in_turn(std::integral_constant<int, B>{}, k);
+        for (; k < K; ++k) in_turn(std::integral_constant<int, 1>{}, k);
+        return;
+    }
+    for (int l0 = 0; l0 < K; l0 += 64) {
         // two at a time, so that one's LDS reads pass while the other is compared
-        for (unsigned long long m = __ballot(in); m;) {
+        for (unsigned long long m = admitted(l0); m;) {
             const int k0 = l0 + __ffsll(m) - 1;
             m &= m - 1;
             const int k1 = m ? l0 + __ffsll(m) - 1 : k0;
             m &= m - 1;
-            each(k0);
-            each(k1);
+            const double x0 = gs[3 * k0], y0 = gs[3 * k0 + 1], z0 = gs[3 * k0 + 2];
+            const double x1 = gs[3 * k1], y1 = gs[3 * k1 + 1], z1 = gs[3 * k1 + 2];
+            each(k0, x0, y0, z0);
+            each(k1, x1, y1, z1);
         }
     }
 }
 
 // The nearest generator of each particle (FP64 argmin, ties to the smaller index).
 template <int NP>
-__device__ __forceinline__ void nearest_site(const double *gs, int K, const LaneParticles<NP> &w,
-                                             int (&best)[NP]) {
+__device__ __forceinline__ void nearest_site(const double *gs, int K, int bounds_from,
+                                             const LaneParticles<NP> &w, int (&best)[NP]) {
     double bd[NP];
 #pragma unroll
     for (int q = 0; q < NP; ++q) {
         best[q] = 0;
         bd[q] = INFINITY;
     }
-    near_sites<false, NP>(gs, K, w, [&](int k) {
-        const double gx = gs[3 * k], gy = gs[3 * k + 1], gz = gs[3 * k + 2];
+    near_sites<false, NP>(gs, K, bounds_from, w, [&](int k, double gx, double gy, double gz) {
 #pragma unroll
         for (int q = 0; q < NP; ++q) {
             const double dx = w.p[q][0] - gx, dy = w.p[q][1] - gy, dz = w.p[q][2] - gz;
@@ -220,20 +257,21 @@ __device__ __forceinline__ void count_owners(const bool (&there)[NP], const int 
     }
 }
 
-// The tiles of kNearTile particles a wave takes: consecutive ones, a workgroup's waves side by
+// The tiles of 64 NP particles a wave takes: consecutive ones, a workgroup's waves side by
 // side, so that a workgroup meets few generators and adds few of them to the totals at its end.
 struct NearTiles {
     int64_t at, end;
 };
+template <int NP>
 __device__ __forceinline__ NearTiles near_tiles(int64_t n) {
-    const int64_t tiles = (n + kNearTile - 1) / kNearTile;
+    const int64_t tiles = (n + 64 * NP - 1) / (64 * NP);
     const int64_t waves = (int64_t)gridDim.x * (kBlock / 64);
     const int64_t w = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
     return NearTiles{w * tiles / waves, (w + 1) * tiles / waves};
 }
 // Workgroups for them, `most` at most.
-inline unsigned near_blocks(int64_t n, int64_t most) {
-    const int64_t tiles = (n + kNearTile - 1) / kNearTile;
+inline unsigned near_blocks(int64_t n, int np, int64_t most) {
+    const int64_t tiles = (n + 64 * np - 1) / (64 * np);
     const int64_t want = (tiles + kBlock / 64 - 1) / (kBlock / 64);
     return (unsigned)(want > most ? most : want);
 }
