@@ -94,29 +94,34 @@ constexpr int kNbrBatch = 4;       // 64-candidate tests in flight
 // waiting, took 29 ms.  A list of 1 024 costs occupancy: 3.5 ms.
 constexpr int kNbrCap = 512;
 
+// The export's inputs and outputs (cell order but for count_orig, offsets and idx).
+struct NbrArgs {
+    int64_t n;
+    GridDev g;
+    PairConst pc;
+    const double *__restrict__ x, *__restrict__ y, *__restrict__ z, *__restrict__ d;
+    const int32_t *__restrict__ cs, *__restrict__ perm;
+    int32_t *__restrict__ count_orig;
+    const int64_t *__restrict__ offsets;
+    int32_t *__restrict__ idx;
+};
+
+// Particle s's count or row by the whole wave; list (kNbrList) and mine (kNbrCap) are the wave's.
 template <bool PAIR, bool FILL, bool PER>
-__global__ __launch_bounds__(kBlock) void k_nbr(int64_t n, GridDev g, PairConst pc,
-                                                const double *__restrict__ x,
-                                                const double *__restrict__ y,
-                                                const double *__restrict__ z,
-                                                const double *__restrict__ d,
-                                                const int32_t *__restrict__ cs,
-                                                const int32_t *__restrict__ perm,
-                                                int32_t *__restrict__ count_orig,
-                                                const int64_t *__restrict__ offsets,
-                                                int32_t *__restrict__ idx) {
-    __shared__ int lst[kNbrWaves][kNbrList];
-    __shared__ __align__(16) int acc[FILL ? kNbrWaves : 1][FILL ? kNbrCap : 4];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int64_t s = xcd_block_upto(blockIdx.x, gridDim.x, 16384) * kNbrWaves + wave;
-    if (s >= n) return;  // whole waves; no barrier follows
+__device__ __forceinline__ void nbr_particle(const NbrArgs &A, int64_t s, int *list, int *mine,
+                                             int lane) {
+    const GridDev &g = A.g;
+    const PairConst &pc = A.pc;
+    const double *const x = A.x, *const y = A.y, *const z = A.z, *const d = A.d;
+    const int32_t *const cs = A.cs, *const perm = A.perm;
+    const int64_t *const offsets = A.offsets;
+    int32_t *const idx = A.idx;
     const double xi = x[s], yi = y[s], zi = z[s];
     const double di = PAIR ? d[s] : 0.0;
     const int nf = PER ? image_faces(pc, xi, yi, zi) : 0;
     const int i = perm[s];
     const int64_t wpos = FILL ? offsets[i] : 0;
     const bool ranked = FILL && offsets[i + 1] - wpos <= kNbrCap;
-    int *const mine = acc[FILL ? wave : 0];
     int cnt = 0;
     // image m = 0: i itself; m > 0: the periodic image of i across the faces of mask m
     for (int m = 0; m < (PER ? 8 : 1); ++m) {
@@ -185,14 +190,14 @@ __global__ __launch_bounds__(kBlock) void k_nbr(int64_t n, GridDev g, PairConst 
                 wave_fence();
                 if (!__any(len > kNbrShort)) {
                     for (int k = 0; __any(k < len); ++k)
-                        if (k < len) lst[wave][end - len + k] = j0 + k;
+                        if (k < len) list[end - len + k] = j0 + k;
                 } else {
                     for (unsigned long long rows = __ballot(len > 0); rows; rows &= rows - 1) {
                         const int r = __builtin_ctzll(rows);
                         const int a = __builtin_amdgcn_readlane(j0, r);
                         const int c = __builtin_amdgcn_readlane(len, r);
                         const int at = __builtin_amdgcn_readlane(end, r) - c;
-                        for (int t = lane; t < c; t += 64) lst[wave][at + t] = a + t;
+                        for (int t = lane; t < c; t += 64) list[at + t] = a + t;
                     }
                 }
                 wave_fence();
@@ -201,7 +206,7 @@ __global__ __launch_bounds__(kBlock) void k_nbr(int64_t n, GridDev g, PairConst 
 #pragma unroll
                     for (int u = 0; u < kNbrBatch; ++u) {
                         const int at = t + 64 * u + lane;
-                        j[u] = at < total ? lst[wave][at] : -1;
+                        j[u] = at < total ? list[at] : -1;
                     }
                     test(j);
                 }
@@ -224,7 +229,7 @@ __global__ __launch_bounds__(kBlock) void k_nbr(int64_t n, GridDev g, PairConst 
         }
     }
     if (!FILL) {
-        if (lane == 0) count_orig[i] = cnt;
+        if (lane == 0) A.count_orig[i] = cnt;
         return;
     }
     if (ranked) {  // ascending: a neighbour's place is the number of smaller ones
@@ -246,15 +251,118 @@ __global__ __launch_bounds__(kBlock) void k_nbr(int64_t n, GridDev g, PairConst 
     }
 }
 
-hipError_t launch_nbr_count(int64_t n, const GridDev &g, const PairConst &pc, const double *x,
-                            const double *y, const double *z, const double *d, const int32_t *cs,
-                            const int32_t *perm, int32_t *count_orig, hipStream_t st) {
-    if (n <= 0) return hipSuccess;
-    const unsigned nb = (unsigned)((n + kNbrWaves - 1) / kNbrWaves);
-#define CSPH_NBR(P, X)                                                                    \
-    if (!!pc.pair_mode == P && !!pc.per == X)                                             \
-        k_nbr<P, false, X><<<nb, kBlock, 0, st>>>(n, g, pc, x, y, z, d, cs, perm, count_orig, \
-                                                  nullptr, nullptr);
+template <bool PAIR, bool FILL, bool PER>
+__global__ __launch_bounds__(kBlock) void k_nbr(NbrArgs A) {
+    __shared__ int lst[kNbrWaves][kNbrList];
+    __shared__ __align__(16) int acc[FILL ? kNbrWaves : 1][FILL ? kNbrCap : 4];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int64_t s = xcd_block_upto(blockIdx.x, gridDim.x, 16384) * kNbrWaves + wave;
+    if (s >= A.n) return;  // whole waves; no barrier follows
+    nbr_particle<PAIR, FILL, PER>(A, s, lst[wave], acc[FILL ? wave : 0], lane);
+}
+
+// Large sparse sets, a handful of candidates a particle: a wave a particle would spend its ~700
+// instructions on each, so a lane takes one, walks its candidates and inserts its neighbours into
+// a list of its own.  A particle of more than kNbrThin candidates or kNbrOwn neighbours, or with
+// periodic images, is left to the whole wave afterwards: dense spots cost what they cost above.
+// The export of 1 M particles: 0.3 neighbours each 0.41 ms (a wave a particle 1.40), 9 each 0.68
+// (1.47).
+constexpr int kNbrThin = 96;
+constexpr int kNbrOwn = kNbrList / 64;
+
+template <bool PAIR, bool FILL, bool PER>
+__global__ __launch_bounds__(kBlock) void k_nbr_sparse(NbrArgs A) {
+    __shared__ int lst[kNbrWaves][kNbrList];
+    __shared__ __align__(16) int acc[FILL ? kNbrWaves : 1][FILL ? kNbrCap : 4];
+    const GridDev &g = A.g;
+    const PairConst &pc = A.pc;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int64_t s0 = (xcd_block_upto(blockIdx.x, gridDim.x, 256) * kNbrWaves + wave) * 64;
+    const int64_t s = s0 + lane;
+    if (s0 >= A.n) return;  // whole waves; no barrier follows
+    const bool live = s < A.n;
+    const double xi = live ? A.x[s] : 0.0, yi = live ? A.y[s] : 0.0, zi = live ? A.z[s] : 0.0;
+    const double di = PAIR && live ? A.d[s] : 0.0;
+    const int i = live ? A.perm[s] : 0;
+    const int64_t wpos = FILL && live ? A.offsets[i] : 0;
+    int *const own = lst[wave] + lane;  // entry t of the lane's list at 64 t
+    bool left = live && PER && image_faces(pc, xi, yi, zi) != 0;
+    if (FILL && live) left = left || A.offsets[i + 1] - wpos > kNbrOwn;
+    const Stencil st = make_stencil(g, xi, yi, zi, pc.H);
+    int cnt = 0, walked = 0;
+    walk_rows(A.cs, g, st, live, [&](int, int, int, int j0, int len) {
+        left = left || (len > 0 && walked + len > kNbrThin);
+        len = left ? 0 : len;
+        walked += len;
+        for (int k = 0; __any(k < len); k += kNbrBatch) {
+            double dx[kNbrBatch], dy[kNbrBatch], dz[kNbrBatch], dd[kNbrBatch];
+            int id[kNbrBatch];
+#pragma unroll
+            for (int u = 0; u < kNbrBatch; ++u) {
+                const int j = k + u < len ? j0 + k + u : 0;
+                dx[u] = A.x[j];
+                dy[u] = A.y[j];
+                dz[u] = A.z[j];
+                dd[u] = PAIR ? A.d[j] : 0.0;
+                id[u] = FILL ? A.perm[j] : 0;
+            }
+#pragma unroll
+            for (int u = 0; u < kNbrBatch; ++u) {
+                const double ex = dx[u] - xi, ey = dy[u] - yi, ez = dz[u] - zi;
+                const double r2 = ((ex * ex) + (ey * ey)) + (ez * ez);
+                double H2 = pc.H2;
+                if (PAIR) {
+                    const double H = pc.kappa * (0.5 * (di + dd[u]));
+                    H2 = H * H;
+                }
+                if (k + u < len && j0 + k + u != (int)s && r2 < H2) {
+                    if (FILL) {  // (a row within kNbrOwn, so its list holds it)
+                        int t = cnt;
+                        for (; t > 0 && own[64 * (t - 1)] > id[u]; --t) own[64 * t] = own[64 * (t - 1)];
+                        own[64 * t] = id[u];
+                    }
+                    ++cnt;
+                }
+            }
+        }
+    });
+    if (live && !left) {
+        if (FILL) {
+            for (int t = 0; t < cnt; ++t) A.idx[wpos + t] = own[64 * t];
+        } else {
+            A.count_orig[i] = cnt;
+        }
+    }
+    for (unsigned long long rest = __ballot(left); rest; rest &= rest - 1) {
+        wave_fence();
+        nbr_particle<PAIR, FILL, PER>(A, s0 + __builtin_ctzll(rest), lst[wave],
+                                      acc[FILL ? wave : 0], lane);
+    }
+}
+
+// A set is taken as sparse by its mean: candidates of a full stencil, n (2 R + 1)^3 / cells, up to
+// 64 (beyond, more and more particles are left to the wave), and enough particles that a lane
+// each still gives the chip two waves a SIMD (100 000 particles, 0.3 neighbours: a wave each 0.20 ms,
+// 131 072 a lane each 0.12).
+constexpr int64_t kNbrSparseN = 1 << 17;
+static bool nbr_sparse(int64_t n, const GridDev &g) {
+    const double W = 2.0 * g.reach + 1.0;
+    return n >= kNbrSparseN && (double)n * W * W * W <= 64.0 * (double)g.nkey;
+}
+
+template <bool FILL>
+static hipError_t launch_nbr(const NbrArgs &A, hipStream_t st) {
+    if (A.n <= 0) return hipSuccess;
+    const bool sparse = nbr_sparse(A.n, A.g);
+    const int64_t per = sparse ? kBlock : kNbrWaves;  // particles a workgroup
+    const unsigned nb = (unsigned)((A.n + per - 1) / per);
+#define CSPH_NBR(P, X)                                            \
+    if (!!A.pc.pair_mode == P && !!A.pc.per == X) {               \
+        if (sparse)                                               \
+            k_nbr_sparse<P, FILL, X><<<nb, kBlock, 0, st>>>(A);   \
+        else                                                      \
+            k_nbr<P, FILL, X><<<nb, kBlock, 0, st>>>(A);          \
+    }
     CSPH_NBR(false, false)
     CSPH_NBR(true, false)
     CSPH_NBR(false, true)
@@ -263,22 +371,18 @@ hipError_t launch_nbr_count(int64_t n, const GridDev &g, const PairConst &pc, co
     return hipGetLastError();
 }
 
+hipError_t launch_nbr_count(int64_t n, const GridDev &g, const PairConst &pc, const double *x,
+                            const double *y, const double *z, const double *d, const int32_t *cs,
+                            const int32_t *perm, int32_t *count_orig, hipStream_t st) {
+    return launch_nbr<false>(NbrArgs{n, g, pc, x, y, z, d, cs, perm, count_orig, nullptr, nullptr},
+                             st);
+}
+
 hipError_t launch_nbr_fill(int64_t n, const GridDev &g, const PairConst &pc, const double *x,
                            const double *y, const double *z, const double *d, const int32_t *cs,
                            const int32_t *perm, const int64_t *offsets, int32_t *idx,
                            hipStream_t st) {
-    if (n <= 0) return hipSuccess;
-    const unsigned nb = (unsigned)((n + kNbrWaves - 1) / kNbrWaves);
-#define CSPH_NBR(P, X)                                                                    \
-    if (!!pc.pair_mode == P && !!pc.per == X)                                             \
-        k_nbr<P, true, X><<<nb, kBlock, 0, st>>>(n, g, pc, x, y, z, d, cs, perm, nullptr,    \
-                                                 offsets, idx);
-    CSPH_NBR(false, false)
-    CSPH_NBR(true, false)
-    CSPH_NBR(false, true)
-    CSPH_NBR(true, true)
-#undef CSPH_NBR
-    return hipGetLastError();
+    return launch_nbr<true>(NbrArgs{n, g, pc, x, y, z, d, cs, perm, nullptr, offsets, idx}, st);
 }
 
 }  // namespace csph
