@@ -95,11 +95,13 @@ __global__ __launch_bounds__(kBlock) void k_pack(int64_t n, SrcState src,
             ((float4 *)recB)[s] = make_float4((float)vx, (float)vy, (float)vz, (float)P);
             ((float4 *)recC)[s] = make_float4((float)Z, (float)c, (float)V, 0.0f);
         } else {
-            // arrays of 16 bytes a record: (x y), (z V), (vx vy), (vz P), (Z c)
-            ((double2 *)recA)[s] = make_double2(x, y);
-            ((double2 *)recA)[n + s] = make_double2(z, V);
-            ((double2 *)recB)[s] = make_double2(vx, vy);
-            ((double2 *)recB)[n + s] = make_double2(vz, P);
+            // arrays of 16 bytes a record: (x y), (z V), (vx vy), (vz P), (Z c); the first four
+            // as records of 32 bytes for list walks (Whole4)
+            const int64_t lo = perm ? s : 2 * s, hi = perm ? n + s : 2 * s + 1;
+            ((double2 *)recA)[lo] = make_double2(x, y);
+            ((double2 *)recA)[hi] = make_double2(z, V);
+            ((double2 *)recB)[lo] = make_double2(vx, vy);
+            ((double2 *)recB)[hi] = make_double2(vz, P);
             ((double2 *)recC)[s] = make_double2(Z, c);
         }
     }
@@ -244,9 +246,9 @@ constexpr int kUS64 = 3;
 constexpr int kPop64 = 2;
 static_assert(kUS64 - 1 <= kRecPad, "the stencil walk reads up to kUS64 - 1 records past a row");
 
-template <bool PAIR, bool WALL, bool PER, bool SPLIT>
+template <bool PAIR, bool WALL, bool LIST, bool PER, bool SPLIT>
 struct Rates64 {
-    Split4 A, B;                   // x y z V, vx vy vz P
+    typename Rec4<LIST>::type A, B;  // x y z V, vx vy vz P
     const double2 *__restrict__ Cz;
     const float4 *__restrict__ F;  // stencil walks: cell-relative FP32 records (the test)
     const double *__restrict__ dsz;
@@ -273,8 +275,9 @@ struct Rates64 {
     Stencil tm;
     float amx = 0.f, amy = 0.f, amz = 0.f, cxm = 0.f;
     double ar = 0.0, avx = 0.0, avy = 0.0, avz = 0.0, aE = 0.0, sig = 0.0;
-    // ring counters in entries; an entry is the partner's 16-byte record offset, bit 0 set for
-    // a mirror image, bits 1-3 the periodic image mask.  cnt: the exact members popped, |N(i)|
+    // ring counters in entries; an entry is the partner's 16-byte record offset (a list walk's:
+    // 32-byte), bit 0 set for a mirror image, bits 1-3 the periodic image mask.  cnt: the exact
+    // members popped, |N(i)|
     int qw = 0, qr = 0, cnt = 0;
     int sub = 0, ls = 0;  // SPLIT: the lane's share of i, log2 of the lanes per particle
     int2 *lay;            // few_images: the wave's layout
@@ -292,13 +295,13 @@ struct Rates64 {
         const uint32_t e = LISTED ? *(const uint32_t *)(qb + list + (has ? qr - q0 : 0) * 4)
                                   : slot(qr);
         qr += has ? 1 : 0;
-        const uint32_t jo = has ? (MIR ? e & ~15u : e) : 0u;
+        const uint32_t jo = has ? (MIR ? e & (LIST ? ~31u : ~15u) : e) : 0u;
         const bool ghost = MIR && (e & 1u);
         const int mm = PER && MIR ? (int)((e >> 1) & 7u) : 0;
-        const int j = (int)(jo >> 4);
+        const int j = (int)(jo >> (LIST ? 5 : 4));
         const double4 aj = A.at(jo);
         const double4 bj = B.at(jo);
-        const double2 zj = *(const double2 *)((const char *)Cz + jo);
+        const double2 zj = *(const double2 *)((const char *)Cz + (LIST ? jo >> 1 : jo));
         const double yj = ghost ? 2.0 * yw - aj.y : aj.y;
         double dx = aj.x - a.x, dy = yj - a.y, dz = aj.z - a.z;
         if (PER) {  // image mm: d = (x_j - x_i) - k L
@@ -460,7 +463,7 @@ struct Rates64 {
     // The whole walk: a Verlet list, or the stencil (and, for a wave with particles in the
     // wall band, the stencil around their images; for a wave with particles near periodic
     // faces, the stencils around their periodic images); every pop drained.  Returns |N(i)|.
-    template <bool LIST, bool ZS>
+    template <bool ZS>
     __device__ __forceinline__ int run(const int32_t *__restrict__ lst, int len, int64_t nl) {
         const bool anyw = WALL && __any(near_wall);
         if (LIST) {
@@ -498,7 +501,7 @@ struct Rates64 {
             int e[kU] = {k < len ? ee.x : 0, k + 1 < len ? ee.y : 0};
             double4 aj[kU];
 #pragma unroll
-            for (int u = 0; u < kU; ++u) aj[u] = A.at((uint32_t)e[u] << 4);
+            for (int u = 0; u < kU; ++u) aj[u] = A.at((uint32_t)e[u] << 5);
 #pragma unroll
             for (int u = 0; u < kU; ++u) {
                 const bool ghost = WALL && e[u] < 0;
@@ -508,7 +511,7 @@ struct Rates64 {
                 const bool acc = (k + u < len) && r2 < pc.H2;
                 // list entries carry the mirror flag in the sign bit
                 const uint32_t eu = (uint32_t)e[u];
-                slot(qw) = WALL ? (eu << 4) | (eu >> 31) : eu << 4;
+                slot(qw) = WALL ? (eu << 5) | (eu >> 31) : eu << 5;
                 qw += acc ? 1 : 0;
             }
             k += kU;
@@ -520,7 +523,9 @@ struct Rates64 {
 // kernel would spill at the 96 VGPRs of 5 waves (measured 9.22 against 7.72 ms on the porous
 // shock's first 20 steps).
 template <bool PAIR, bool WALL, bool LIST, bool PER, bool SPLIT>
-__global__ __launch_bounds__(kRate64Block, 4) void k_rates64(int64_t n, Split4 A, Split4 B,
+__global__ __launch_bounds__(kRate64Block, 4) void k_rates64(int64_t n,
+                                                    typename Rec4<LIST>::type A,
+                                                    typename Rec4<LIST>::type B,
                                                     const double2 *__restrict__ Cz,
                                                     const float4 *__restrict__ F,
                                                     const double *__restrict__ rho,
@@ -535,7 +540,7 @@ __global__ __launch_bounds__(kRate64Block, 4) void k_rates64(int64_t n, Split4 A
     __shared__ int qj[kQ][kRate64Block];
     constexpr bool few = PER && !SPLIT && !WALL;
     __shared__ int2 lay[few ? kRate64Block / 64 : 1][few ? kLay : 1];
-    Rates64<PAIR, WALL, PER, SPLIT> k;
+    Rates64<PAIR, WALL, LIST, PER, SPLIT> k;
     k.qb = (char *)&qj[0][0];
     k.lay = lay[few ? threadIdx.x >> 6 : 0];
     k.d32 = d32;
@@ -591,8 +596,8 @@ __global__ __launch_bounds__(kRate64Block, 4) void k_rates64(int64_t n, Split4 A
     if (PER && k.live) k.nf = image_faces(pc, k.a.x, k.a.y, k.a.z);
     const int len = LIST && k.live ? min(vl.count[s], vl.cap) : 0;
     const int32_t *lst = LIST ? vl.idx + (k.live ? s * kVlChunk : 0) : nullptr;
-    int cnt = *o.zflag == 0 ? k.template run<LIST, true>(lst, len, n)
-                            : k.template run<LIST, false>(lst, len, n);
+    int cnt = *o.zflag == 0 ? k.template run<true>(lst, len, n)
+                            : k.template run<false>(lst, len, n);
     if (SPLIT) {
         k.ar = split_sum(k.ar, ls);
         k.avx = split_sum(k.avx, ls);
@@ -1106,9 +1111,10 @@ static hipError_t rates_out(int64_t n, int mixed, const GridDev &g, const PairCo
     const bool pair = pc.pair_mode != 0, wall = pc.wall != 0, list = vl.idx != nullptr;
     const bool per = pc.per != 0;
     if (list && (pair || per)) return hipErrorInvalidValue;
-#define CSPH_RATES64_ARGS                                                                     \
-    n, split4(w.recA, n), split4(w.recB, n), (const double2 *)w.recC, (const float4 *)w.recF, \
-        rho_sorted, d_sorted, (const float *)w.rank, w.cs, g, pc, t_dev, t_host, o, want_dt, vl, ls
+#define CSPH_RATES64_ARGS(L)                                                                  \
+    n, Rec4<L>::make(w.recA, n), Rec4<L>::make(w.recB, n), (const double2 *)w.recC,           \
+        (const float4 *)w.recF, rho_sorted, d_sorted, (const float *)w.rank, w.cs, g, pc,     \
+        t_dev, t_host, o, want_dt, vl, ls
 #define CSPH_RATES_CASE(P, W, L, X)                                                           \
     if (pair == P && wall == W && list == L && per == X) {                                    \
         if (mixed)                                                                            \
@@ -1118,9 +1124,10 @@ static hipError_t rates_out(int64_t n, int mixed, const GridDev &g, const PairCo
                 w.cs, g, pc, t_dev,                                                           \
                 t_host, o, want_dt, vl);                                                      \
         else if (ls > 0 && !L)                                                                \
-            k_rates64<P, W, false, X, true><<<nb64, kRate64Block, 0, st>>>(CSPH_RATES64_ARGS); \
+            k_rates64<P, W, false, X, true>                                                   \
+                <<<nb64, kRate64Block, 0, st>>>(CSPH_RATES64_ARGS(false));                    \
         else                                                                                  \
-            k_rates64<P, W, L, X, false><<<nb64, kRate64Block, 0, st>>>(CSPH_RATES64_ARGS);   \
+            k_rates64<P, W, L, X, false><<<nb64, kRate64Block, 0, st>>>(CSPH_RATES64_ARGS(L)); \
     }
     CSPH_RATES_CASE(false, false, false, false)
     CSPH_RATES_CASE(false, true, false, false)
