@@ -285,8 +285,9 @@ __global__ __launch_bounds__(kBlock) void k_scan_tops(int64_t *__restrict__ tile
 constexpr int64_t kOwnTiles = 1024;
 
 // sums: every workgroup adds up the sums of the tiles before its own (up to kOwnTiles of
-// them), which leaves out the launch that scans them.  vec: in and out are 16-byte aligned 32-bit arrays; a thread's kScanItems = 8 values then move
-// as two 16-byte loads and stores (the tail tile goes element by element).
+// them), which leaves out the launch that scans them.  vec: in and out are 16-byte aligned 32-bit
+// arrays; a thread's kScanItems = 8 values then move as two 16-byte loads and stores (the tail
+// tile goes element by element).
 template <typename TI, typename TO>
 __global__ __launch_bounds__(kBlock) void k_scan_apply(const TI *in, TO *out, int64_t len,
                                                        const int64_t *__restrict__ tile_off,
@@ -357,12 +358,6 @@ template hipError_t launch_scan_exclusive<int32_t, int64_t>(const int32_t *, int
                                                             int64_t *, hipStream_t);
 
 // ---------------------------------------------------------------- counting sort by cell
-
-__global__ __launch_bounds__(kBlock) void k_fill_i32(int32_t *p, int32_t v, int64_t count) {
-    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < count;
-         i += (int64_t)gridDim.x * kBlock)
-        p[i] = v;
-}
 
 // The histogram cleared, and the caller's words set.
 __global__ __launch_bounds__(kBlock) void k_clear(int32_t *p, int64_t count, ClearWords w) {

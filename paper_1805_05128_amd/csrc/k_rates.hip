@@ -135,10 +135,11 @@ hipError_t launch_pack(const csph_state &s, int64_t n, const int32_t *perm, cons
 
 // ---------------------------------------------------------------- wave min -> global
 
-// The FP32 rate kernel runs one wave per workgroup: its occupancy is bound by the LDS rings,
-// and a wave's ring is released as soon as the wave ends (partner counts, hence wave run
-// times, vary widely; a larger workgroup holds its rings until its slowest wave ends).  The
-// FP64 kernel's occupancy is bound by registers; it keeps four-wave workgroups.
+// The FP32 rate kernel runs one wave per workgroup: a wave's registers and ring are released as
+// soon as it ends (partner counts, hence wave run times, vary widely; a larger workgroup holds its
+// slots until its slowest wave ends).  Both kernels' occupancy is bound by registers: 94 to 121
+// VGPRs, five waves a SIMD without walls and periodic sides and four with them (the rings would
+// allow five); the FP64 kernel, four waves, keeps four-wave workgroups.
 constexpr int kRate32Block = 64;
 constexpr int kSlot = kRate32Block * (int)sizeof(float4);  // bytes per ring row
 constexpr int kRing = kQ * kSlot;                        // bytes per wave's rings
@@ -147,10 +148,11 @@ constexpr int kSlot64 = kRate64Block * (int)sizeof(int);  // FP64 kernel: bytes 
 // most workgroups per die chunk (xcd_block_upto; measured on the porous shock's 100 steps,
 // where the wall band's costly waves made one die the last to finish): ~131 k / ~65 k
 // particles, fewer in launches too small for four rounds of such chunks.  The
-// FP32 kernel's 2 048-wave chunks read 1.86 GB per launch beyond L2 (512: 2.31 GB, 1 024:
-// 2.01 GB) in the same time; 4 096 leaves an eighth of the waves outside the whole rounds of
-// chunks, unmapped, and reads 4.1 GB.  The FP64 kernel's 256 four-wave groups read 3.51 GB
-// (64: 4.73 GB, 512: 3.22 GB), again in the same time.
+// FP32 kernel's 2 048-wave chunks read 1.77 GB per launch beyond L2; sizes measured side by side on
+// an earlier form of the kernel, all in the same time: 512 2.31 GB, 1 024 2.01 GB, 2 048 1.86 GB.
+// 4 096 leaves an eighth of the waves outside the whole rounds of chunks, unmapped, and reads
+// 4.1 GB.  The FP64 kernel's 256 four-wave groups read 3.61 GB; side by side on an earlier form,
+// again in the same time: 64 4.73 GB, 256 3.51 GB, 512 3.22 GB.
 constexpr unsigned kRate32Chunk = 2048;
 constexpr unsigned kRate64Chunk = 256;
 

@@ -94,8 +94,9 @@ __device__ __forceinline__ double wrap_axis(const PerDev &p, int a, double v) {
 
 // The workgroup's five double-double sums in a fixed tree (pairs 128, 64, 32, .. 1 apart):
 // wave k % 4 adds up sum k, the last six levels between its lanes, so that one barrier replaces
-// eight; out(k, sum) in lane 0 of that wave.  Every thread's values are in LDS, and what it did
-// before is seen by the workgroup, once the barrier is passed.
+// eight; out(k, sum) in lane 0 of that wave.  The barrier follows all that the workgroup did
+// before the call; none follows the sums, so on return other waves may still read their LDS: a
+// second call, or another use of it, needs a barrier of its own.
 template <typename F>
 __device__ __forceinline__ void block_dd_sums(const DD acc[5], F &&out) {
     __shared__ double sh[2][5][kBlock];
@@ -244,7 +245,7 @@ __global__ __launch_bounds__(kBlock) void k_integrate(int64_t n, State9 s, Rates
         for (int o = 32; o > 0; o >>= 1) npairs += __shfl_xor(npairs, o, 64);
         if ((threadIdx.x & 63) == 0 && npairs) atomicAdd(lg.pairs, npairs);
     }
-    if (VORO) {  // the reduction above ended with a barrier: every count is in LDS
+    if (VORO) {  // the barrier inside the sums above followed every count
         for (int k = threadIdx.x; k < vo.K; k += kBlock) {
             if (hp[k]) atomicAdd(&vo.site_part[k], (unsigned long long)hp[k]);
             if (hq[k] && vo.site_pairs) atomicAdd(&vo.site_pairs[k], hq[k]);
