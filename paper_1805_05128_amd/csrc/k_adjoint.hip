@@ -1006,7 +1006,8 @@ hipError_t launch_dt_adjoint(int64_t n, const int32_t *perm, double *const sorte
 // then the mirror walks for the workgroups holding wall-band particles, added to its outputs
 // (the epilogue is linear in the walks' sums, so the two launches give the one-walk gather's
 // result up to the order of the additions).  The wall's walks and state take some 60 more
-// VGPRs, which in one kernel would hold every workgroup to two waves per SIMD instead of three.
+// VGPRs, which in one kernel would hold every workgroup to two waves per SIMD instead of four
+// (three with periodic sides).
 static void vjp_gather(unsigned nb, int ls, int64_t n, const VjpIn &in, const VjpOut &o,
                        const int32_t *perm, const int32_t *cs, const GridDev &g,
                        const PairConst &pc, const EosDev &eos, bool wall, const VjpWall &wl,

@@ -7,7 +7,7 @@
 // generators whose lower bound does not exceed the smallest upper bound are scanned, in the
 // same order and by the same expressions, so the argmin and its ties are the full scan's.
 // 2.9 M particles and 64 generators: ownership with counts 82 -> 53 us (its 93 MB take 17 us at
-// 5.5 TB/s; the rest is the wave's bounds and sums), the balancer's statistics 448 -> 97 us.
+// 5.5 TB/s; the rest is the wave's bounds and sums), the balancer's statistics 448 -> 85 us.
 #pragma once
 
 #include "csph_internal.h"
